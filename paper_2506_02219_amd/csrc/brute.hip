@@ -1,203 +1,278 @@
-// Exact evaluation of Eq. (1), F(q_j) = sum_i m_i f(p_i, q_j), by tiling the
-// sources through LDS (each workgroup stages a tile of sources once and every
-// lane reuses it for its own queries).  The float64 variant computes every
-// term and the sum in double and provides the reference values; the float32
-// variants are the GPU brute-force comparator.
+// Exact evaluation of Eq. (1), F(q_j) = sum_i m_i f(p_i, q_j).  The float64
+// variant computes every term and the sum in double and provides the
+// reference values; the float32 variant is the GPU brute-force comparator.
 //
-// The smooth-distance sum is accumulated relative to the nearest source seen
-// so far (s = sum w exp(-alpha (r - rmin))), rescaling s when rmin drops, so
-// that it neither underflows nor overflows; the result is
-// rmin - log(s) / alpha.
+// A workgroup of 16 wavefronts owns 64 U queries (U per lane), and every
+// wavefront sums its own share of the sources for all of them: tiles of 64
+// consecutive sources, tile t to wavefront t mod 16, staged in the
+// wavefront's own part of LDS and read back as broadcast loads, so that the
+// main loop has no workgroup barrier.  The sixteen partial sums are added in
+// wavefront order at the end.  The shares do not depend on U or on the
+// launch, and neither does the result.
+//
+// The arithmetic bounds it (vector issue).  Splitting the sources inside the
+// workgroup is what fills the chip for the query counts of an error
+// measurement: 16,384 queries against 2^20 sources are 256 workgroups of 16
+// wavefronts, where one query per lane and all sources per lane (the former
+// kernel) gave 64 workgroups of four.  U is the largest of 4, 2, 1 that still
+// leaves a workgroup for each of the 256 compute units: more queries per lane
+// mean fewer LDS reads per term (the smooth distance stops at 2: its groups of
+// sources fill the registers, 27.6 against 26.8 ms in float64 for 2^14 sources
+// x 10^6 queries with 4).  Measured, one query per lane and a correctly rounded
+// square root and division before -> now, 2^18 sources x 2^14 queries: float64
+// potential 27.5 -> 2.2 ms, winding 42.7 -> 3.7, smooth distance 47.5 -> 6.9;
+// float32 23.8 -> 1.04, 42.7 -> 1.86, 42.7 -> 4.2.  2^20 x 2^14, float64
+// potential: 110.8 -> 9.0 ms, 1.9e12 terms/s, about 20 issue slots a term
+// against the 3.9e13 lane operations a second of the chip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "sbh_internal.hpp"
 
 namespace sbh {
 
-constexpr int kBruteThreads = 256;
+constexpr int kBruteWaves = 16;
+constexpr int kBruteThreads = 64 * kBruteWaves;
+constexpr int kBruteCUs = 256;   // compute units of an MI355X
+constexpr int kSmGroup = 4;      // sources of the smooth distance taken together
 
-template <int K, typename R>
-__device__ __forceinline__ void brute_accumulate(R px, R py, R pz, R w, R nx, R ny, R nz, R qx, R qy, R qz, R eps2,
-                                                 R alpha, R& acc, R& rmin)
+template <typename R>
+struct alignas(16) Vec4 {
+    R x, y, z, w;
+};
+
+// x^(-1/2), x > 0 (Z: or x = 0, which gives infinity).  float64: the hardware
+// approximation (relative error below 2^-20) and one third-order correction,
+// y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2, whose remainder is below 2^-60;
+// roundings leave about one unit in the last place, as a correctly rounded
+// square root followed by a division does, in six operations.
+template <bool Z>
+__device__ __forceinline__ double rsqrt_r(double x)
 {
-    const R dx = px - qx, dy = py - qy, dz = pz - qz;
-    const R r2 = dx * dx + dy * dy + dz * dz;
-    if constexpr (K == SBH_POTENTIAL) {
-        acc += w / sqrt(r2 + eps2);
-    } else if constexpr (K == SBH_WINDING) {
-        if (r2 > R(0)) {
-            const R r = sqrt(r2);
-            acc += (nx * dx + ny * dy + nz * dz) / (R(4.0 * M_PI) * r2 * r);
-        }
-    } else {
-        const R r = sqrt(r2);
-        if (r < rmin) {
-            acc = acc * exp(-alpha * (rmin - r)) + w;
-            rmin = r;
-        } else {
-            acc += w * exp(-alpha * (r - rmin));
-        }
-    }
+    const double y = __builtin_amdgcn_rsq(x);
+    double e = fma(-x * y, y, 1.0);
+    if constexpr (Z) e = fmin(e, 0.5);   // x = 0: y is infinite and e NaN, of which fmin keeps 0.5
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+template <bool Z>
+__device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
+
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
+
+// one wavefront's LDS stores become visible to its own loads (and the other way round)
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int K, typename R>
+// Z: the potential's eps is 0, so a source at the query gives an infinite term.
+// The smooth-distance sum is kept relative to the nearest source seen so far
+// (s = sum w exp(-alpha (r - rmin))), so that it neither underflows nor
+// overflows; the result is rmin - log(s) / alpha.  Sources are taken kSmGroup
+// at a time (one test for a nearer source each); rmin starts at the smallest
+// distance of the wavefront's first tile, so that the rescaling of s at a
+// nearer source is seldom reached.
+template <int K, typename R, int U, bool Z>
 __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict__ src, const float* __restrict__ w,
                                                          const float* __restrict__ nrm, int64_t n,
                                                          const float* __restrict__ queries, int64_t nq, R eps2,
                                                          R alpha, R* __restrict__ out)
 {
-    constexpr int NW = (K == SBH_WINDING) ? kBruteThreads : 1;
-    __shared__ R sx[kBruteThreads], sy[kBruteThreads], sz[kBruteThreads], sw[kBruteThreads];
-    __shared__ R snx[NW], sny[NW], snz[NW];
-    const int64_t j = (int64_t)blockIdx.x * kBruteThreads + threadIdx.x;
-    const bool valid = j < nq;
-    R qx = 0, qy = 0, qz = 0;
-    if (valid) {
-        qx = queries[3 * j];
-        qy = queries[3 * j + 1];
-        qz = queries[3 * j + 2];
-    }
-    R total = 0, rmin = R(INFINITY);
-    for (int64_t t0 = 0; t0 < n; t0 += kBruteThreads) {
-        const int64_t i = t0 + threadIdx.x;
-        if (i < n) {
-            sx[threadIdx.x] = (R)src[3 * i];
-            sy[threadIdx.x] = (R)src[3 * i + 1];
-            sz[threadIdx.x] = (R)src[3 * i + 2];
-            sw[threadIdx.x] = (R)w[i];
-            if constexpr (K == SBH_WINDING) {
-                snx[threadIdx.x] = (R)w[i] * (R)nrm[3 * i];
-                sny[threadIdx.x] = (R)w[i] * (R)nrm[3 * i + 1];
-                snz[threadIdx.x] = (R)w[i] * (R)nrm[3 * i + 2];
-            }
-        }
-        __syncthreads();
-        const int cnt = (int)((n - t0) < kBruteThreads ? (n - t0) : kBruteThreads);
-        R acc = (K == SBH_SMOOTHDIST) ? total : R(0);
-        for (int k = 0; k < cnt; ++k) {
-            R nx = 0, ny = 0, nz = 0;
-            if constexpr (K == SBH_WINDING) {
-                nx = snx[k];
-                ny = sny[k];
-                nz = snz[k];
-            }
-            brute_accumulate<K, R>(sx[k], sy[k], sz[k], sw[k], nx, ny, nz, qx, qy, qz, eps2, alpha, acc, rmin);
-        }
-        if constexpr (K == SBH_SMOOTHDIST) total = acc;
-        else total += acc;  // per-tile partial sums
-        __syncthreads();
-    }
-    if (valid) {
-        R v = total;
-        if constexpr (K == SBH_SMOOTHDIST) v = rmin - log(total) / alpha;
-        // a query with a non-finite coordinate has no defined value
-        const bool fin = __builtin_isfinite(qx) && __builtin_isfinite(qy) && __builtin_isfinite(qz);
-        out[j] = fin ? v : R(NAN);
-    }
-}
-
-// The float32 comparator for the potential and the winding number: a tile of
-// 256 sources staged in LDS as (x, y, z, w) (and w n for the dipoles), read
-// back as one broadcast 16-byte load per source, and kQPL queries per lane, so
-// that a workgroup streams the sources once for 256 kQPL queries and every LDS
-// read feeds kQPL terms.  A term is three differences, the squared distance
-// with eps^2 folded in (three fused multiply-adds), the hardware reciprocal
-// square root and the weighted accumulation.
-constexpr int kQPL = 4;
-
-template <int K>
-__global__ void __launch_bounds__(kBruteThreads) k_brute32(const float* __restrict__ src, const float* __restrict__ w,
-                                                           const float* __restrict__ nrm, int64_t n,
-                                                           const float* __restrict__ queries, int64_t nq, float eps2,
-                                                           float* __restrict__ out)
-{
-    static_assert(K == SBH_POTENTIAL || K == SBH_WINDING, "the smooth distance keeps its rescaling kernel");
-    __shared__ float4 sp[kBruteThreads];
-    __shared__ float4 sd[K == SBH_WINDING ? kBruteThreads : 1];
-    const int64_t j0 = (int64_t)blockIdx.x * (kBruteThreads * kQPL) + threadIdx.x;
-    float qx[kQPL], qy[kQPL], qz[kQPL], total[kQPL];
+    constexpr bool WN = K == SBH_WINDING, SM = K == SBH_SMOOTHDIST;
+    // Sources a loop iteration.  The float32 winding number issues faster one by one (5.5 against 6.7 ms
+    // for 2^14 sources x 10^6 queries): unrolled, the compiler sends every term's comparison through
+    // the one vcc register.
+    constexpr int kUnroll = WN && std::is_same_v<R, float> ? 1 : 4;
+    __shared__ Vec4<R> tile[kBruteWaves][64];
+    __shared__ Vec4<R> tdip[WN ? kBruteWaves : 1][WN ? 64 : 1];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j0 = (int64_t)blockIdx.x * (64 * U) + lane;
+    R qx[U], qy[U], qz[U], total[U], rmin[U];
 #pragma unroll
-    for (int u = 0; u < kQPL; ++u) {
-        const int64_t j = j0 + (int64_t)u * kBruteThreads;
+    for (int u = 0; u < U; ++u) {
+        const int64_t j = j0 + 64 * u;
         const bool valid = j < nq;
-        qx[u] = valid ? queries[3 * j] : 0.0f;
-        qy[u] = valid ? queries[3 * j + 1] : 0.0f;
-        qz[u] = valid ? queries[3 * j + 2] : 0.0f;
-        total[u] = 0.0f;
+        qx[u] = valid ? (R)queries[3 * j] : R(0);
+        qy[u] = valid ? (R)queries[3 * j + 1] : R(0);
+        qz[u] = valid ? (R)queries[3 * j + 2] : R(0);
+        total[u] = R(0);
+        rmin[u] = R(INFINITY);
     }
-    for (int64_t t0 = 0; t0 < n; t0 += kBruteThreads) {
-        const int64_t i = t0 + threadIdx.x;
-        if (i < n) {
-            const float wi = w[i];
-            sp[threadIdx.x] = make_float4(src[3 * i], src[3 * i + 1], src[3 * i + 2], wi);
-            if constexpr (K == SBH_WINDING)
-                sd[threadIdx.x] = make_float4(wi * nrm[3 * i], wi * nrm[3 * i + 1], wi * nrm[3 * i + 2], 0.0f);
+    // the wavefront's next tile travels in registers while the current one is summed
+    float gx = 0.f, gy = 0.f, gz = 0.f, gw = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
+    auto load = [&](int64_t t0) {
+        const int64_t i = t0 + lane;
+        if (i >= n) return;
+        gx = src[3 * i];
+        gy = src[3 * i + 1];
+        gz = src[3 * i + 2];
+        gw = w[i];
+        if constexpr (WN) {
+            hx = nrm[3 * i];
+            hy = nrm[3 * i + 1];
+            hz = nrm[3 * i + 2];
         }
-        __syncthreads();
-        const int cnt = (int)((n - t0) < kBruteThreads ? (n - t0) : kBruteThreads);
-        float acc[kQPL];   // the tile's partial sums, added to the totals after the tile
+    };
+    constexpr int64_t kStride = 64 * kBruteWaves;
+    int64_t t0 = (int64_t)wv * 64;
+    load(t0);
+    for (; t0 < n; t0 += kStride) {
+        // (the smooth distance takes whole groups of sources: lanes past the end hold one infinitely far away)
+        if (SM && t0 + lane >= n) tile[wv][lane] = {R(INFINITY), R(0), R(0), R(0)};
+        else tile[wv][lane] = {(R)gx, (R)gy, (R)gz, (R)gw};
+        if constexpr (WN) tdip[wv][lane] = {(R)gw * (R)hx, (R)gw * (R)hy, (R)gw * (R)hz, R(0)};
+        load(t0 + kStride);
+        wave_lds_fence();
+        const int cnt = (int)((n - t0) < 64 ? (n - t0) : 64);
+        if (SM && t0 == (int64_t)wv * 64) {   // the first tile's smallest distance
+            for (int k = 0; k < cnt; ++k) {
+                const Vec4<R> p = tile[wv][k];
 #pragma unroll
-        for (int u = 0; u < kQPL; ++u) acc[u] = 0.0f;
+                for (int u = 0; u < U; ++u) {
+                    const R dx = p.x - qx[u], dy = p.y - qy[u], dz = p.z - qz[u];
+                    const R r2 = fma_r(dz, dz, fma_r(dy, dy, dx * dx));
+                    rmin[u] = r2 < rmin[u] ? r2 : rmin[u];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) rmin[u] = sqrt(rmin[u]);
+        }
+        R acc[U];   // the tile's partial sums, added to the totals after the tile
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = R(0);
+        if constexpr (SM) {
+            for (int k = 0; k < cnt; k += kSmGroup) {
+                R r[kSmGroup][U], pw[kSmGroup];
+#pragma unroll
+                for (int i = 0; i < kSmGroup; ++i) {
+                    const Vec4<R> p = tile[wv][k + i];
+                    pw[i] = p.w;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const R dx = p.x - qx[u], dy = p.y - qy[u], dz = p.z - qz[u];
+                        r[i][u] = sqrt(fma_r(dz, dz, fma_r(dy, dy, dx * dx)));
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    R m = r[0][u];
+#pragma unroll
+                    for (int i = 1; i < kSmGroup; ++i) m = fmin(m, r[i][u]);
+                    if (m < rmin[u]) {   // a nearer source: the sums so far move to its distance
+                        const R f = exp(-alpha * (rmin[u] - m));
+                        total[u] *= f;
+                        acc[u] *= f;
+                        rmin[u] = m;
+                    }
+#pragma unroll
+                    for (int i = 0; i < kSmGroup; ++i) acc[u] = fma_r(pw[i], exp(-alpha * (r[i][u] - rmin[u])), acc[u]);
+                }
+            }
+        } else
+#pragma unroll kUnroll
         for (int k = 0; k < cnt; ++k) {
-            const float4 p = sp[k];
-            float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (K == SBH_WINDING) m = sd[k];
+            const Vec4<R> p = tile[wv][k];
+            Vec4<R> m{};
+            if constexpr (WN) m = tdip[wv][k];
 #pragma unroll
-            for (int u = 0; u < kQPL; ++u) {
-                const float dx = p.x - qx[u], dy = p.y - qy[u], dz = p.z - qz[u];
+            for (int u = 0; u < U; ++u) {
+                const R dx = p.x - qx[u], dy = p.y - qy[u], dz = p.z - qz[u];
                 if constexpr (K == SBH_POTENTIAL) {
-                    const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, eps2)));
-                    acc[u] = fmaf(p.w, __builtin_amdgcn_rsqf(r2), acc[u]);
+                    const R r2 = fma_r(dz, dz, fma_r(dy, dy, fma_r(dx, dx, eps2)));
+                    acc[u] = fma_r(p.w, rsqrt_r<Z>(r2), acc[u]);
                 } else {
-                    // (n . d) / (4 pi |d|^3); a source at the query itself adds nothing
-                    const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                    const float ir = __builtin_amdgcn_rsqf(r2);
-                    const float v = fmaf(m.z, dz, fmaf(m.y, dy, m.x * dx)) * (ir * ir * ir);
-                    acc[u] += r2 > 0.0f ? v : 0.0f;
+                    // (n . d) / (4 pi |d|^3), the constant at the end; a source at the query itself adds nothing
+                    const R r2 = fma_r(dz, dz, fma_r(dy, dy, dx * dx));
+                    const R ir = rsqrt_r<false>(r2);
+                    const R v = fma_r(m.z, dz, fma_r(m.y, dy, m.x * dx)) * (ir * ir * ir);
+                    acc[u] += r2 > R(0) ? v : R(0);
                 }
             }
         }
 #pragma unroll
-        for (int u = 0; u < kQPL; ++u) total[u] += acc[u];
-        __syncthreads();
+        for (int u = 0; u < U; ++u) total[u] += acc[u];
+        wave_lds_fence();   // the tile is overwritten next
     }
+    // the wavefronts' partial sums in wavefront order (each wavefront's tile holds its U x 64 values)
+    static_assert(U <= 4, "a wavefront's tile must hold its partial sums");
+    R* part = reinterpret_cast<R*>(&tile[wv][0]);
 #pragma unroll
-    for (int u = 0; u < kQPL; ++u) {
-        const int64_t j = j0 + (int64_t)u * kBruteThreads;
-        if (j >= nq) continue;
-        float v = total[u];
-        if constexpr (K == SBH_WINDING) v *= (float)(1.0 / (4.0 * M_PI));
-        // a query with a non-finite coordinate has no defined value
-        const bool fin = __builtin_isfinite(qx[u]) && __builtin_isfinite(qy[u]) && __builtin_isfinite(qz[u]);
-        out[j] = fin ? v : NAN;
+    for (int u = 0; u < U; ++u) part[64 * u + lane] = total[u];
+    __shared__ R pmin[SM ? kBruteWaves : 1][SM ? 64 * U : 1];
+    if constexpr (SM) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) pmin[wv][64 * u + lane] = rmin[u];
     }
+    __syncthreads();
+    if (threadIdx.x >= 64 * U) return;
+    const int s = threadIdx.x;   // this thread's query of the workgroup
+    const int64_t j = (int64_t)blockIdx.x * (64 * U) + s;
+    if (j >= nq) return;
+    R sum = R(0), m = R(INFINITY);
+    if constexpr (SM) {
+        for (int v = 0; v < kBruteWaves; ++v) m = pmin[v][s] < m ? pmin[v][s] : m;
+    }
+    for (int v = 0; v < kBruteWaves; ++v) {
+        const R x = reinterpret_cast<const R*>(&tile[v][0])[s];
+        if constexpr (SM) sum += pmin[v][s] < R(INFINITY) ? x * exp(-alpha * (pmin[v][s] - m)) : R(0);
+        else sum += x;
+    }
+    if constexpr (WN) sum *= R(1.0 / (4.0 * M_PI));
+    if constexpr (SM) sum = m - log(sum) / alpha;
+    // a query with a non-finite coordinate has no defined value
+    const float x = queries[3 * j], y = queries[3 * j + 1], z = queries[3 * j + 2];
+    const bool fin = __builtin_isfinite(x) && __builtin_isfinite(y) && __builtin_isfinite(z);
+    out[j] = fin ? sum : R(NAN);
 }
 
-template <int K>
-static hipError_t launch_brute_k(const float* src, const float* w, const float* nrm, int64_t n, const float* q,
-                                 int64_t nq, float eps, float alpha, int fp64, void* out, hipStream_t s)
+template <int K, typename R, bool Z>
+static void launch_brute_u(const float* src, const float* w, const float* nrm, int64_t n, const float* q, int64_t nq,
+                           R eps2, R alpha, void* out, hipStream_t s)
 {
-    const unsigned blocks = (unsigned)((nq + kBruteThreads - 1) / kBruteThreads);
-    if (fp64) {
-        k_brute<K, double><<<blocks, kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, (double)eps * (double)eps,
-                                                            (double)alpha, (double*)out);
-    } else if constexpr (K == SBH_SMOOTHDIST) {
-        k_brute<K, float><<<blocks, kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, eps * eps, alpha, (float*)out);
-    } else {
-        const unsigned b32 = (unsigned)((nq + kBruteThreads * kQPL - 1) / (kBruteThreads * kQPL));
-        k_brute32<K><<<b32, kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, eps * eps, (float*)out);
+    const auto blocks = [&](int u) { return (unsigned)((nq + 64 * u - 1) / (64 * u)); };
+    if constexpr (K != SBH_SMOOTHDIST) {
+        if (nq >= (int64_t)64 * 4 * kBruteCUs) {
+            k_brute<K, R, 4, Z><<<blocks(4), kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, eps2, alpha, (R*)out);
+            return;
+        }
     }
+    if (nq >= (int64_t)64 * 2 * kBruteCUs)
+        k_brute<K, R, 2, Z><<<blocks(2), kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, eps2, alpha, (R*)out);
+    else
+        k_brute<K, R, 1, Z><<<blocks(1), kBruteThreads, 0, s>>>(src, w, nrm, n, q, nq, eps2, alpha, (R*)out);
+}
+
+template <int K, typename R>
+static hipError_t launch_brute_k(const float* src, const float* w, const float* nrm, int64_t n, const float* q,
+                                 int64_t nq, R eps2, R alpha, void* out, hipStream_t s)
+{
+    if constexpr (K == SBH_POTENTIAL && std::is_same_v<R, double>) {
+        if (eps2 == R(0)) {
+            launch_brute_u<K, R, true>(src, w, nrm, n, q, nq, eps2, alpha, out, s);
+            return hipGetLastError();
+        }
+    }
+    launch_brute_u<K, R, false>(src, w, nrm, n, q, nq, eps2, alpha, out, s);
     return hipGetLastError();
 }
 
 hipError_t launch_brute(const float* src, const float* w, const float* nrm, int64_t n, const float* queries,
                         int64_t nq, int kernel, float eps, float alpha, int fp64, void* out, hipStream_t s)
 {
-    if (kernel == SBH_POTENTIAL) return launch_brute_k<SBH_POTENTIAL>(src, w, nrm, n, queries, nq, eps, alpha, fp64, out, s);
-    if (kernel == SBH_WINDING) return launch_brute_k<SBH_WINDING>(src, w, nrm, n, queries, nq, eps, alpha, fp64, out, s);
-    return launch_brute_k<SBH_SMOOTHDIST>(src, w, nrm, n, queries, nq, eps, alpha, fp64, out, s);
+#define SBH_BRUTE(KK)                                                                                             \
+    (fp64 ? launch_brute_k<KK, double>(src, w, nrm, n, queries, nq, (double)eps * (double)eps, (double)alpha, out, \
+                                       s)                                                                         \
+          : launch_brute_k<KK, float>(src, w, nrm, n, queries, nq, eps * eps, alpha, out, s))
+    if (kernel == SBH_POTENTIAL) return SBH_BRUTE(SBH_POTENTIAL);
+    if (kernel == SBH_WINDING) return SBH_BRUTE(SBH_WINDING);
+    return SBH_BRUTE(SBH_SMOOTHDIST);
+#undef SBH_BRUTE
 }
 
 }  // namespace sbh
