@@ -43,19 +43,8 @@ struct alignas(16) Vec4 {
     R x, y, z, w;
 };
 
-// x^(-1/2), x > 0 (Z: or x = 0, which gives infinity).  float64: the hardware
-// approximation (relative error below 2^-20) and one third-order correction,
-// y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2, whose remainder is below 2^-60;
-// roundings leave about one unit in the last place, as a correctly rounded
-// square root followed by a division does, in six operations.
 template <bool Z>
-__device__ __forceinline__ double rsqrt_r(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * y, y, 1.0);
-    if constexpr (Z) e = fmin(e, 0.5);   // x = 0: y is infinite and e NaN, of which fmin keeps 0.5
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
+__device__ __forceinline__ double rsqrt_r(double x) { return rsqrt64<Z>(x); }
 template <bool Z>
 __device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
 

@@ -157,6 +157,19 @@ constexpr float kInv4Pi = 0.0795774715459476679f;
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// x^(-1/2), x > 0 (Z: or x = 0, which gives infinity).  float64: the hardware
+// approximation (relative error below 2^-20) and one third-order correction,
+// y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2, whose remainder is below 2^-60;
+// roundings leave about one unit in the last place, as a correctly rounded
+// square root followed by a division does, in six operations.
+template <bool Z>
+__device__ __forceinline__ double rsqrt64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double e = fma(-x * y, y, 1.0);
+    if constexpr (Z) e = fmin(e, 0.5);   // x = 0: y is infinite and e NaN, of which fmin keeps 0.5
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 // The evaluation code is compiled with floating-point contraction off and
 // explicit fmaf where a fused multiply-add is wanted, so that a value is the
 // same in every kernel that inlines it (single-tree and batched launches
