@@ -161,8 +161,11 @@ typedef struct sbh_tree_desc {      /* host copy of a tree's sizes */
  *   free(ptr, bytes, stream, ctx) returns an allocation; work that reads it
  *     has been enqueued on `stream` before the call (or has completed when
  *     `stream` is 0 and the library has waited for the device first).
- * The default (both NULL) is hipMallocAsync / hipFreeAsync on the call's
- * stream.  A PyTorch caller can pass its caching allocator here.
+ * The default (both NULL) takes memory with hipMallocAsync on the call's
+ * stream and keeps what is freed for later calls, handed out again in stream
+ * order: at most 2 GiB per process, all of it returned when sbh_free or
+ * sbh_batch_free releases the last object that uses it.  A PyTorch caller can
+ * pass its caching allocator here.
  */
 typedef void* (*sbh_alloc_fn)(size_t bytes, hipStream_t stream, void* ctx);
 typedef void (*sbh_free_fn)(void* ptr, size_t bytes, hipStream_t stream, void* ctx);

@@ -8,9 +8,11 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <list>
 #include <mutex>
 #include <new>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "sbh_internal.hpp"
@@ -114,21 +116,153 @@ Allocator allocator_current()
     return g_alloc;
 }
 
+// The default allocator: blocks of hipMallocAsync memory, kept when they are freed and handed out again
+// in stream order.  (The pools behind hipMallocAsync unmap what is freed while the device is idle,
+// whatever their release threshold: 2.5 of the 5 ms of a 2^22-point build with its release.)  A freed block carries an
+// event recorded on the stream it was freed on; it is taken again when that event has completed, or by
+// the same stream, which waits for it (so that streams gain no dependency on one another), and for at
+// most a quarter less than its size.  Idle blocks hold at most kIdleBytes, the oldest going back to the
+// device beyond that, and all of them go back when sbh_free or sbh_batch_free releases the last block in
+// use, or when an allocation fails.  One lock guards the lists; nothing but HIP calls is made under it.
+constexpr size_t kIdleBytes = (size_t)2 << 30;
+struct Block {
+    void* p;
+    size_t bytes;
+    int device;
+    hipEvent_t freed;
+    hipStream_t stream;   // the stream of the last free (a hint: the event decides)
+};
+// (never destroyed: objects may be freed while the process ends)
+std::mutex& g_blocks_mu = *new std::mutex;
+std::unordered_map<void*, Block>& g_live = *new std::unordered_map<void*, Block>;
+std::list<Block>& g_idle = *new std::list<Block>;   // oldest first
+size_t g_idle_bytes = 0;
+
+// back to the device once the work that uses the block is done; the lock is held
+void release_block(const Block& b)
+{
+    (void)hipEventSynchronize(b.freed);
+    (void)hipEventDestroy(b.freed);
+    (void)hipFreeAsync(b.p, nullptr);
+}
+void release_idle()
+{
+    for (const Block& b : g_idle) release_block(b);
+    g_idle.clear();
+    g_idle_bytes = 0;
+}
+
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+hipError_t block_alloc(void** p, size_t bytes, hipStream_t s)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    // a few sizes per factor of two, so that trees of about the same size share blocks
+    const size_t unit = bytes >= ((size_t)16 << 20) ? (size_t)2 << 20 : bytes >= ((size_t)1 << 20) ? (size_t)256 << 10 : 4096;
+    bytes = (bytes + unit - 1) / unit * unit;
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    auto best = g_idle.end();
+    for (auto it = g_idle.begin(); it != g_idle.end(); ++it) {
+        if (it->device != dev || it->bytes < bytes || it->bytes - bytes > it->bytes / 4) continue;
+        if (best != g_idle.end() && best->bytes <= it->bytes) continue;
+        if (it->stream == s || hipEventQuery(it->freed) == hipSuccess) best = it;
+    }
+    (void)hipGetLastError();   // an event that has not completed leaves hipErrorNotReady
+    if (best != g_idle.end() && hipStreamWaitEvent(s, best->freed, 0) == hipSuccess) {
+        g_live.emplace(best->p, *best);
+        *p = best->p;
+        g_idle_bytes -= best->bytes;
+        g_idle.erase(best);
+        return hipSuccess;
+    }
+    Block b{nullptr, bytes, dev, nullptr, s};
+    e = hipMallocAsync(&b.p, bytes, s);
+    if (e != hipSuccess && !g_idle.empty()) {
+        (void)hipGetLastError();
+        release_idle();
+        (void)hipStreamSynchronize(nullptr);
+        e = hipMallocAsync(&b.p, bytes, s);
+    }
+    if (e != hipSuccess) return e;
+    *p = b.p;
+    // (without its event or its place in the list it is an ordinary allocation, freed by hipFreeAsync)
+    if (hipEventCreateWithFlags(&b.freed, hipEventDisableTiming) == hipSuccess) g_live.emplace(b.p, b);
+    return hipSuccess;
+}
+
+// false: not one of the blocks
+bool block_free(void* p, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    const auto it = g_live.find(p);
+    if (it == g_live.end()) return false;
+    Block b = it->second;
+    g_live.erase(it);
+    b.stream = s;
+    int dev = 0;
+    const bool other = s == nullptr && hipGetDevice(&dev) == hipSuccess && dev != b.device;
+    if (other) (void)hipSetDevice(b.device);   // the null stream of the block's device
+    if (hipEventRecord(b.freed, s) == hipSuccess) {
+        g_idle.push_back(b);
+        g_idle_bytes += b.bytes;
+    } else {   // as an allocation without a block
+        (void)hipEventDestroy(b.freed);
+        (void)hipFreeAsync(p, s);
+    }
+    if (other) (void)hipSetDevice(dev);
+    while (g_idle_bytes > kIdleBytes) {
+        g_idle_bytes -= g_idle.front().bytes;
+        release_block(g_idle.front());
+        g_idle.pop_front();
+    }
+    return true;
+}
+
 hipError_t dev_alloc(const Allocator& a, void** p, size_t bytes, hipStream_t s)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 256;
-    if (!a.alloc) return hipMallocAsync(p, bytes, s);
-    *p = a.alloc(bytes, s, a.ctx);
-    return *p ? hipSuccess : hipErrorOutOfMemory;
+    if (a.alloc) {
+        *p = a.alloc(bytes, s, a.ctx);
+        return *p ? hipSuccess : hipErrorOutOfMemory;
+    }
+    if (capturing(s)) return hipMallocAsync(p, bytes, s);   // a node of the graph, freed by one too
+    try {
+        return block_alloc(p, bytes, s);
+    } catch (...) {   // host memory for the lists
+        return *p ? hipSuccess : hipErrorOutOfMemory;
+    }
 }
 
 void dev_free(const Allocator& a, void* p, size_t bytes, hipStream_t s)
 {
     if (!p) return;
     if (bytes == 0) bytes = 256;
-    if (!a.alloc) (void)hipFreeAsync(p, s);
-    else a.free(p, bytes, s, a.ctx);
+    if (a.alloc) {
+        a.free(p, bytes, s, a.ctx);
+        return;
+    }
+    bool mine = false;
+    try {
+        mine = block_free(p, s);
+    } catch (...) {   // host memory for the idle list: the block is out of the live one, and freed below
+    }
+    if (!mine) (void)hipFreeAsync(p, s);
+}
+
+// with no block in use, what is idle goes back to the device
+void dev_trim()
+{
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    if (!g_live.empty() || g_idle.empty()) return;
+    release_idle();
+    (void)hipStreamSynchronize(nullptr);   // unmaps what was released
 }
 
 }  // namespace sbh
@@ -397,6 +531,7 @@ sbh_status sbh_free(sbh_tree* tree)
     (void)hipDeviceSynchronize();
     free_impl(&tree->impl, 0);
     delete tree;
+    sbh::dev_trim();
     return SBH_OK;
 }
 
@@ -850,6 +985,7 @@ sbh_status sbh_batch_free(sbh_batch* b)
     (void)hipDeviceSynchronize();
     batch_release(b);
     delete b;
+    sbh::dev_trim();
     return SBH_OK;
 }
 
