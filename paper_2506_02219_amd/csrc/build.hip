@@ -8,15 +8,17 @@
 //   2. Morton code: cell_a = min(2^20-1, (u32) fl32(fl32(x_a - lo_a) *
 //      inv_side) * 2^20), bits of x/y/z interleaved into 60 bits;
 //   3. stable LSD radix sort of (code, index), 8-bit digits;
-//   4. levels top-down: a node at level l is a maximal run of equal
-//      (bits*l)-bit prefix; it is split iff count > leaf_size and l < max;
-//      its children are found by binary search for each digit and compacted
-//      in (parent, digit) order, which is breadth-first order;
-//   5. aggregates bottom-up (leaves from points, internal nodes from
-//      children) and packing into the per-node child blocks.
-// Levels need their node counts on the host, so the build synchronises twice
-// per level (its internal nodes, then their children); it is not part of the
-// timed evaluation.
+//   4. topology in two passes over the sorted codes.  A node at level l is a
+//      maximal run of equal (bits*l)-bit prefix; it is split iff count >
+//      leaf_size and l < max.  Which levels have a node that starts at point
+//      i, and which of those are internal, follows from the codes within
+//      leaf_size points of i alone, so the first pass counts nodes and
+//      internal nodes per level and block of points, the host reads the level
+//      totals once, and the second pass writes every node, in breadth-first
+//      order (Morton order within a level), with the leaves' aggregates;
+//   5. the internal nodes' aggregates bottom-up, written with every node's
+//      slot in its parent's child block.
+// The build synchronises once for the sizes and once at its end.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -419,187 +421,381 @@ __global__ void k_gather_points(const float* __restrict__ src, const float* __re
     }
 }
 
-// flags[i] = node i of this level is internal; also resets first/nchild
-__global__ void k_level_flags(const int32_t* __restrict__ lc, int n, int level, int leaf, int maxlev,
-                              uint32_t* __restrict__ flags, int32_t* __restrict__ lfirst,
-                              int32_t* __restrict__ lnch)
+// Level of the deepest node that holds both codes: their common leading digits
+// (60 / bits for equal codes).
+__device__ __forceinline__ int common_level(uint64_t a, uint64_t b, int bits)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    flags[i] = (lc[i] > leaf && level < maxlev) ? 1u : 0u;
-    lfirst[i] = -1;
-    lnch[i] = 0;
+    const uint64_t x = a ^ b;
+    return x == 0ull ? 60 / bits : (__clzll((long long)x) - 4) / bits;
 }
 
-__global__ void k_internal_map(const uint32_t* __restrict__ flags, const uint32_t* __restrict__ iscan, int n,
-                               int32_t* __restrict__ imap)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && flags[i]) imap[iscan[i]] = i;
-}
+// Marks of point i: the nodes that start at it are those of levels s .. e, the
+// internal ones those of levels s .. w (none when s > e).
+//   w: a node that holds the leaf_size + 1 points from i on has more than
+//      leaf_size points, so the nodes at i are internal down to the common
+//      level of codes i and i + leaf_size (and above max_level);
+//   s: one level below the deepest node that holds both i - 1 and i, if that
+//      node is internal, that is if some leaf_size + 1 consecutive points
+//      around i share its prefix.
+constexpr int kTopoLevels = 22;    // levels of a tree: at most 60 / 3 + 1 = 21
+constexpr int kTopoThreads = 256;
+constexpr int kTopoChunks = 4;     // groups of 64 consecutive points per wavefront
+constexpr int kTopoPoints = kTopoThreads * kTopoChunks;
+struct Mark {
+    int s, e, w;
+};
+__device__ __forceinline__ uint16_t pack_mark(Mark m) { return (uint16_t)(m.s | (m.e << 5) | ((m.w + 1) << 10)); }
+__device__ __forceinline__ Mark unpack_mark(uint16_t v) { return {v & 31, (v >> 5) & 31, (int)(v >> 10) - 1}; }
+constexpr uint16_t kNoNode = 31;   // s = 31, e = 0, w = -1
 
-__device__ __forceinline__ int32_t lower_bound_prefix(const uint64_t* __restrict__ codes, int32_t b, int32_t e,
-                                                      int shift, uint64_t key)
+// Marks of every point, and per block of kTopoPoints points the number of
+// nodes (channel 2 l) and internal nodes (2 l + 1) of each level that start in
+// it: counts[channel * gridDim.x + block].  One ballot per level and wavefront
+// chunk, lane l keeping level l's counts.
+__global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __restrict__ codes, int64_t n, int bits,
+                                                            int leaf, int max_level, uint16_t* __restrict__ marks,
+                                                            uint32_t* __restrict__ counts)
 {
-    while (b < e) {
-        const int32_t mid = b + ((e - b) >> 1);
-        if ((codes[mid] >> shift) < key) b = mid + 1;
-        else e = mid;
+    __shared__ int8_t win[kTopoPoints + 64];   // w of the block's points and of the leaf_size points before them
+    __shared__ uint32_t wc[kTopoThreads / 64][2][kTopoLevels];
+    const int64_t base = (int64_t)blockIdx.x * kTopoPoints;
+    for (int k = threadIdx.x; k < kTopoPoints + leaf; k += kTopoThreads) {
+        const int64_t i = base - leaf + k;
+        int w = -1;
+        if (i >= 0 && i + leaf < n) w = min(common_level(codes[i], codes[i + leaf], bits), max_level - 1);
+        win[k] = (int8_t)w;
     }
-    return b;
-}
-
-// one thread per (internal node k of this level, digit slot)
-__global__ void k_children(const int32_t* __restrict__ lb, const int32_t* __restrict__ lc,
-                           const int32_t* __restrict__ imap, int n_int, int level, int bits, int d3,
-                           const uint64_t* __restrict__ codes, uint32_t blk_off, uint32_t* __restrict__ btopo, int ts,
-                           uint32_t* __restrict__ ccount, int32_t* __restrict__ cbegin, uint32_t* __restrict__ cflag)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n_int * d3) return;
-    const int k = (int)(t / d3), dg = (int)(t % d3);
-    const int i = imap[k];
-    const int32_t b = lb[i], e = lb[i] + lc[i];
-    const int shift = 60 - bits * (level + 1);
-    const uint64_t prefix = codes[b] >> (shift + bits);
-    const uint64_t key = (prefix << bits) | (uint64_t)dg;
-    const int32_t lo = lower_bound_prefix(codes, b, e, shift, key);
-    const int32_t hi = lower_bound_prefix(codes, lo, e, shift, key + 1);
-    const uint32_t cnt = (uint32_t)(hi - lo);
-    btopo[(int64_t)(blk_off + k) * ts + dg] = cnt;
-    ccount[t] = cnt;
-    cbegin[t] = lo;
-    cflag[t] = cnt > 0 ? 1u : 0u;
-}
-
-// one thread per (internal node k, slot): emit the non-empty children into the next level
-__global__ void k_emit(const uint32_t* __restrict__ ccount, const int32_t* __restrict__ cbegin,
-                       const uint32_t* __restrict__ cscan, const int32_t* __restrict__ imap, int n_int, int d3,
-                       int32_t off_cur, int32_t off_next, uint32_t blk_off, int32_t* __restrict__ nb_next,
-                       int32_t* __restrict__ nc_next, int32_t* __restrict__ npar_next, int32_t* __restrict__ ndig_next,
-                       int32_t* __restrict__ npblk_next, int32_t* __restrict__ lfirst, int32_t* __restrict__ lnch)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n_int * d3) return;
-    const int k = (int)(t / d3), dg = (int)(t % d3);
-    const int i = imap[k];
-    const uint32_t cnt = ccount[t];
-    if (cnt > 0) {
-        const uint32_t c = cscan[t];
-        nb_next[c] = cbegin[t];
-        nc_next[c] = (int32_t)cnt;
-        npar_next[c] = off_cur + i;
-        ndig_next[c] = dg;
-        npblk_next[c] = (int32_t)(blk_off + k);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t cn = 0u, ci = 0u;
+    for (int c = 0; c < kTopoChunks; ++c) {
+        const int k = (wv * kTopoChunks + c) * 64 + lane;   // the point's place in the block
+        const int64_t i = base + k;
+        Mark m{31, 0, -1};
+        if (i < n) {
+            m.w = win[k + leaf];
+            const int up = i == 0 ? -1 : common_level(codes[i - 1], codes[i], bits);   // the parent's level
+            bool starts = i == 0;
+            if (i > 0 && up < max_level)
+                for (int t = 0; t < leaf && !starts; ++t) starts = win[k + t] >= up;   // windows from i - leaf to i - 1
+            if (starts) {
+                m.s = up + 1;
+                m.e = max(m.s, m.w + 1);
+            } else {
+                m.w = -1;
+            }
+            marks[i] = pack_mark(m);
+        }
+        for (int l = 0; l <= max_level; ++l) {
+            const uint64_t nm = __ballot(m.s <= l && l <= m.e), im = __ballot(m.s <= l && l <= m.w);
+            if (lane == l) {
+                cn += (uint32_t)__popcll(nm);
+                ci += (uint32_t)__popcll(im);
+            }
+        }
     }
-    if (dg == 0) {
-        int nch = 0;
-        for (int q = 0; q < d3; ++q) nch += ccount[(int64_t)k * d3 + q] > 0;
-        lfirst[i] = off_next + (int32_t)cscan[t];
-        lnch[i] = nch;
+    if (lane < kTopoLevels) {
+        wc[wv][0][lane] = cn;
+        wc[wv][1][lane] = ci;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * (max_level + 1)) {
+        uint32_t t = 0u;
+        for (int v = 0; v < kTopoThreads / 64; ++v) t += wc[v][threadIdx.x & 1][threadIdx.x >> 1];
+        counts[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
     }
 }
 
-// block of internal node k (level l) gets the block id of its first internal child
-__global__ void k_set_base(const uint32_t* __restrict__ cscan_prev, int n_int_prev, int d3, uint32_t blk_off_prev,
-                           const uint32_t* __restrict__ iscan_next, uint32_t blk_off_next, uint32_t* __restrict__ btopo,
-                           int ts)
+// Exclusive scan of one channel's block counts per workgroup, in place; totals[channel] = its sum.
+__global__ void __launch_bounds__(1024) k_topo_scan(uint32_t* __restrict__ counts, int nblocks,
+                                                    uint32_t* __restrict__ totals)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_int_prev) return;
-    const uint32_t fc = cscan_prev[(int64_t)k * d3];
-    btopo[(int64_t)(blk_off_prev + k) * ts + d3] = blk_off_next + iscan_next[fc];
+    __shared__ uint32_t ws[16];
+    uint32_t* __restrict__ c = counts + (int64_t)blockIdx.x * nblocks;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t carry = 0u;
+    for (int b0 = 0; b0 < nblocks; b0 += 4096) {
+        const int b = b0 + 4 * (int)threadIdx.x;
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = b + k < nblocks ? c[b + k] : 0u;
+        const uint32_t sum = v[0] + v[1] + v[2] + v[3];
+        const uint32_t incl = wave_inclusive_scan(sum, lane);
+        if (lane == 63) ws[wv] = incl;
+        __syncthreads();
+        uint32_t run = carry + incl - sum;
+        for (int k = 0; k < 16; ++k) {
+            if (k < wv) run += ws[k];
+            carry += ws[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (b + k < nblocks) c[b + k] = run;
+            run += v[k];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
 // ---------------------------------------------------------------------------
 // 5. Aggregates and packing
 // ---------------------------------------------------------------------------
-// Aggregates of one level's nodes (offset off, n of them), in float64: from
-// the points of a leaf, from the children's float64 aggregates for an
-// internal node (mass, w-weighted centre of mass, summed w n, and the second
-// moment about the centre of mass by the parallel-axis rule, a sum of
-// non-negative terms).  The tree stores each as the float32 nearest to its
-// float64 value: one rounding, so a one-point leaf's centre of mass is its
-// point and its second moment exactly 0, as the definitions give.
-__global__ void k_aggregate(int32_t off, int32_t n, const int32_t* __restrict__ nbegin,
-                            const int32_t* __restrict__ ncount, const int32_t* __restrict__ nfirst,
-                            const int32_t* __restrict__ nnchild, const float4* __restrict__ pts,
-                            const float4* __restrict__ pdip, double4* __restrict__ agg64, double4* __restrict__ dip64,
-                            double* __restrict__ spr64, float4* __restrict__ nagg, float4* __restrict__ ndip,
-                            float* __restrict__ nspr, double* __restrict__ quad64)
+// Aggregates, in float64: from the points of a leaf, from the children's
+// float64 aggregates for an internal node (mass, w-weighted centre of mass,
+// summed w n, and the second moment about the centre of mass by the
+// parallel-axis rule, a sum of non-negative terms).  The tree stores each as
+// the float32 nearest to its float64 value: one rounding, so a one-point
+// leaf's centre of mass is its point and its second moment exactly 0, as the
+// definitions give.
+struct BuildArrays {
+    // nodes
+    int32_t *nbegin, *ncount, *nlevel, *ndigit, *nparent, *nfirst, *nnchild, *npblk;
+    float4 *nagg, *ndip;
+    float* nspr;
+    double4 *agg64, *dip64;
+    double *spr64, *quad64;
+    // child blocks, by internal node: its node id and its first child
+    int32_t *inode, *bfirst;
+    uint32_t* btopo;
+    float4 *bagg, *bdip;
+    float* bspr;
+    int ts, d3, has_dip;
+};
+
+// stores node g's aggregates, float32 copies also in its slot of its parent's block (pblk, digit)
+__device__ __forceinline__ void store_node(const BuildArrays& a, int32_t g, int32_t pblk, int32_t digit, uint32_t count,
+                                           double m, double cx, double cy, double cz, double s2, double dx, double dy,
+                                           double dz)
+{
+    const float4 ag = make_float4((float)cx, (float)cy, (float)cz, (float)m);
+    const float4 di = make_float4((float)dx, (float)dy, (float)dz, 0.0f);
+    a.agg64[g] = make_double4(cx, cy, cz, m);
+    a.spr64[g] = s2;
+    a.nagg[g] = ag;
+    a.nspr[g] = (float)s2;
+    a.ncount[g] = (int32_t)count;
+    if (a.has_dip) {
+        a.dip64[g] = make_double4(dx, dy, dz, 0.0);
+        a.ndip[g] = di;
+    }
+    if (pblk < 0) return;   // the root
+    const int64_t slot = (int64_t)pblk * a.d3 + digit;
+    a.btopo[(int64_t)pblk * a.ts + digit] = count;
+    a.bagg[slot] = ag;
+    a.bspr[slot] = (float)s2;
+    if (a.has_dip) a.bdip[slot] = di;
+}
+
+__device__ __forceinline__ void aggregate_leaf(const BuildArrays& a, int32_t g, int32_t pblk, int32_t digit, int32_t b,
+                                               int32_t e, const float4* __restrict__ pts,
+                                               const float4* __restrict__ pdip)
 {
 #pragma clang fp contract(off)
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t g = off + i;
     double m = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
-    const int32_t f = nfirst[g];
-    if (f < 0) {
-        const int32_t b = nbegin[g], e = b + ncount[g];
-        for (int32_t s = b; s < e; ++s) {
-            const float4 p = pts[s];
-            const double w = p.w;
-            m += w; sx += w * (double)p.x; sy += w * (double)p.y; sz += w * (double)p.z;
-            if (pdip) { const float4 q = pdip[s]; dx += q.x; dy += q.y; dz += q.z; }
-        }
-    } else {
-        const int32_t e = f + nnchild[g];
-        for (int32_t c = f; c < e; ++c) {
-            const double4 a = agg64[c];
-            m += a.w; sx += a.w * a.x; sy += a.w * a.y; sz += a.w * a.z;
-            if (pdip) { const double4 q = dip64[c]; dx += q.x; dy += q.y; dz += q.z; }
-        }
+    for (int32_t s = b; s < e; ++s) {
+        const float4 p = pts[s];
+        const double w = p.w;
+        m += w; sx += w * (double)p.x; sy += w * (double)p.y; sz += w * (double)p.z;
+        if (pdip) { const float4 q = pdip[s]; dx += q.x; dy += q.y; dz += q.z; }
     }
     const double cx = sx / m, cy = sy / m, cz = sz / m;
     double s2 = 0.0;
-    if (f < 0) {
-        const int32_t b = nbegin[g], e = b + ncount[g];
-        for (int32_t s = b; s < e; ++s) {
-            const float4 p = pts[s];
-            const double ex = (double)p.x - cx, ey = (double)p.y - cy, ez = (double)p.z - cz;
-            s2 += (double)p.w * (ex * ex + ey * ey + ez * ez);
-        }
-    } else {
-        const int32_t e = f + nnchild[g];
-        for (int32_t c = f; c < e; ++c) {
-            const double4 a = agg64[c];
-            const double ex = a.x - cx, ey = a.y - cy, ez = a.z - cz;
-            s2 += a.w * (spr64[c] + (ex * ex + ey * ey + ez * ez));
-        }
+    for (int32_t s = b; s < e; ++s) {
+        const float4 p = pts[s];
+        const double ex = (double)p.x - cx, ey = (double)p.y - cy, ez = (double)p.z - cz;
+        s2 += (double)p.w * (ex * ex + ey * ey + ez * ez);
     }
     s2 /= m;
-    if (quad64) {
-        // second-moment tensor about the centre of mass, Q = sum w (p - c)(p - c)^T: over the
-        // points of a leaf; over the children of a node by the parallel-axis rule,
-        // Q = sum_c (Q_c + m_c (c_c - c)(c_c - c)^T)
+    if (a.quad64) {
+        // second-moment tensor about the centre of mass, Q = sum w (p - c)(p - c)^T
         double Q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        if (f < 0) {
-            const int32_t b = nbegin[g], e = b + ncount[g];
-            for (int32_t s = b; s < e; ++s) {
-                const float4 p = pts[s];
-                const double ww = p.w, ex = (double)p.x - cx, ey = (double)p.y - cy, ez = (double)p.z - cz;
-                Q[0] += ww * ex * ex; Q[1] += ww * ey * ey; Q[2] += ww * ez * ez;
-                Q[3] += ww * ex * ey; Q[4] += ww * ex * ez; Q[5] += ww * ey * ez;
-            }
-        } else {
-            const int32_t e = f + nnchild[g];
-            for (int32_t c = f; c < e; ++c) {
-                const double4 a = agg64[c];
-                const double* qc = quad64 + 6 * (int64_t)c;
-                const double ex = a.x - cx, ey = a.y - cy, ez = a.z - cz;
-                Q[0] += qc[0] + a.w * ex * ex; Q[1] += qc[1] + a.w * ey * ey; Q[2] += qc[2] + a.w * ez * ez;
-                Q[3] += qc[3] + a.w * ex * ey; Q[4] += qc[4] + a.w * ex * ez; Q[5] += qc[5] + a.w * ey * ez;
+        for (int32_t s = b; s < e; ++s) {
+            const float4 p = pts[s];
+            const double ww = p.w, ex = (double)p.x - cx, ey = (double)p.y - cy, ez = (double)p.z - cz;
+            Q[0] += ww * ex * ex; Q[1] += ww * ey * ey; Q[2] += ww * ez * ez;
+            Q[3] += ww * ex * ey; Q[4] += ww * ex * ez; Q[5] += ww * ey * ez;
+        }
+        for (int k = 0; k < 6; ++k) a.quad64[6 * (int64_t)g + k] = Q[k];
+    }
+    store_node(a, g, pblk, digit, (uint32_t)(e - b), m, cx, cy, cz, s2, dx, dy, dz);
+}
+
+// internal node of block k: its children are nodes bfirst[k] .. bfirst[k + 1] - 1 (the children of
+// consecutive blocks follow one another through all levels)
+__device__ __forceinline__ void aggregate_block(const BuildArrays& a, int32_t k, int32_t n_blocks, int32_t n_nodes)
+{
+#pragma clang fp contract(off)
+    const int32_t g = a.inode[k], f = a.bfirst[k], e = k + 1 < n_blocks ? a.bfirst[k + 1] : n_nodes;
+    double m = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
+    uint32_t count = 0u;
+    for (int32_t c = f; c < e; ++c) {
+        const double4 q = a.agg64[c];
+        m += q.w; sx += q.w * q.x; sy += q.w * q.y; sz += q.w * q.z;
+        count += (uint32_t)a.ncount[c];
+        if (a.has_dip) { const double4 d = a.dip64[c]; dx += d.x; dy += d.y; dz += d.z; }
+    }
+    const double cx = sx / m, cy = sy / m, cz = sz / m;
+    double s2 = 0.0;
+    for (int32_t c = f; c < e; ++c) {
+        const double4 q = a.agg64[c];
+        const double ex = q.x - cx, ey = q.y - cy, ez = q.z - cz;
+        s2 += q.w * (a.spr64[c] + (ex * ex + ey * ey + ez * ez));
+    }
+    s2 /= m;
+    if (a.quad64) {   // parallel-axis rule: Q = sum_c (Q_c + m_c (c_c - c)(c_c - c)^T)
+        double Q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int32_t c = f; c < e; ++c) {
+            const double4 q = a.agg64[c];
+            const double* qc = a.quad64 + 6 * (int64_t)c;
+            const double ex = q.x - cx, ey = q.y - cy, ez = q.z - cz;
+            Q[0] += qc[0] + q.w * ex * ex; Q[1] += qc[1] + q.w * ey * ey; Q[2] += qc[2] + q.w * ez * ez;
+            Q[3] += qc[3] + q.w * ex * ey; Q[4] += qc[4] + q.w * ex * ez; Q[5] += qc[5] + q.w * ey * ez;
+        }
+        for (int t = 0; t < 6; ++t) a.quad64[6 * (int64_t)g + t] = Q[t];
+    }
+    a.nnchild[g] = e - f;
+    store_node(a, g, a.npblk[g], a.ndigit[g], count, m, cx, cy, cz, s2, dx, dy, dz);
+}
+
+// the internal nodes of one level
+__global__ void __launch_bounds__(256) k_aggregate(BuildArrays a, int32_t blk0, int32_t n, int32_t n_blocks,
+                                                   int32_t n_nodes)
+{
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) aggregate_block(a, blk0 + i, n_blocks, n_nodes);
+}
+
+struct TopoOff {
+    int32_t node[kTopoLevels + 1];   // first node of each level
+    int32_t blk[kTopoLevels + 1];    // first block of each level's internal nodes
+};
+
+// The internal nodes of levels top .. 0, which hold few nodes each, in one
+// workgroup: a launch per level costs more than its work.
+constexpr int kTopNodes = 1024;
+__global__ void __launch_bounds__(kTopNodes) k_aggregate_top(BuildArrays a, TopoOff off, int top, int32_t n_blocks,
+                                                             int32_t n_nodes)
+{
+    for (int l = top; l >= 0; --l) {
+        const int32_t k = off.blk[l] + (int32_t)threadIdx.x;
+        if (k < off.blk[l + 1]) aggregate_block(a, k, n_blocks, n_nodes);
+        __threadfence_block();
+        __syncthreads();
+    }
+}
+
+// Every node, from the marks and the scanned counts: a point's nodes are
+// numbered, level by level, by the nodes of that level that start before it
+// (counts of the blocks before, of the block's wavefronts before, and a
+// ballot).  The last node of level l - 1 to start at or before the point is
+// its parent, and the first child of a node that starts at the point is its
+// node of the next level.  A point has at most one leaf (its deepest node),
+// whose aggregates follow once the levels are done.
+__global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __restrict__ codes,
+                                                            const uint16_t* __restrict__ marks, int64_t n,
+                                                            const uint32_t* __restrict__ counts, TopoOff off,
+                                                            int depth, int bits, int leaf, int max_level,
+                                                            BuildArrays a, const float4* __restrict__ pts,
+                                                            const float4* __restrict__ pdip)
+{
+    __shared__ uint32_t wc[kTopoThreads / 64][2][kTopoLevels];
+    const int64_t base = (int64_t)blockIdx.x * kTopoPoints;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint16_t mk[kTopoChunks];
+    uint32_t cn = 0u, ci = 0u;   // lane l: level l's nodes and internal nodes before the wavefront's current chunk
+#pragma unroll
+    for (int c = 0; c < kTopoChunks; ++c) {
+        const int64_t i = base + (wv * kTopoChunks + c) * 64 + lane;
+        mk[c] = i < n ? marks[i] : kNoNode;
+        const Mark m = unpack_mark(mk[c]);
+        for (int l = 0; l <= depth; ++l) {
+            const uint64_t nm = __ballot(m.s <= l && l <= m.e), im = __ballot(m.s <= l && l <= m.w);
+            if (lane == l) {
+                cn += (uint32_t)__popcll(nm);
+                ci += (uint32_t)__popcll(im);
             }
         }
-        for (int k = 0; k < 6; ++k) quad64[6 * (int64_t)g + k] = Q[k];
     }
-    agg64[g] = make_double4(cx, cy, cz, m);
-    spr64[g] = s2;
-    nagg[g] = make_float4((float)cx, (float)cy, (float)cz, (float)m);
-    nspr[g] = (float)s2;
-    if (pdip) {
-        dip64[g] = make_double4(dx, dy, dz, 0.0);
-        ndip[g] = make_float4((float)dx, (float)dy, (float)dz, 0.0f);
+    if (lane < kTopoLevels) {
+        wc[wv][0][lane] = cn;
+        wc[wv][1][lane] = ci;
+    }
+    __syncthreads();
+    cn = ci = 0u;
+    if (lane <= depth) {
+        cn = counts[(int64_t)(2 * lane) * gridDim.x + blockIdx.x];
+        ci = counts[(int64_t)(2 * lane + 1) * gridDim.x + blockIdx.x];
+        for (int v = 0; v < wv; ++v) {
+            cn += wc[v][0][lane];
+            ci += wc[v][1][lane];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < kTopoChunks; ++c) {
+        const int64_t i = base + (wv * kTopoChunks + c) * 64 + lane;
+        const Mark m = unpack_mark(mk[c]);
+        if (__ballot(m.s <= m.e) == 0ull) continue;   // no node starts here
+        const uint64_t code = i < n ? codes[i] : 0ull;
+        int32_t id = -1, blk = -1;               // this point's node of the level before, its block
+        int32_t before_n = 0, before_b = 0;      // nodes and blocks of the level before that start at or before it
+        int32_t leaf_id = -1, leaf_pblk = -1, leaf_digit = 0;
+        for (int l = 0; l <= depth; ++l) {
+            const bool node = m.s <= l && l <= m.e, inner = m.s <= l && l <= m.w;
+            const uint64_t nm = __ballot(node), im = __ballot(inner);
+            const int32_t rn = (int32_t)__builtin_amdgcn_readlane((int)cn, l) +
+                               (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
+            const int32_t ri = (int32_t)__builtin_amdgcn_readlane((int)ci, l) +
+                               (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(im >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)im, 0u));
+            if (blk >= 0) {   // the point's internal node of the level before: its children start here
+                a.nfirst[id] = off.node[l] + rn;
+                a.bfirst[blk] = off.node[l] + rn;
+                a.inode[blk] = id;
+                a.btopo[(int64_t)blk * a.ts + a.d3] = (uint32_t)(off.blk[l] + ri);
+            }
+            blk = -1;
+            if (node) {
+                id = off.node[l] + rn;
+                const int32_t digit = l ? (int32_t)(code >> (60 - bits * l)) & (a.d3 - 1) : 0;
+                const int32_t pblk = l ? off.blk[l - 1] + before_b - 1 : -1;
+                a.nbegin[id] = (int32_t)i;
+                a.nlevel[id] = l;
+                a.ndigit[id] = digit;
+                a.nparent[id] = l ? off.node[l - 1] + before_n - 1 : -1;
+                a.npblk[id] = pblk;
+                if (inner) {
+                    blk = off.blk[l] + ri;
+                } else {
+                    a.nfirst[id] = -1;
+                    a.nnchild[id] = 0;
+                    leaf_id = id;
+                    leaf_pblk = pblk;
+                    leaf_digit = digit;
+                }
+            }
+            before_n = rn + (node ? 1 : 0);
+            before_b = ri + (inner ? 1 : 0);
+            if (lane == l) {
+                cn += (uint32_t)__popcll(nm);
+                ci += (uint32_t)__popcll(im);
+            }
+        }
+        if (leaf_id >= 0) {
+            // its end: within leaf_size points, except at the deepest level
+            const int shift = 60 - bits * m.e;
+            const uint64_t pre = code >> shift;
+            int64_t end = i + 1;
+            while (end < n && end <= i + leaf && (codes[end] >> shift) == pre) ++end;
+            if (end == i + leaf + 1 && end < n && (codes[end] >> shift) == pre) {   // the first code past the prefix
+                int64_t hi = n;
+                while (end < hi) {
+                    const int64_t mid = end + ((hi - end) >> 1);
+                    if ((codes[mid] >> shift) == pre) end = mid + 1;
+                    else hi = mid;
+                }
+            }
+            aggregate_leaf(a, leaf_id, leaf_pblk, leaf_digit, (int32_t)i, (int32_t)end, pts, pdip);
+        }
     }
 }
 
@@ -669,66 +865,6 @@ __global__ void k_pack_quad(int32_t n_nodes, const int32_t* __restrict__ npblk, 
     bquad[2 * slot + 1] = make_float4((float)(3.0 * Q[4]), (float)(3.0 * Q[5]), (float)(0.5 * (Q[0] + Q[1] + Q[2])), 0.0f);
 }
 
-__global__ void k_pack(int32_t n_nodes, const int32_t* __restrict__ npblk, const int32_t* __restrict__ ndig,
-                       const float4* __restrict__ nagg, const float4* __restrict__ ndip,
-                       const float* __restrict__ nspr, float4* __restrict__ bagg, float4* __restrict__ bdip,
-                       float* __restrict__ bspr, int d3)
-{
-    const int32_t g = blockIdx.x * blockDim.x + threadIdx.x + 1;
-    if (g >= n_nodes) return;
-    const int64_t slot = (int64_t)npblk[g] * d3 + ndig[g];
-    bagg[slot] = nagg[g];
-    bspr[slot] = nspr[g];
-    if (bdip) bdip[slot] = ndip[g];
-}
-
-// the root's level arrays: first point 0, all n points, no parent, digit 0, no parent block
-__global__ void k_root_init(int32_t n, int32_t* b, int32_t* c, int32_t* par, int32_t* dig, int32_t* pblk)
-{
-    if (threadIdx.x != 0) return;
-    b[0] = 0;
-    c[0] = n;
-    par[0] = -1;
-    dig[0] = 0;
-    pblk[0] = -1;
-}
-
-// The per-level arrays concatenated into the node and block arrays, each
-// family in one launch (the tables travel as kernel arguments).
-constexpr int kLevelTab = 24;   // levels of a tree: at most 60 / 3 + 1 = 21
-struct LevelTab {
-    int64_t off[kLevelTab + 1];          // first node of each level
-    const int32_t* src[7][kLevelTab];    // begin, count, digit, parent, first child, child count, parent block
-};
-struct NodeDst {
-    int32_t* p[8];                       // the same seven node arrays, then the level
-};
-struct TopoTab {
-    int64_t off[kLevelTab + 1];          // first topology word of each level's blocks
-    const uint32_t* src[kLevelTab];
-};
-
-__global__ void k_concat_levels(LevelTab tab, int n_levels, NodeDst dst)
-{
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= tab.off[n_levels]) return;
-    int l = 0;
-    while (g >= tab.off[l + 1]) ++l;
-    const int64_t i = g - tab.off[l];
-#pragma unroll
-    for (int a = 0; a < 7; ++a) dst.p[a][g] = tab.src[a][l][i];
-    dst.p[7][g] = l;
-}
-
-__global__ void k_concat_topo(TopoTab tab, int n_levels, uint32_t* __restrict__ btopo)
-{
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= tab.off[n_levels]) return;
-    int l = 0;
-    while (g >= tab.off[l + 1]) ++l;
-    btopo[g] = tab.src[l][g - tab.off[l]];
-}
-
 // ---------------------------------------------------------------------------
 // Host orchestration
 // ---------------------------------------------------------------------------
@@ -791,13 +927,14 @@ struct DevPool {
     }
 };
 
-inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
-
-struct LevelBufs {
-    int32_t n = 0;
-    int32_t *b = nullptr, *c = nullptr, *par = nullptr, *dig = nullptr, *pblk = nullptr, *first = nullptr,
-            *nch = nullptr;
+// what the host reads once per build: the root cube with the validity flag (launch_bbox), and
+// the nodes and internal nodes of every level
+struct BuildInfo {
+    float params[8];
+    uint32_t totals[2 * kTopoLevels];
 };
+
+inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
 
@@ -830,29 +967,22 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
 
     // 1. root cube + validation
     const int nbb = (int)std::min<int64_t>(1024, (n + 2047) / 2048 > 0 ? (n + 2047) / 2048 : 1);
-    float* params = tmp.alloc<float>(8);
+    BuildInfo* info = tmp.alloc<BuildInfo>(1);
+    float* params = reinterpret_cast<float*>(info);   // its first member
     float* partial = tmp.alloc<float>((int64_t)nbb * 8);
     SBH_ALLOC_OK("allocating bbox buffers");
     SBH_TRY(launch_bbox(src, w, nrm, n, params, partial, nbb, s), "bbox kernel");
-    float hp[8];
-    SBH_TRY(hipMemcpyAsync(hp, params, 6 * sizeof(float), hipMemcpyDeviceToHost, s), "bbox copy");
-    SBH_TRY(hipStreamSynchronize(s), "bbox sync");
-    if (hp[5] != 0.0f) {
-        *msg = "sbh_build: non-finite coordinate or normal, or weight not finite and > 0";
-        return SBH_EINVAL;
-    }
-    t->lo[0] = hp[0]; t->lo[1] = hp[1]; t->lo[2] = hp[2];
-    t->side = hp[3]; t->inv_side = hp[4];
-    for (int l = 0; l < kMaxLevels; ++l) t->diam[l] = (float)(std::sqrt(3.0) * (double)t->side / std::pow((double)d, l));
-
     // 2-3. codes and sort
     uint64_t* keys = tmp.alloc<uint64_t>(n);
     uint32_t* vals = tmp.alloc<uint32_t>(n);
     uint64_t* keys2 = tmp.alloc<uint64_t>(n);
     uint32_t* vals2 = tmp.alloc<uint32_t>(n);
     uint32_t* hist = tmp.alloc<uint32_t>((int64_t)radix_sort_hist_size(n));
-    const int64_t scan_cap = std::max<int64_t>((int64_t)radix_sort_hist_size(n), n * (int64_t)d3 / 2 + d3 * 4);
-    uint32_t* stmp = tmp.alloc<uint32_t>((int64_t)scan_tmp_size(std::max<int64_t>(scan_cap, n)) + 8);
+    uint32_t* stmp = tmp.alloc<uint32_t>((int64_t)scan_tmp_size((int64_t)radix_sort_hist_size(n)) + 8);
+    const int64_t nblocks = (n + kTopoPoints - 1) / kTopoPoints;
+    const int channels = 2 * (max_level + 1);
+    uint16_t* marks = tmp.alloc<uint16_t>(n);
+    uint32_t* counts = tmp.alloc<uint32_t>(nblocks * channels);
     SBH_ALLOC_OK("allocating sort buffers");
     SBH_TRY(launch_morton(src, n, params, keys, vals, s), "morton kernel");
     SBH_TRY(radix_sort_pairs(keys, vals, keys2, vals2, n, 0, 64, hist, stmp, s), "radix sort");
@@ -873,103 +1003,40 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
     SBH_TRY(hipMemcpyAsync(t->codes, keys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s), "codes copy");
     const uint64_t* codes = t->codes;
 
-    // 4. levels
-    std::vector<LevelBufs> lv;
-    std::vector<uint32_t> blk_off;   // first block id of each level's internal nodes
-    std::vector<int32_t> n_int_lv;
-    LevelBufs root;
-    root.n = 1;
-    root.b = tmp.alloc<int32_t>(1); root.c = tmp.alloc<int32_t>(1); root.par = tmp.alloc<int32_t>(1);
-    root.dig = tmp.alloc<int32_t>(1); root.pblk = tmp.alloc<int32_t>(1);
-    root.first = tmp.alloc<int32_t>(1); root.nch = tmp.alloc<int32_t>(1);
-    SBH_ALLOC_OK("allocating root");
-    k_root_init<<<1, 64, 0, s>>>((int32_t)n, root.b, root.c, root.par, root.dig, root.pblk);
-    SBH_TRY(hipGetLastError(), "root init kernel");
-    lv.push_back(root);
-    uint32_t* total = stmp;  // scan totals land here; scans use stmp+1.. as scratch
-    uint32_t* scan_scratch = stmp + 1;
-    std::vector<uint32_t*> cscan_lv;
-    std::vector<uint32_t*> iscan_lv;
-    int64_t n_blocks = 0;
-    // btopo is built in per-level pieces, then concatenated
-    std::vector<uint32_t*> btopo_lv;
-
-    for (int level = 0;; ++level) {
-        LevelBufs& L = lv[level];
-        uint32_t* flags = tmp.alloc<uint32_t>(L.n);
-        uint32_t* iscan = tmp.alloc<uint32_t>(L.n);
-        SBH_ALLOC_OK("allocating level flags");
-        k_level_flags<<<nblk(L.n), 256, 0, s>>>(L.c, L.n, level, leaf_size, max_level, flags, L.first, L.nch);
-        SBH_TRY(hipGetLastError(), "level flags kernel");
-        SBH_TRY(scan_exclusive_u32(flags, iscan, L.n, total, scan_scratch, s), "internal scan");
-        uint32_t n_int = 0;
-        SBH_TRY(hipMemcpyAsync(&n_int, total, 4, hipMemcpyDeviceToHost, s), "internal count copy");
-        SBH_TRY(hipStreamSynchronize(s), "level sync");
-        iscan_lv.push_back(iscan);
-        blk_off.push_back((uint32_t)n_blocks);
-        n_int_lv.push_back((int32_t)n_int);
-        // base pointers of the previous level's blocks
-        if (level > 0 && n_int_lv[level - 1] > 0) {
-            // btopo_lv[level-1] is that level's own piece, indexed from 0
-            k_set_base<<<nblk(n_int_lv[level - 1]), 256, 0, s>>>(cscan_lv[level - 1], n_int_lv[level - 1], d3, 0u,
-                                                                 iscan, (uint32_t)n_blocks, btopo_lv[level - 1], ts);
-            SBH_TRY(hipGetLastError(), "set base kernel");
-        }
-        if (n_int == 0) {
-            btopo_lv.push_back(nullptr);
-            cscan_lv.push_back(nullptr);
-            break;
-        }
-        int32_t* imap = tmp.alloc<int32_t>(n_int);
-        uint32_t* bt = tmp.alloc<uint32_t>((int64_t)n_int * ts);
-        uint32_t* ccount = tmp.alloc<uint32_t>((int64_t)n_int * d3);
-        int32_t* cbegin = tmp.alloc<int32_t>((int64_t)n_int * d3);
-        uint32_t* cflag = tmp.alloc<uint32_t>((int64_t)n_int * d3);
-        uint32_t* cscan = tmp.alloc<uint32_t>((int64_t)n_int * d3);
-        SBH_ALLOC_OK("allocating level children");
-        SBH_TRY(hipMemsetAsync(bt, 0, (size_t)n_int * ts * sizeof(uint32_t), s), "topo clear");
-        k_internal_map<<<nblk(L.n), 256, 0, s>>>(flags, iscan, L.n, imap);
-        SBH_TRY(hipGetLastError(), "internal map kernel");
-        // each level writes its own piece of the topology array (block ids
-        // relative to the level); the pieces are concatenated at the end
-        k_children<<<nblk((int64_t)n_int * d3), 256, 0, s>>>(L.b, L.c, imap, (int)n_int, level, bits, d3, codes, 0u,
-                                                             bt, ts, ccount, cbegin, cflag);
-        SBH_TRY(hipGetLastError(), "children kernel");
-        SBH_TRY(scan_exclusive_u32(cflag, cscan, (int64_t)n_int * d3, total, scan_scratch, s), "children scan");
-        uint32_t n_next = 0;
-        SBH_TRY(hipMemcpyAsync(&n_next, total, 4, hipMemcpyDeviceToHost, s), "children count copy");
-        SBH_TRY(hipStreamSynchronize(s), "children sync");
-        int32_t off_cur = 0;
-        for (int l = 0; l < level; ++l) off_cur += lv[l].n;
-        const int32_t off_next = off_cur + L.n;
-        LevelBufs N;
-        N.n = (int32_t)n_next;
-        N.b = tmp.alloc<int32_t>(N.n); N.c = tmp.alloc<int32_t>(N.n); N.par = tmp.alloc<int32_t>(N.n);
-        N.dig = tmp.alloc<int32_t>(N.n); N.pblk = tmp.alloc<int32_t>(N.n);
-        N.first = tmp.alloc<int32_t>(N.n); N.nch = tmp.alloc<int32_t>(N.n);
-        SBH_ALLOC_OK("allocating next level");
-        k_emit<<<nblk((int64_t)n_int * d3), 256, 0, s>>>(ccount, cbegin, cscan, imap, (int)n_int, d3, off_cur,
-                                                         off_next, (uint32_t)n_blocks, N.b, N.c, N.par, N.dig, N.pblk,
-                                                         L.first, L.nch);
-        SBH_TRY(hipGetLastError(), "emit kernel");
-        btopo_lv.push_back(bt);
-        cscan_lv.push_back(cscan);
-        n_blocks += n_int;
-        lv.push_back(N);
+    // 4. topology: the marks and counts, then the sizes
+    k_topo_mark<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(codes, n, bits, leaf_size, max_level, marks, counts);
+    SBH_TRY(hipGetLastError(), "topology mark kernel");
+    k_topo_scan<<<channels, 1024, 0, s>>>(counts, (int)nblocks, info->totals);
+    SBH_TRY(hipGetLastError(), "topology scan kernel");
+    BuildInfo h;
+    SBH_TRY(hipMemcpyAsync(&h, info, sizeof(h), hipMemcpyDeviceToHost, s), "sizes copy");
+    SBH_TRY(hipStreamSynchronize(s), "sizes sync");
+    if (h.params[5] != 0.0f) {
+        *msg = "sbh_build: non-finite coordinate or normal, or weight not finite and > 0";
+        return SBH_EINVAL;
     }
-    // a level whose nodes are all leaves ends the loop; trailing empty levels cannot occur
-    const int n_levels = (int)lv.size();
-    int64_t n_nodes = 0;
-    for (auto& L : lv) n_nodes += L.n;
+    t->lo[0] = h.params[0]; t->lo[1] = h.params[1]; t->lo[2] = h.params[2];
+    t->side = h.params[3]; t->inv_side = h.params[4];
+    for (int l = 0; l < kMaxLevels; ++l) t->diam[l] = (float)(std::sqrt(3.0) * (double)t->side / std::pow((double)d, l));
+    TopoOff off{};
+    int64_t n_nodes = 0, n_blocks = 0;
+    int n_levels = 0;
+    for (int l = 0; l <= max_level; ++l) {
+        if (h.totals[2 * l] > 0) n_levels = l + 1;
+        n_nodes += h.totals[2 * l];
+        n_blocks += h.totals[2 * l + 1];
+        if (n_nodes >= (int64_t)1 << 31) {
+            *msg = "sbh_build: tree too large";
+            return SBH_EINVAL;
+        }
+        off.node[l + 1] = (int32_t)n_nodes;
+        off.blk[l + 1] = (int32_t)n_blocks;
+    }
     t->n_nodes = n_nodes;
     t->n_blocks = n_blocks;
     t->depth = n_levels - 1;
-    if (n_nodes >= (int64_t)1 << 31) {
-        *msg = "sbh_build: tree too large";
-        return SBH_EINVAL;
-    }
 
-    // concatenate level arrays into node arrays
+    // node arrays
     t->slab_bytes[1] =
         carve_bytes<int32_t>(n_nodes) * 7 + carve_bytes<float4>(n_nodes) * (nrm ? 2 : 1) + carve_bytes<float>(n_nodes);
     SBH_TRY(dev_alloc(t->mem, &t->slab[1], t->slab_bytes[1], s), "allocating nodes");
@@ -985,24 +1052,6 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
         t->nagg = c.take<float4>(n_nodes);
         if (nrm) t->ndip = c.take<float4>(n_nodes);
         t->nspr = c.take<float>(n_nodes);
-    }
-    int32_t* npblk = tmp.alloc<int32_t>(n_nodes);
-    SBH_ALLOC_OK("allocating parent blocks");
-    if (n_levels > kLevelTab) {
-        *msg = "sbh_build: too many levels";
-        return SBH_EINVAL;
-    }
-    {
-        LevelTab tab{};
-        for (int l = 0; l < n_levels; ++l) {
-            const LevelBufs& L = lv[l];
-            tab.off[l + 1] = tab.off[l] + L.n;
-            const int32_t* src[7] = {L.b, L.c, L.dig, L.par, L.first, L.nch, L.pblk};
-            for (int a = 0; a < 7; ++a) tab.src[a][l] = src[a];
-        }
-        const NodeDst dst{{t->nbegin, t->ncount, t->ndigit, t->nparent, t->nfirst, t->nnchild, npblk, t->nlevel}};
-        k_concat_levels<<<nblk(n_nodes), 256, 0, s>>>(tab, n_levels, dst);
-        SBH_TRY(hipGetLastError(), "node concatenation kernel");
     }
     // block arrays
     const int64_t nbk = n_blocks > 0 ? n_blocks : 1;
@@ -1021,29 +1070,31 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
         if (compress) t->bq = c.take<uint2>(nbk * d3);
         if (quadrupole) t->bquad = c.take<float4>(2 * nbk * d3);
     }
-    if (n_blocks > 0) {   // a level's blocks follow the previous level's (blk_off)
-        TopoTab tt{};
-        for (int l = 0; l < n_levels; ++l) {
-            const bool has = n_int_lv[l] > 0 && btopo_lv[l];
-            tt.off[l + 1] = tt.off[l] + (has ? (int64_t)n_int_lv[l] * ts : 0);
-            tt.src[l] = btopo_lv[l];
-        }
-        k_concat_topo<<<nblk(tt.off[n_levels]), 256, 0, s>>>(tt, n_levels, t->btopo);
-        SBH_TRY(hipGetLastError(), "topology concatenation kernel");
-    }
-    // 5. aggregates bottom-up, then pack into the child blocks
+    // nodes and leaves, then the internal nodes bottom-up, each also into its slot of its parent's block
     {
-        std::vector<int64_t> off(n_levels + 1, 0);
-        for (int l = 0; l < n_levels; ++l) off[l + 1] = off[l] + lv[l].n;
+        int32_t* npblk = tmp.alloc<int32_t>(n_nodes);
+        int32_t* inode = tmp.alloc<int32_t>(nbk);
+        int32_t* bfirst = tmp.alloc<int32_t>(nbk);
         double4* agg64 = tmp.alloc<double4>(n_nodes);
         double4* dip64 = nrm ? tmp.alloc<double4>(n_nodes) : nullptr;
         double* spr64 = tmp.alloc<double>(n_nodes);
         double* quad64 = quadrupole ? tmp.alloc<double>(6 * n_nodes) : nullptr;
         SBH_ALLOC_OK("allocating float64 aggregates");
-        for (int l = n_levels - 1; l >= 0; --l) {
-            k_aggregate<<<nblk(lv[l].n), 256, 0, s>>>((int32_t)off[l], lv[l].n, t->nbegin, t->ncount, t->nfirst,
-                                                      t->nnchild, t->pts, t->pdip, agg64, dip64, spr64, t->nagg,
-                                                      t->ndip, t->nspr, quad64);
+        const BuildArrays a{t->nbegin, t->ncount, t->nlevel, t->ndigit, t->nparent, t->nfirst, t->nnchild, npblk,
+                            t->nagg,   t->ndip,   t->nspr,   agg64,     dip64,      spr64,     quad64,     inode,
+                            bfirst,    t->btopo,  t->bagg,   t->bdip,   t->bspr,    ts,        d3,         nrm ? 1 : 0};
+        k_topo_emit<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(codes, marks, n, counts, off, t->depth, bits, leaf_size,
+                                                               max_level, a, t->pts, t->pdip);
+        SBH_TRY(hipGetLastError(), "topology kernel");
+        int top = -1;   // levels 0 .. top hold at most kTopNodes internal nodes each
+        while (top + 1 < n_levels - 1 && off.blk[top + 2] - off.blk[top + 1] <= kTopNodes) ++top;
+        for (int l = n_levels - 2; l > top; --l) {
+            const int32_t n_int = off.blk[l + 1] - off.blk[l];
+            k_aggregate<<<nblk(n_int), 256, 0, s>>>(a, off.blk[l], n_int, (int32_t)n_blocks, (int32_t)n_nodes);
+            SBH_TRY(hipGetLastError(), "aggregate kernel");
+        }
+        if (top >= 0) {
+            k_aggregate_top<<<1, kTopNodes, 0, s>>>(a, off, top, (int32_t)n_blocks, (int32_t)n_nodes);
             SBH_TRY(hipGetLastError(), "aggregate kernel");
         }
         if (quadrupole && n_nodes > 1) {
@@ -1057,16 +1108,12 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
             SBH_TRY(hipGetLastError(), "compress kernel");
             for (int l = 1; l < n_levels; ++l) {
                 const double sl = (double)t->side / std::pow((double)d, (double)l);
-                k_compress<<<nblk(lv[l].n), 256, 0, s>>>((int32_t)off[l], lv[l].n, sl, t->nparent, npblk, t->ndigit,
-                                                         agg64, qagg, t->bq, d3);
+                const int32_t cnt = off.node[l + 1] - off.node[l];
+                k_compress<<<nblk(cnt), 256, 0, s>>>(off.node[l], cnt, sl, t->nparent, npblk, t->ndigit, agg64, qagg,
+                                                     t->bq, d3);
                 SBH_TRY(hipGetLastError(), "compress kernel");
             }
         }
-    }
-    if (n_nodes > 1) {
-        k_pack<<<nblk(n_nodes - 1), 256, 0, s>>>((int32_t)n_nodes, npblk, t->ndigit, t->nagg, t->ndip, t->nspr,
-                                                 t->bagg, t->bdip, t->bspr, d3);
-        SBH_TRY(hipGetLastError(), "pack kernel");
     }
     SBH_TRY(hipStreamSynchronize(s), "build sync");
     return SBH_OK;
