@@ -7,7 +7,8 @@
 //      fl32(1/side) (correctly rounded), plus an input validity flag;
 //   2. Morton code: cell_a = min(2^20-1, (u32) fl32(fl32(x_a - lo_a) *
 //      inv_side) * 2^20), bits of x/y/z interleaved into 60 bits;
-//   3. stable LSD radix sort of (code, index), 8-bit digits;
+//   3. stable LSD radix sort of (code, index), 10-bit digits; up to 8192 points
+//      in one workgroup;
 //   4. topology in two passes over the sorted codes.  A node at level l is a
 //      maximal run of equal (bits*l)-bit prefix; it is split iff count >
 //      leaf_size and l < max.  Which levels have a node that starts at point
@@ -34,6 +35,17 @@ namespace sbh {
 // ---------------------------------------------------------------------------
 // 1. Root cube and validation
 // ---------------------------------------------------------------------------
+struct float3v {
+    float x, y, z;
+};
+// a point's three floats in one 12-byte load
+__device__ __forceinline__ float3v load3(const float* __restrict__ p, int64_t i)
+{
+    float3v v;
+    __builtin_memcpy(&v, p + 3 * i, sizeof(v));
+    return v;
+}
+
 constexpr int kBboxThreads = 256;
 
 __global__ void __launch_bounds__(kBboxThreads) k_bbox_partial(const float* __restrict__ src,
@@ -45,13 +57,14 @@ __global__ void __launch_bounds__(kBboxThreads) k_bbox_partial(const float* __re
     float mx0 = -INFINITY, mx1 = -INFINITY, mx2 = -INFINITY;
     int bad = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float x = src[3 * i], y = src[3 * i + 1], z = src[3 * i + 2];
+        const float3v p = load3(src, i);
+        const float x = p.x, y = p.y, z = p.z;
         const float wi = w[i];
         bad |= !(__builtin_isfinite(x) && __builtin_isfinite(y) && __builtin_isfinite(z));
         bad |= !(wi > 0.0f && __builtin_isfinite(wi));
         if (nrm) {
-            const float a = nrm[3 * i], b = nrm[3 * i + 1], c = nrm[3 * i + 2];
-            bad |= !(__builtin_isfinite(a) && __builtin_isfinite(b) && __builtin_isfinite(c));
+            const float3v m = load3(nrm, i);
+            bad |= !(__builtin_isfinite(m.x) && __builtin_isfinite(m.y) && __builtin_isfinite(m.z));
         }
         mn0 = fminf(mn0, x); mn1 = fminf(mn1, y); mn2 = fminf(mn2, z);
         mx0 = fmaxf(mx0, x); mx1 = fmaxf(mx1, y); mx2 = fmaxf(mx2, z);
@@ -132,7 +145,7 @@ __global__ void __launch_bounds__(kBboxThreads) k_bbox_final(const float* __rest
     params[5] = bad;
 }
 
-hipError_t launch_bbox(const float* src, const float* w, const float* nrm, int64_t n, float* params_dev,
+static hipError_t launch_bbox(const float* src, const float* w, const float* nrm, int64_t n, float* params_dev,
                        float* partial_dev, int nblocks, hipStream_t s)
 {
     k_bbox_partial<<<nblocks, kBboxThreads, 0, s>>>(src, w, nrm, n, partial_dev);
@@ -164,33 +177,76 @@ __device__ __forceinline__ uint32_t quantize(float x, float lo, float inv_side)
     return c > 1048575u ? 1048575u : c;
 }
 
-__global__ void k_morton(const float* __restrict__ src, int64_t n, const float* __restrict__ params,
-                         uint64_t* __restrict__ keys, uint32_t* __restrict__ vals)
+__device__ __forceinline__ uint64_t morton_code(float3v x, const float* __restrict__ params)
+{
+    const float inv = params[4];
+    return spread_bits3(quantize(x.x, params[0], inv)) | (spread_bits3(quantize(x.y, params[1], inv)) << 1) |
+           (spread_bits3(quantize(x.z, params[2], inv)) << 2);
+}
+
+__device__ __forceinline__ float4 point_dipole(float3v m, float w) { return make_float4(w * m.x, w * m.y, w * m.z, 0.0f); }
+
+// Codes, and each point as one record of 16 bytes (x, y, z, w), or 32 with its
+// dipole: the sort's permutation then reads one record per point instead of
+// one line from each of the input arrays (2^22 points with normals: the gather
+// 263 -> 99 us, this kernel 50).
+__global__ void k_morton(const float* __restrict__ src, const float* __restrict__ w, const float* __restrict__ nrm,
+                         int64_t n, const float* __restrict__ params, uint64_t* __restrict__ keys,
+                         float4* __restrict__ rec)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float inv = params[4];
-    const uint32_t cx = quantize(src[3 * i], params[0], inv);
-    const uint32_t cy = quantize(src[3 * i + 1], params[1], inv);
-    const uint32_t cz = quantize(src[3 * i + 2], params[2], inv);
-    keys[i] = spread_bits3(cx) | (spread_bits3(cy) << 1) | (spread_bits3(cz) << 2);
-    vals[i] = (uint32_t)i;
+    const float3v x = load3(src, i);
+    const float wi = w[i];
+    keys[i] = morton_code(x, params);
+    const float4 p = make_float4(x.x, x.y, x.z, wi);
+    if (nrm) {
+        rec[2 * i] = p;
+        rec[2 * i + 1] = point_dipole(load3(nrm, i), wi);
+    } else {
+        rec[i] = p;
+    }
 }
 
-hipError_t launch_morton(const float* src, int64_t n, const float* params_dev, uint64_t* keys, uint32_t* vals,
-                         hipStream_t s)
+// the sorted points from their records
+__global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* __restrict__ perm, int64_t n,
+                                float4* __restrict__ pts, float4* __restrict__ pdip)
 {
-    const int64_t nb = (n + 255) / 256;
-    k_morton<<<(unsigned)nb, 256, 0, s>>>(src, n, params_dev, keys, vals);
-    return hipGetLastError();
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= n) return;
+    const int64_t i = perm[s];
+    if (pdip) {
+        const float4 p = rec[2 * i], d = rec[2 * i + 1];
+        pts[s] = p;
+        pdip[s] = d;
+    } else {
+        pts[s] = rec[i];
+    }
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of uint32 (tile scan + recursive scan of tile sums)
+// 3. Stable LSD radix sort of (uint64 code, uint32 index), six passes of
+// 10-bit digits over the 60 bits.  A workgroup owns a tile of 8192
+// consecutive keys, its wavefront v the v-th sixteenth, which it walks in
+// eight chunks of 64 in order: a key's rank among the tile's equal digits is
+// (wavefronts before) + (chunks of this wavefront before) + (lanes of the
+// chunk before), the last from one ballot per digit bit.  A pass is three
+// kernels: the tiles' histograms; their prefix sums over a chunk of tiles,
+// with the chunk's totals; and the scatter, which adds up the chunks before
+// its own, sorts the tile in LDS and writes each digit's keys as one run.
+// Memory traffic and the scatter's latency bound it.  Six passes against the
+// former eight of 8-bit digits, whose scatter wrote every key on its own:
+// 657 -> 345 us for 2^22 keys (the scatter 45 us a pass, 2.2 TB/s).
 // ---------------------------------------------------------------------------
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kRsBits = 10;
+constexpr int kRsBins = 1 << kRsBits;
+constexpr int kRsPasses = 6;
+constexpr int kRsThreads = 1024;
+constexpr int kRsWaves = kRsThreads / 64;
+constexpr int kRsItems = 8;
+constexpr int kRsTile = kRsThreads * kRsItems;
+constexpr int kRsMaxChunks = 64;   // chunks of tiles (every scatter workgroup reads a row of each)
+static_assert(kRsPasses * kRsBits >= 60 && kRsPasses % 2 == 0 && kRsBins == kRsThreads, "radix sort layout");
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane)
 {
@@ -201,226 +257,257 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane)
     return v;
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_scan_tile(const uint32_t* in, uint32_t* out, int64_t n,
-                                                            uint32_t* __restrict__ tile_sums)
+// exclusive scan over the workgroup's 1024 threads; ws: one word per wavefront (reused by the next call)
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* ws)
 {
-    __shared__ uint32_t tile[kScanTile];
-    __shared__ uint32_t wsum[kScanThreads / 64];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t idx = base + k * kScanThreads + threadIdx.x;
-        tile[k * kScanThreads + threadIdx.x] = idx < n ? in[idx] : 0u;
-    }
-    __syncthreads();
-    uint32_t v[kScanItems], tsum = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = tile[threadIdx.x * kScanItems + k];
-        tsum += v[k];
-    }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t incl = wave_inclusive_scan(tsum, lane);
-    if (lane == 63) wsum[wv] = incl;
+    const uint32_t incl = wave_inclusive_scan(v, lane);
+    if (lane == 63) ws[wv] = incl;
     __syncthreads();
-    uint32_t woff = 0, total = 0;
-    for (int k = 0; k < kScanThreads / 64; ++k) {
-        if (k < wv) woff += wsum[k];
-        total += wsum[k];
-    }
-    uint32_t run = woff + incl - tsum;
-    for (int k = 0; k < kScanItems; ++k) {
-        tile[threadIdx.x * kScanItems + k] = run;
-        run += v[k];
-    }
+    uint32_t run = incl - v;
+    for (int k = 0; k < wv; ++k) run += ws[k];
     __syncthreads();
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t idx = base + k * kScanThreads + threadIdx.x;
-        if (idx < n) out[idx] = tile[k * kScanThreads + threadIdx.x];
-    }
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
+    return run;
 }
 
-__global__ void k_scan_add(uint32_t* out, int64_t n, const uint32_t* __restrict__ offs)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < n) out[idx] += offs[idx / kScanTile];
-}
+__device__ __forceinline__ uint32_t rs_digit(uint64_t key, int shift) { return (uint32_t)(key >> shift) & (kRsBins - 1); }
 
-size_t scan_tmp_size(int64_t n)
+// Ranks of the tile's keys within their wavefront's equal digits, and, once all
+// have them, the tile-local position of the first key of each (wavefront,
+// digit): start[digit] + wcnt[wavefront][digit].  cnt: keys of the tile.
+struct RsLds {
+    uint16_t wcnt[kRsWaves][kRsBins];
+    uint32_t start[kRsBins];
+    uint32_t ws[kRsWaves];
+};
+__device__ __forceinline__ void rs_rank(RsLds& S, const uint64_t (&kk)[kRsItems], uint32_t (&rank)[kRsItems], int cnt,
+                                        int shift)
 {
-    size_t total = 1;  // room for the final total
-    while (n > 1) {
-        const int64_t nb = (n + kScanTile - 1) / kScanTile;
-        total += (size_t)nb + 64;
-        n = nb;
-    }
-    return total + 64;
-}
-
-// out may alias in.  *total_dev receives the sum of all inputs.
-hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total_dev, uint32_t* tmp,
-                              hipStream_t s)
-{
-    if (n <= 0) return hipMemsetAsync(total_dev, 0, sizeof(uint32_t), s);
-    const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb == 1) {
-        k_scan_tile<<<1, kScanThreads, 0, s>>>(in, out, n, total_dev);
-        return hipGetLastError();
-    }
-    uint32_t* sums = tmp;
-    k_scan_tile<<<(unsigned)nb, kScanThreads, 0, s>>>(in, out, n, sums);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = scan_exclusive_u32(sums, sums, nb, total_dev, tmp + nb + 64, s);
-    if (e != hipSuccess) return e;
-    k_scan_add<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out, n, sums);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// 3. Stable LSD radix sort of (uint64 key, uint32 value), 8-bit digits.
-// Each block owns a tile of 4096 keys; wave w of the block owns the w-th
-// quarter and walks it in 16 chunks of 64 in order, so ranks computed as
-// (digit offset of the tile) + (earlier waves) + (earlier chunks of this
-// wave) + (earlier lanes of this chunk) preserve the input order of equal
-// digits.
-// ---------------------------------------------------------------------------
-constexpr int kRsThreads = 256;
-constexpr int kRsWaves = kRsThreads / 64;
-constexpr int kRsChunks = 16;
-constexpr int kRsTile = kRsThreads * kRsChunks;
-
-__global__ void __launch_bounds__(kRsThreads) k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
-                                                        uint32_t* __restrict__ hist, int nb)
-{
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int w = 0; w < kRsWaves; ++w) S.wcnt[w][threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int k = 0; k < kRsChunks; ++k) {
-        const int64_t idx = base + k * kRsThreads + threadIdx.x;
-        if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
-}
-
-__global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __restrict__ keys,
-                                                           const uint32_t* __restrict__ vals, int64_t n, int shift,
-                                                           const uint32_t* __restrict__ offs, int nb,
-                                                           uint64_t* __restrict__ kout, uint32_t* __restrict__ vout)
-{
-    __shared__ uint32_t wcnt[kRsWaves][256];
-    __shared__ uint32_t gbase[256];
-    for (int w = 0; w < kRsWaves; ++w) wcnt[w][threadIdx.x] = 0;
-    gbase[threadIdx.x] = offs[(int64_t)threadIdx.x * nb + blockIdx.x];
-    __syncthreads();
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint64_t kk[kRsChunks];
-    uint32_t vv[kRsChunks], rank[kRsChunks], dig[kRsChunks];
-    const int64_t wbase = (int64_t)blockIdx.x * kRsTile + (int64_t)wv * (kRsChunks * 64);
-    for (int c = 0; c < kRsChunks; ++c) {
-        const int64_t idx = wbase + c * 64 + lane;
-        const bool valid = idx < n;
-        const uint64_t key = valid ? keys[idx] : 0ull;
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const bool valid = wv * (64 * kRsItems) + c * 64 + lane < cnt;
+        const uint32_t d = rs_digit(kk[c], shift);
         uint64_t m = __ballot(valid);
-        for (int b = 0; b < 8; ++b) {
+#pragma unroll
+        for (int b = 0; b < kRsBits; ++b) {
             const bool bit = (d >> b) & 1u;
             const uint64_t bb = __ballot(bit);
             m &= bit ? bb : ~bb;
         }
-        const uint32_t below = __popcll(m & lt_mask);
-        const uint32_t cnt = __popcll(m);
-        const uint32_t base = wcnt[wv][d];
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        const uint32_t base = S.wcnt[wv][d];
         __builtin_amdgcn_wave_barrier();
-        if (valid && below == 0) wcnt[wv][d] = base + cnt;
+        if (valid && below == 0) S.wcnt[wv][d] = (uint16_t)(base + (uint32_t)__popcll(m));
         __builtin_amdgcn_wave_barrier();
-        kk[c] = key;
-        vv[c] = valid ? vals[idx] : 0u;
         rank[c] = base + below;
-        dig[c] = valid ? d : 256u;
     }
     __syncthreads();
-    {
-        uint32_t run = 0;
-        for (int w = 0; w < kRsWaves; ++w) {
-            const uint32_t t = wcnt[w][threadIdx.x];
-            wcnt[w][threadIdx.x] = run;
-            run += t;
+    uint32_t run = 0u;   // this thread's digit: the wavefronts' counts become what is before each
+    for (int w = 0; w < kRsWaves; ++w) {
+        const uint32_t t = S.wcnt[w][threadIdx.x];
+        S.wcnt[w][threadIdx.x] = (uint16_t)run;
+        run += t;
+    }
+    S.start[threadIdx.x] = block_exclusive_scan(run, S.ws);
+    __syncthreads();
+}
+
+// tile of a workgroup: consecutive tiles on one die, whose L2 then joins their neighbouring runs
+__device__ __forceinline__ int rs_tile(int b, int tiles)
+{
+    const int per = (tiles + 7) >> 3;
+    return (b & 7) * per + (b >> 3);
+}
+
+__global__ void __launch_bounds__(kRsThreads) k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
+                                                        uint32_t* __restrict__ hist, int tiles)
+{
+    __shared__ uint32_t h[kRsBins];
+    const int tile = rs_tile(blockIdx.x, tiles);
+    if (tile >= tiles) return;
+    h[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t base = (int64_t)tile * kRsTile + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kRsItems; ++k) {
+        const int64_t i = base + k * kRsThreads;
+        if (i < n) atomicAdd(&h[rs_digit(keys[i], shift)], 1u);
+    }
+    __syncthreads();
+    hist[(int64_t)tile * kRsBins + threadIdx.x] = h[threadIdx.x];
+}
+
+// per digit: exclusive prefix sums of the histograms of chunk blockIdx.y's tiles, in place, and its total
+__global__ void __launch_bounds__(256) k_rs_prefix(uint32_t* __restrict__ hist, int tiles, int per,
+                                                   uint32_t* __restrict__ ctot)
+{
+    const int b = blockIdx.x * 256 + threadIdx.x;
+    const int t0 = blockIdx.y * per, t1 = min(tiles, t0 + per);
+    uint32_t run = 0u;
+    for (int t = t0; t < t1; t += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = t + k < t1 ? hist[(int64_t)(t + k) * kRsBins + b] : 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (t + k < t1) hist[(int64_t)(t + k) * kRsBins + b] = run;
+            run += v[k];
+        }
+    }
+    ctot[(int64_t)blockIdx.y * kRsBins + b] = run;
+}
+
+// vin == nullptr: the first pass, where a key's value is its index
+__global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __restrict__ keys,
+                                                           const uint32_t* __restrict__ vin, int64_t n, int shift,
+                                                           const uint32_t* __restrict__ hist, int tiles, int per,
+                                                           int chunks, const uint32_t* __restrict__ ctot,
+                                                           uint64_t* __restrict__ kout, uint32_t* __restrict__ vout)
+{
+    __shared__ RsLds S;
+    __shared__ uint64_t buf[kRsTile];   // the tile's keys in digit order, then its values
+    __shared__ uint32_t gbase[kRsBins];
+    const int tile = rs_tile(blockIdx.x, tiles);
+    if (tile >= tiles) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t base = (int64_t)tile * kRsTile;
+    const int cnt = (int)((n - base) < kRsTile ? (n - base) : kRsTile);
+    uint64_t kk[kRsItems];
+    uint32_t vv[kRsItems], rank[kRsItems];
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = wv * (64 * kRsItems) + c * 64 + lane;
+        kk[c] = p < cnt ? keys[base + p] : 0ull;
+        vv[c] = p < cnt ? (vin ? vin[base + p] : (uint32_t)(base + p)) : 0u;
+    }
+    // where this tile's keys of digit threadIdx.x go
+    uint32_t total = 0u, before = hist[(int64_t)tile * kRsBins + threadIdx.x];
+    const int mine = tile / per;
+    for (int c = 0; c < chunks; ++c) {
+        const uint32_t t = ctot[(int64_t)c * kRsBins + threadIdx.x];
+        before += c < mine ? t : 0u;
+        total += t;
+    }
+    const uint32_t first = block_exclusive_scan(total, S.ws);
+    rs_rank(S, kk, rank, cnt, shift);
+    gbase[threadIdx.x] = first + before - S.start[threadIdx.x];
+    uint32_t lpos[kRsItems];
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = wv * (64 * kRsItems) + c * 64 + lane;
+        const uint32_t d = rs_digit(kk[c], shift);
+        lpos[c] = S.start[d] + S.wcnt[wv][d] + rank[c];
+        if (p < cnt) buf[lpos[c]] = kk[c];
+    }
+    __syncthreads();
+    uint32_t gpos[kRsItems];
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = c * kRsThreads + threadIdx.x;
+        if (p < cnt) {
+            const uint64_t key = buf[p];
+            gpos[c] = gbase[rs_digit(key, shift)] + (uint32_t)p;
+            kout[gpos[c]] = key;
         }
     }
     __syncthreads();
-    for (int c = 0; c < kRsChunks; ++c) {
-        if (dig[c] < 256u) {
-            const uint32_t pos = gbase[dig[c]] + wcnt[wv][dig[c]] + rank[c];
-            kout[pos] = kk[c];
-            vout[pos] = vv[c];
+    uint32_t* vbuf = reinterpret_cast<uint32_t*>(buf);
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c)
+        if (wv * (64 * kRsItems) + c * 64 + lane < cnt) vbuf[lpos[c]] = vv[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = c * kRsThreads + threadIdx.x;
+        if (p < cnt) vout[gpos[c]] = vbuf[p];
+    }
+}
+
+// At most one tile: codes, the whole sort in LDS and the gather in one
+// workgroup, where the passes' launches would cost more than their work.
+__global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restrict__ src, const float* __restrict__ w,
+                                                           const float* __restrict__ nrm, int n,
+                                                           const float* __restrict__ params,
+                                                           uint64_t* __restrict__ codes, uint32_t* __restrict__ perm,
+                                                           float4* __restrict__ pts, float4* __restrict__ pdip)
+{
+    __shared__ RsLds S;
+    __shared__ uint64_t kbuf[kRsTile];
+    __shared__ uint16_t vbuf[kRsTile];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint64_t kk[kRsItems];
+    uint32_t vv[kRsItems], rank[kRsItems];
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = wv * (64 * kRsItems) + c * 64 + lane;
+        kk[c] = p < n ? morton_code(load3(src, p), params) : 0ull;
+        vv[c] = (uint32_t)p;
+    }
+    for (int pass = 0; pass < kRsPasses; ++pass) {
+        const int shift = pass * kRsBits;
+        rs_rank(S, kk, rank, n, shift);
+#pragma unroll
+        for (int c = 0; c < kRsItems; ++c) {
+            const int p = wv * (64 * kRsItems) + c * 64 + lane;
+            const uint32_t d = rs_digit(kk[c], shift);
+            const uint32_t l = S.start[d] + S.wcnt[wv][d] + rank[c];
+            if (p < n) {
+                kbuf[l] = kk[c];
+                vbuf[l] = (uint16_t)vv[c];
+            }
         }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kRsItems; ++c) {
+            const int p = wv * (64 * kRsItems) + c * 64 + lane;
+            kk[c] = p < n ? kbuf[p] : 0ull;
+            vv[c] = p < n ? vbuf[p] : 0u;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {
+        const int p = wv * (64 * kRsItems) + c * 64 + lane;
+        if (p >= n) continue;
+        const float3v x = load3(src, vv[c]);
+        const float wi = w[vv[c]];
+        codes[p] = kk[c];
+        perm[p] = vv[c];
+        pts[p] = make_float4(x.x, x.y, x.z, wi);
+        if (pdip) pdip[p] = point_dipole(load3(nrm, vv[c]), wi);
     }
 }
 
-size_t radix_sort_hist_size(int64_t n)
-{
-    const int64_t nb = (n + kRsTile - 1) / kRsTile;
-    return (size_t)nb * 256;
-}
+// Scratch of the sort beside the second key and value buffers: the histograms and the chunks' totals.
+static int rs_tiles(int64_t n) { return (int)((n + kRsTile - 1) / kRsTile); }
+static int rs_per_chunk(int tiles) { return std::max(32, (tiles + kRsMaxChunks - 1) / kRsMaxChunks); }
 
-hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
-                            int begin_bit, int end_bit, uint32_t* hist, uint32_t* scan_tmp, hipStream_t s)
+// codes (in keys) and indices 0 .. n - 1 sorted into keys and vals
+static hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
+                                   uint32_t* hist, uint32_t* ctot, hipStream_t s)
 {
-    const int nb = (int)((n + kRsTile - 1) / kRsTile);
-    uint64_t *ks = keys, *kd = keys_tmp;
-    uint32_t *vs = vals, *vd = vals_tmp;
-    int passes = 0;
-    for (int shift = begin_bit; shift < end_bit; shift += 8, ++passes) {
-        k_rs_hist<<<nb, kRsThreads, 0, s>>>(ks, n, shift, hist, nb);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        e = scan_exclusive_u32(hist, hist, (int64_t)nb * 256, scan_tmp, scan_tmp + 1, s);
-        if (e != hipSuccess) return e;
-        k_rs_scatter<<<nb, kRsThreads, 0, s>>>(ks, vs, n, shift, hist, nb, kd, vd);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        uint64_t* tk = ks; ks = kd; kd = tk;
-        uint32_t* tv = vs; vs = vd; vd = tv;
-    }
-    if (passes & 1) {
-        hipError_t e = hipMemcpyAsync(keys, ks, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return e;
-        e = hipMemcpyAsync(vals, vs, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
+    const int tiles = rs_tiles(n), per = rs_per_chunk(tiles), chunks = (tiles + per - 1) / per;
+    const unsigned grid = (unsigned)((tiles + 7) / 8 * 8);
+    for (int pass = 0; pass < kRsPasses; ++pass) {
+        const int shift = pass * kRsBits;
+        const bool even = pass % 2 == 0;
+        const uint64_t* ks = even ? keys : keys_tmp;
+        k_rs_hist<<<grid, kRsThreads, 0, s>>>(ks, n, shift, hist, tiles);
+        k_rs_prefix<<<dim3(kRsBins / 256, (unsigned)chunks), 256, 0, s>>>(hist, tiles, per, ctot);
+        k_rs_scatter<<<grid, kRsThreads, 0, s>>>(ks, pass == 0 ? nullptr : even ? vals : vals_tmp, n, shift, hist, tiles,
+                                                 per, chunks, ctot, even ? keys_tmp : keys, even ? vals_tmp : vals);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
-// 4. Levels
+// 4. Topology
 // ---------------------------------------------------------------------------
-struct float3v {
-    float x, y, z;
-};
-
-__global__ void k_gather_points(const float* __restrict__ src, const float* __restrict__ w,
-                                const float* __restrict__ nrm, const uint32_t* __restrict__ perm, int64_t n,
-                                float4* __restrict__ pts, float4* __restrict__ pdip)
-{
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const uint32_t i = perm[s];
-    const float wi = w[i];
-    // a point's three floats in one 12-byte load: the reads are random, so each
-    // separate load would be another cache-line request
-    float3v x;
-    __builtin_memcpy(&x, src + 3 * (int64_t)i, sizeof(x));
-    pts[s] = make_float4(x.x, x.y, x.z, wi);
-    if (pdip) {
-        float3v m;
-        __builtin_memcpy(&m, nrm + 3 * (int64_t)i, sizeof(m));
-        pdip[s] = make_float4(wi * m.x, wi * m.y, wi * m.z, 0.0f);
-    }
-}
-
 // Level of the deepest node that holds both codes: their common leading digits
 // (60 / bits for equal codes).
 __device__ __forceinline__ int common_level(uint64_t a, uint64_t b, int bits)
@@ -972,22 +1059,7 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
     float* partial = tmp.alloc<float>((int64_t)nbb * 8);
     SBH_ALLOC_OK("allocating bbox buffers");
     SBH_TRY(launch_bbox(src, w, nrm, n, params, partial, nbb, s), "bbox kernel");
-    // 2-3. codes and sort
-    uint64_t* keys = tmp.alloc<uint64_t>(n);
-    uint32_t* vals = tmp.alloc<uint32_t>(n);
-    uint64_t* keys2 = tmp.alloc<uint64_t>(n);
-    uint32_t* vals2 = tmp.alloc<uint32_t>(n);
-    uint32_t* hist = tmp.alloc<uint32_t>((int64_t)radix_sort_hist_size(n));
-    uint32_t* stmp = tmp.alloc<uint32_t>((int64_t)scan_tmp_size((int64_t)radix_sort_hist_size(n)) + 8);
-    const int64_t nblocks = (n + kTopoPoints - 1) / kTopoPoints;
-    const int channels = 2 * (max_level + 1);
-    uint16_t* marks = tmp.alloc<uint16_t>(n);
-    uint32_t* counts = tmp.alloc<uint32_t>(nblocks * channels);
-    SBH_ALLOC_OK("allocating sort buffers");
-    SBH_TRY(launch_morton(src, n, params, keys, vals, s), "morton kernel");
-    SBH_TRY(radix_sort_pairs(keys, vals, keys2, vals2, n, 0, 64, hist, stmp, s), "radix sort");
-
-    // sorted points (owned by the tree)
+    // 2-3. codes, sort and the sorted points, in the tree's arrays
     t->slab_bytes[0] = carve_bytes<float4>(n) * (nrm ? 2 : 1) + carve_bytes<uint32_t>(n) + carve_bytes<uint64_t>(n);
     SBH_TRY(dev_alloc(t->mem, &t->slab[0], t->slab_bytes[0], s), "allocating points");
     {
@@ -997,10 +1069,28 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
         t->perm = c.take<uint32_t>(n);
         t->codes = c.take<uint64_t>(n);
     }
-    k_gather_points<<<nblk(n), 256, 0, s>>>(src, w, nrm, vals, n, t->pts, t->pdip);
-    SBH_TRY(hipGetLastError(), "gather kernel");
-    SBH_TRY(hipMemcpyAsync(t->perm, vals, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s), "perm copy");
-    SBH_TRY(hipMemcpyAsync(t->codes, keys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s), "codes copy");
+    const int64_t nblocks = (n + kTopoPoints - 1) / kTopoPoints;
+    const int channels = 2 * (max_level + 1);
+    uint16_t* marks = tmp.alloc<uint16_t>(n);
+    uint32_t* counts = tmp.alloc<uint32_t>(nblocks * channels);
+    SBH_ALLOC_OK("allocating topology buffers");
+    if (n <= kRsTile) {
+        k_sort_small<<<1, kRsThreads, 0, s>>>(src, w, nrm, (int)n, params, t->codes, t->perm, t->pts, t->pdip);
+        SBH_TRY(hipGetLastError(), "sort kernel");
+    } else {
+        const int64_t tiles = rs_tiles(n);
+        uint64_t* keys2 = tmp.alloc<uint64_t>(n);
+        uint32_t* vals2 = tmp.alloc<uint32_t>(n);
+        float4* rec = tmp.alloc<float4>(nrm ? 2 * n : n);
+        uint32_t* hist = tmp.alloc<uint32_t>(tiles * kRsBins);
+        uint32_t* ctot = tmp.alloc<uint32_t>((int64_t)kRsMaxChunks * kRsBins);
+        SBH_ALLOC_OK("allocating sort buffers");
+        k_morton<<<nblk(n), 256, 0, s>>>(src, w, nrm, n, params, t->codes, rec);
+        SBH_TRY(hipGetLastError(), "morton kernel");
+        SBH_TRY(radix_sort_pairs(t->codes, t->perm, keys2, vals2, n, hist, ctot, s), "radix sort");
+        k_gather_points<<<nblk(n), 256, 0, s>>>(rec, t->perm, n, t->pts, t->pdip);
+        SBH_TRY(hipGetLastError(), "gather kernel");
+    }
     const uint64_t* codes = t->codes;
 
     // 4. topology: the marks and counts, then the sizes

@@ -351,19 +351,6 @@ __device__ __forceinline__ float query_value(float F, float r0, float logwbar, f
 // ---------------------------------------------------------------------------
 // Host-side launchers (defined in the .hip files).  All return hipError_t.
 // ---------------------------------------------------------------------------
-struct BuildScratch;
-
-hipError_t launch_bbox(const float* src, const float* w, const float* nrm, int64_t n, float* params_dev,
-                       float* partial_dev, int nblocks, hipStream_t s);
-hipError_t launch_morton(const float* src, int64_t n, const float* params_dev, uint64_t* keys, uint32_t* vals,
-                         hipStream_t s);
-hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
-                            int begin_bit, int end_bit, uint32_t* hist, uint32_t* scan_tmp, hipStream_t s);
-size_t radix_sort_hist_size(int64_t n);
-hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total_dev, uint32_t* tmp,
-                              hipStream_t s);
-size_t scan_tmp_size(int64_t n);
-
 struct EvalLaunch {
     int kernel;
     int samples;
