@@ -535,6 +535,27 @@ __device__ __forceinline__ uint16_t pack_mark(Mark m) { return (uint16_t)(m.s | 
 __device__ __forceinline__ Mark unpack_mark(uint16_t v) { return {v & 31, (v >> 5) & 31, (int)(v >> 10) - 1}; }
 constexpr uint16_t kNoNode = 31;   // s = 31, e = 0, w = -1
 
+// adds to lane l the wavefront's nodes and internal nodes of level l
+__device__ __forceinline__ void count_levels(Mark m, int lane, uint32_t& cn, uint32_t& ci)
+{
+    uint64_t todo = __ballot(m.s <= m.e);   // the points with nodes; each round takes the levels of the first one left
+    for (uint32_t seen = 0u; todo != 0ull;) {
+        const int p = (int)__builtin_ctzll(todo);
+        const int s = __builtin_amdgcn_readlane(m.s, p), e = __builtin_amdgcn_readlane(m.e, p);
+        for (uint32_t ls = ((2u << e) - (1u << s)) & ~seen; ls != 0u; ls &= ls - 1u) {
+            const int l = (int)__builtin_ctz(ls);
+            const uint64_t nm = __ballot(m.s <= l && l <= m.e), im = __ballot(m.s <= l && l <= m.w);
+            if (lane == l) {
+                cn += (uint32_t)__popcll(nm);
+                ci += (uint32_t)__popcll(im);
+            }
+        }
+        seen |= (2u << e) - (1u << s);
+        // the points whose levels have all been seen
+        todo &= __ballot((((2u << m.e) - (1u << m.s)) & ~seen) != 0u);
+    }
+}
+
 // Marks of every point, and per block of kTopoPoints points the number of
 // nodes (channel 2 l) and internal nodes (2 l + 1) of each level that start in
 // it: counts[channel * gridDim.x + block].  One ballot per level and wavefront
@@ -573,13 +594,7 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __re
             }
             marks[i] = pack_mark(m);
         }
-        for (int l = 0; l <= max_level; ++l) {
-            const uint64_t nm = __ballot(m.s <= l && l <= m.e), im = __ballot(m.s <= l && l <= m.w);
-            if (lane == l) {
-                cn += (uint32_t)__popcll(nm);
-                ci += (uint32_t)__popcll(im);
-            }
-        }
+        count_levels(m, lane, cn, ci);
     }
     if (lane < kTopoLevels) {
         wc[wv][0][lane] = cn;
@@ -709,40 +724,75 @@ __device__ __forceinline__ void aggregate_leaf(const BuildArrays& a, int32_t g, 
 }
 
 // internal node of block k: its children are nodes bfirst[k] .. bfirst[k + 1] - 1 (the children of
-// consecutive blocks follow one another through all levels)
+// consecutive blocks follow one another through all levels).  Children are read eight at a time,
+// all loads in flight together (an octree node's once for both sums).
 __device__ __forceinline__ void aggregate_block(const BuildArrays& a, int32_t k, int32_t n_blocks, int32_t n_nodes)
 {
 #pragma clang fp contract(off)
     const int32_t g = a.inode[k], f = a.bfirst[k], e = k + 1 < n_blocks ? a.bfirst[k + 1] : n_nodes;
+    const int32_t pblk = a.npblk[g], digit = a.ndigit[g];
     double m = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
     uint32_t count = 0u;
-    for (int32_t c = f; c < e; ++c) {
-        const double4 q = a.agg64[c];
-        m += q.w; sx += q.w * q.x; sy += q.w * q.y; sz += q.w * q.z;
-        count += (uint32_t)a.ncount[c];
-        if (a.has_dip) { const double4 d = a.dip64[c]; dx += d.x; dy += d.y; dz += d.z; }
+    double4 q[8];
+    double sp[8];
+    for (int32_t c = f; c < e; c += 8) {
+        int32_t nc[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int32_t x = c + t < e ? c + t : e - 1;   // (past the end: the last child, unused)
+            q[t] = a.agg64[x];
+            sp[t] = a.spr64[x];
+            nc[t] = a.ncount[x];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (c + t >= e) continue;
+            m += q[t].w; sx += q[t].w * q[t].x; sy += q[t].w * q[t].y; sz += q[t].w * q[t].z;
+            count += (uint32_t)nc[t];
+        }
     }
     const double cx = sx / m, cy = sy / m, cz = sz / m;
     double s2 = 0.0;
-    for (int32_t c = f; c < e; ++c) {
-        const double4 q = a.agg64[c];
-        const double ex = q.x - cx, ey = q.y - cy, ez = q.z - cz;
-        s2 += q.w * (a.spr64[c] + (ex * ex + ey * ey + ez * ez));
+    for (int32_t c = f; c < e; c += 8) {
+        if (e - f > 8) {   // d = 4 and 8: this group's again
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int32_t x = c + t < e ? c + t : e - 1;
+                q[t] = a.agg64[x];
+                sp[t] = a.spr64[x];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (c + t >= e) continue;
+            const double ex = q[t].x - cx, ey = q[t].y - cy, ez = q[t].z - cz;
+            s2 += q[t].w * (sp[t] + (ex * ex + ey * ey + ez * ez));
+        }
     }
     s2 /= m;
+    if (a.has_dip) {
+        for (int32_t c = f; c < e; c += 4) {
+            double4 d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] = a.dip64[c + t < e ? c + t : e - 1];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (c + t < e) { dx += d[t].x; dy += d[t].y; dz += d[t].z; }
+        }
+    }
     if (a.quad64) {   // parallel-axis rule: Q = sum_c (Q_c + m_c (c_c - c)(c_c - c)^T)
         double Q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         for (int32_t c = f; c < e; ++c) {
-            const double4 q = a.agg64[c];
+            const double4 qq = a.agg64[c];
             const double* qc = a.quad64 + 6 * (int64_t)c;
-            const double ex = q.x - cx, ey = q.y - cy, ez = q.z - cz;
-            Q[0] += qc[0] + q.w * ex * ex; Q[1] += qc[1] + q.w * ey * ey; Q[2] += qc[2] + q.w * ez * ez;
-            Q[3] += qc[3] + q.w * ex * ey; Q[4] += qc[4] + q.w * ex * ez; Q[5] += qc[5] + q.w * ey * ez;
+            const double ex = qq.x - cx, ey = qq.y - cy, ez = qq.z - cz;
+            Q[0] += qc[0] + qq.w * ex * ex; Q[1] += qc[1] + qq.w * ey * ey; Q[2] += qc[2] + qq.w * ez * ez;
+            Q[3] += qc[3] + qq.w * ex * ey; Q[4] += qc[4] + qq.w * ex * ez; Q[5] += qc[5] + qq.w * ey * ez;
         }
         for (int t = 0; t < 6; ++t) a.quad64[6 * (int64_t)g + t] = Q[t];
     }
     a.nnchild[g] = e - f;
-    store_node(a, g, a.npblk[g], a.ndigit[g], count, m, cx, cy, cz, s2, dx, dy, dz);
+    store_node(a, g, pblk, digit, count, m, cx, cy, cz, s2, dx, dy, dz);
 }
 
 // the internal nodes of one level
@@ -760,13 +810,13 @@ struct TopoOff {
 
 // The internal nodes of levels top .. 0, which hold few nodes each, in one
 // workgroup: a launch per level costs more than its work.
-constexpr int kTopNodes = 1024;
-__global__ void __launch_bounds__(kTopNodes) k_aggregate_top(BuildArrays a, TopoOff off, int top, int32_t n_blocks,
+constexpr int kTopThreads = 512, kTopNodes = 1024;
+__global__ void __launch_bounds__(kTopThreads) k_aggregate_top(BuildArrays a, TopoOff off, int top, int32_t n_blocks,
                                                              int32_t n_nodes)
 {
     for (int l = top; l >= 0; --l) {
-        const int32_t k = off.blk[l] + (int32_t)threadIdx.x;
-        if (k < off.blk[l + 1]) aggregate_block(a, k, n_blocks, n_nodes);
+        for (int32_t k = off.blk[l] + (int32_t)threadIdx.x; k < off.blk[l + 1]; k += kTopThreads)
+            aggregate_block(a, k, n_blocks, n_nodes);
         __threadfence_block();
         __syncthreads();
     }
@@ -777,37 +827,37 @@ __global__ void __launch_bounds__(kTopNodes) k_aggregate_top(BuildArrays a, Topo
 // (counts of the blocks before, of the block's wavefronts before, and a
 // ballot).  The last node of level l - 1 to start at or before the point is
 // its parent, and the first child of a node that starts at the point is its
-// node of the next level.  A point has at most one leaf (its deepest node),
-// whose aggregates follow once the levels are done.
+// node of the next level.  A point with nodes has one leaf (its deepest node);
+// the block collects its leaves in LDS and takes their aggregates with every
+// lane busy.  Vector issue (the levels' ballots, the float64 divisions) and the
+// writes, about 180 bytes a node, bound it.
 __global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __restrict__ codes,
                                                             const uint16_t* __restrict__ marks, int64_t n,
                                                             const uint32_t* __restrict__ counts, TopoOff off,
-                                                            int depth, int bits, int leaf, int max_level,
-                                                            BuildArrays a, const float4* __restrict__ pts,
+                                                            int depth, int bits, BuildArrays a, const float4* __restrict__ pts,
                                                             const float4* __restrict__ pdip)
 {
     __shared__ uint32_t wc[kTopoThreads / 64][2][kTopoLevels];
+    __shared__ int4 leaves[kTopoPoints];   // {node, parent's block, digit, first point} of the block's leaves
+    __shared__ int n_leaves[kTopoThreads / 64 + 1];
     const int64_t base = (int64_t)blockIdx.x * kTopoPoints;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     uint16_t mk[kTopoChunks];
     uint32_t cn = 0u, ci = 0u;   // lane l: level l's nodes and internal nodes before the wavefront's current chunk
+    int nl = 0;                  // leaves of the wavefront: one for every point with a node
 #pragma unroll
     for (int c = 0; c < kTopoChunks; ++c) {
         const int64_t i = base + (wv * kTopoChunks + c) * 64 + lane;
         mk[c] = i < n ? marks[i] : kNoNode;
         const Mark m = unpack_mark(mk[c]);
-        for (int l = 0; l <= depth; ++l) {
-            const uint64_t nm = __ballot(m.s <= l && l <= m.e), im = __ballot(m.s <= l && l <= m.w);
-            if (lane == l) {
-                cn += (uint32_t)__popcll(nm);
-                ci += (uint32_t)__popcll(im);
-            }
-        }
+        count_levels(m, lane, cn, ci);
+        nl += (int)__popcll(__ballot(m.s <= m.e));
     }
     if (lane < kTopoLevels) {
         wc[wv][0][lane] = cn;
         wc[wv][1][lane] = ci;
     }
+    if (lane == 0) n_leaves[wv] = nl;
     __syncthreads();
     cn = ci = 0u;
     if (lane <= depth) {
@@ -818,22 +868,36 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __re
             ci += wc[v][1][lane];
         }
     }
+    int leaf0 = 0, all_leaves = 0;   // leaves of the wavefronts before, and of the block
+    for (int v = 0; v < kTopoThreads / 64; ++v) {
+        leaf0 += v < wv ? n_leaves[v] : 0;
+        all_leaves += n_leaves[v];
+    }
 #pragma unroll
     for (int c = 0; c < kTopoChunks; ++c) {
         const int64_t i = base + (wv * kTopoChunks + c) * 64 + lane;
         const Mark m = unpack_mark(mk[c]);
-        if (__ballot(m.s <= m.e) == 0ull) continue;   // no node starts here
+        const uint64_t has = __ballot(m.s <= m.e);
+        if (has == 0ull) continue;   // no node starts here
         const uint64_t code = i < n ? codes[i] : 0ull;
         int32_t id = -1, blk = -1;               // this point's node of the level before, its block
         int32_t before_n = 0, before_b = 0;      // nodes and blocks of the level before that start at or before it
-        int32_t leaf_id = -1, leaf_pblk = -1, leaf_digit = 0;
+        int4 lf = make_int4(-1, -1, 0, (int)i);
         for (int l = 0; l <= depth; ++l) {
             const bool node = m.s <= l && l <= m.e, inner = m.s <= l && l <= m.w;
             const uint64_t nm = __ballot(node), im = __ballot(inner);
-            const int32_t rn = (int32_t)__builtin_amdgcn_readlane((int)cn, l) +
-                               (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
-            const int32_t ri = (int32_t)__builtin_amdgcn_readlane((int)ci, l) +
-                               (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(im >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)im, 0u));
+            int32_t rn = (int32_t)__builtin_amdgcn_readlane((int)cn, l), ri = (int32_t)__builtin_amdgcn_readlane((int)ci, l);
+            if (nm == 0ull) {   // (a node of this level starts wherever an internal one of the level before does)
+                before_n = rn;
+                before_b = ri;
+                continue;
+            }
+            if (lane == l) {
+                cn += (uint32_t)__popcll(nm);
+                ci += (uint32_t)__popcll(im);
+            }
+            rn += (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
+            ri += (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(im >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)im, 0u));
             if (blk >= 0) {   // the point's internal node of the level before: its children start here
                 a.nfirst[id] = off.node[l] + rn;
                 a.bfirst[blk] = off.node[l] + rn;
@@ -855,34 +919,36 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __re
                 } else {
                     a.nfirst[id] = -1;
                     a.nnchild[id] = 0;
-                    leaf_id = id;
-                    leaf_pblk = pblk;
-                    leaf_digit = digit;
+                    lf = make_int4(id, pblk, digit, (int)i);
                 }
             }
             before_n = rn + (node ? 1 : 0);
             before_b = ri + (inner ? 1 : 0);
-            if (lane == l) {
-                cn += (uint32_t)__popcll(nm);
-                ci += (uint32_t)__popcll(im);
-            }
         }
-        if (leaf_id >= 0) {
-            // its end: within leaf_size points, except at the deepest level
+        if (lf.x >= 0)
+            leaves[leaf0 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u))] = lf;
+        leaf0 += (int)__popcll(has);
+    }
+    __syncthreads();
+    // the leaves' aggregates, a thread each: a leaf ends where the next point with a node starts
+    for (int k = threadIdx.x; k < all_leaves; k += kTopoThreads) {
+        const int4 lf = leaves[k];
+        int64_t end;
+        if (k + 1 < all_leaves) {
+            end = leaves[k + 1].w;
+        } else {   // the block's last leaf: the first point past its cell
+            const Mark m = unpack_mark(marks[lf.w]);
             const int shift = 60 - bits * m.e;
-            const uint64_t pre = code >> shift;
-            int64_t end = i + 1;
-            while (end < n && end <= i + leaf && (codes[end] >> shift) == pre) ++end;
-            if (end == i + leaf + 1 && end < n && (codes[end] >> shift) == pre) {   // the first code past the prefix
-                int64_t hi = n;
-                while (end < hi) {
-                    const int64_t mid = end + ((hi - end) >> 1);
-                    if ((codes[mid] >> shift) == pre) end = mid + 1;
-                    else hi = mid;
-                }
+            const uint64_t pre = codes[lf.w] >> shift;
+            int64_t hi = n;
+            end = (int64_t)lf.w + 1;
+            while (end < hi) {
+                const int64_t mid = end + ((hi - end) >> 1);
+                if ((codes[mid] >> shift) == pre) end = mid + 1;
+                else hi = mid;
             }
-            aggregate_leaf(a, leaf_id, leaf_pblk, leaf_digit, (int32_t)i, (int32_t)end, pts, pdip);
         }
+        aggregate_leaf(a, lf.x, lf.y, lf.z, lf.w, (int32_t)end, pts, pdip);
     }
 }
 
@@ -1173,8 +1239,8 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
         const BuildArrays a{t->nbegin, t->ncount, t->nlevel, t->ndigit, t->nparent, t->nfirst, t->nnchild, npblk,
                             t->nagg,   t->ndip,   t->nspr,   agg64,     dip64,      spr64,     quad64,     inode,
                             bfirst,    t->btopo,  t->bagg,   t->bdip,   t->bspr,    ts,        d3,         nrm ? 1 : 0};
-        k_topo_emit<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(codes, marks, n, counts, off, t->depth, bits, leaf_size,
-                                                               max_level, a, t->pts, t->pdip);
+        k_topo_emit<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(codes, marks, n, counts, off, t->depth, bits, a, t->pts,
+                                                               t->pdip);
         SBH_TRY(hipGetLastError(), "topology kernel");
         int top = -1;   // levels 0 .. top hold at most kTopNodes internal nodes each
         while (top + 1 < n_levels - 1 && off.blk[top + 2] - off.blk[top + 1] <= kTopNodes) ++top;
@@ -1184,7 +1250,7 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
             SBH_TRY(hipGetLastError(), "aggregate kernel");
         }
         if (top >= 0) {
-            k_aggregate_top<<<1, kTopNodes, 0, s>>>(a, off, top, (int32_t)n_blocks, (int32_t)n_nodes);
+            k_aggregate_top<<<1, kTopThreads, 0, s>>>(a, off, top, (int32_t)n_blocks, (int32_t)n_nodes);
             SBH_TRY(hipGetLastError(), "aggregate kernel");
         }
         if (quadrupole && n_nodes > 1) {
