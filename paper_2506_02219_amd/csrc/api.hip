@@ -52,7 +52,7 @@ std::mutex g_alloc_mu;
 sbh::Allocator g_alloc{nullptr, nullptr, nullptr};
 
 // The static workspace of sbh_mlp_train_noalloc: the partial gradients of one batch (one row of
-// 1616 floats per 64 rows) and the summed gradient (1616 floats).  Every GPU the library runs on
+// 1616 floats per 64 rows, and one spare).  Every GPU the library runs on
 // holds its own copy until the process ends.  In host code `scratch` names a host-side stand-in,
 // not device memory: kernels get the per-device address that hipGetSymbolAddress returns.
 constexpr size_t kScratchFloats = (size_t)(SBH_NOALLOC_MAX_BATCH_ROWS / 64 + 1) * 1616;
@@ -619,16 +619,14 @@ sbh_status sbh_mlp_train(float* params, float* adam_state, const float* features
     float* work = nullptr;
     const size_t pf = sbh::mlp_partial_floats(b);
     const sbh::Allocator mem = sbh::allocator_current();
-    const size_t wbytes = (pf + 1616) * sizeof(float);
+    const size_t wbytes = pf * sizeof(float);
     hipError_t e = sbh::dev_alloc(mem, (void**)&work, wbytes, stream);
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_train: workspace");
-    float* grad = work + pf;
     for (int32_t s = 0; s < steps && e == hipSuccess; ++s) {
         const int64_t row_begin = ((int64_t)(step0 + s) * b) % n;
         const int64_t rows = (n - row_begin) < b ? (n - row_begin) : b;
-        e = sbh::launch_mlp_grad(params, features, targets, counts, n, row_begin, rows, work, grad, stream);
-        if (e == hipSuccess)
-            e = sbh::launch_mlp_adam(params, adam_state, grad, lr, step0 + s, losses ? losses + s : nullptr, stream);
+        e = sbh::launch_mlp_step(params, adam_state, features, targets, counts, n, row_begin, rows, work, lr, step0 + s,
+                                 losses ? losses + s : nullptr, stream);
     }
     sbh::dev_free(mem, work, wbytes, stream);
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_train: kernel launch");
@@ -653,14 +651,12 @@ sbh_status sbh_mlp_train_noalloc(float* params, float* adam_state, const float* 
     const hipError_t e0 = scratch_ptr(&work);
     if (e0 != hipSuccess) return hip_fail(e0, "sbh_mlp_train_noalloc: address of the static workspace");
     const int64_t b = batch_rows < n ? batch_rows : n;
-    float* grad = work + sbh::mlp_partial_floats(b);
     hipError_t e = hipSuccess;
     for (int32_t s = 0; s < steps && e == hipSuccess; ++s) {
         const int64_t row_begin = ((int64_t)(step0 + s) * b) % n;
         const int64_t rows = (n - row_begin) < b ? (n - row_begin) : b;
-        e = sbh::launch_mlp_grad(params, features, targets, counts, n, row_begin, rows, work, grad, stream);
-        if (e == hipSuccess)
-            e = sbh::launch_mlp_adam(params, adam_state, grad, lr, step0 + s, losses ? losses + s : nullptr, stream);
+        e = sbh::launch_mlp_step(params, adam_state, features, targets, counts, n, row_begin, rows, work, lr, step0 + s,
+                                 losses ? losses + s : nullptr, stream);
     }
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_train_noalloc: kernel launch");
     return SBH_OK;

@@ -237,81 +237,116 @@ struct TrainLds {
     _Float16 x[64 * 16], h1[64 * 32], h2[64 * 32], dz[64 * 16], dh2[64 * 32], dh1[64 * 32];
     float zf[64 * 16], dh2f[64 * 32], dh1f[64 * 32];
     float xf[64 * 8];   // float32 features (skip term)
+    float tg[64 * 8], cn[64 * 8];
+    float b1[32], b2[32], b3[8];
+    float loss[64];
+    int valid[64];
 };
 
 constexpr int kGradStride = 1608 + 8;   // partial-gradient row: 1608 parameters, then the loss
 
+// one wavefront's LDS stores become visible to its own loads
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Rows [row_begin + 64 b, row_begin + 64 b + 64) for block b; rows >= n or
 // with all counts 0 contribute nothing.  Sums (not means) over the rows:
 // the deltas stay O(1) in binary16; k_mlp_reduce divides by the row count.
-__global__ void __launch_bounds__(64) k_mlp_grad(const float* __restrict__ prm, const float* __restrict__ X,
-                                                 const float* __restrict__ Tg, const float* __restrict__ Cn, int64_t n,
-                                                 int64_t row_begin, int64_t rows, float* __restrict__ partial)
+// The chain of dependent layers bounds it, not the matrix units: wavefront g
+// takes the 16 rows of group g through both directions on its own, and then a
+// quarter of the weight gradients' tiles over all 64 rows (one wavefront for
+// all groups in turn took 21.5 us for 8192 rows, now 12.0; four lanes a row in
+// the softmax made no difference).
+__global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm, const float* __restrict__ X,
+                                                  const float* __restrict__ Tg, const float* __restrict__ Cn, int64_t n,
+                                                  int64_t row_begin, int64_t rows, float* __restrict__ partial)
 {
     __shared__ TrainLds S;
-    const int l = threadIdx.x, r = l & 15, hi = l >> 4, q = hi * 4;
-    for (int i = l; i < 32 * 16; i += 64) S.w1[i] = (i % 16) < 8 ? (_Float16)prm[kOffW1 + (i / 16) * 8 + (i % 16)] : (_Float16)0.0f;
-    for (int i = l; i < 32 * 32; i += 64) S.w2[i] = (_Float16)prm[kOffW2 + i];
-    for (int i = l; i < 16 * 32; i += 64) S.w3[i] = (i / 32) < 8 ? (_Float16)prm[kOffW3 + i] : (_Float16)0.0f;
-    // this lane's row
-    const int64_t rel = (int64_t)blockIdx.x * 64 + l;
-    const int64_t row = row_begin + rel;
-    bool valid = rel < rows && row < n;
-    float tg[8], cn[8];
-    float csum = 0.0f;
-    for (int k = 0; k < 8; ++k) {
-        tg[k] = valid ? Tg[8 * row + k] : 0.0f;
-        cn[k] = valid ? Cn[8 * row + k] : 0.0f;
-        csum += cn[k];
-        const float xv = valid ? X[8 * row + k] : 0.0f;
-        S.xf[l * 8 + k] = xv;
-        S.x[l * 16 + k] = (_Float16)xv;
-        S.x[l * 16 + 8 + k] = (_Float16)0.0f;
+    const int tid = threadIdx.x, l = tid & 63, r = l & 15, q = (l >> 4) * 4;
+    const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
+    {   // thread t: two columns of row t / 4
+        const int row = tid >> 2, k = (tid & 3) * 2;
+        const int64_t rel = (int64_t)blockIdx.x * 64 + row, at = 8 * (row_begin + rel) + k;
+        const bool in = rel < rows && row_begin + rel < n;
+        const float2 zero2 = make_float2(0.f, 0.f);
+        const float2 x = in ? make_float2(X[at], X[at + 1]) : zero2;
+        const float2 t = in ? make_float2(Tg[at], Tg[at + 1]) : zero2;
+        const float2 c = in ? make_float2(Cn[at], Cn[at + 1]) : zero2;
+        S.xf[row * 8 + k] = x.x;
+        S.xf[row * 8 + k + 1] = x.y;
+        S.x[row * 16 + k] = (_Float16)x.x;
+        S.x[row * 16 + k + 1] = (_Float16)x.y;
+        S.x[row * 16 + 8 + k] = (_Float16)0.0f;
+        S.x[row * 16 + 9 + k] = (_Float16)0.0f;
+        S.tg[row * 8 + k] = t.x;
+        S.tg[row * 8 + k + 1] = t.y;
+        S.cn[row * 8 + k] = c.x;
+        S.cn[row * 8 + k + 1] = c.y;
     }
-    valid = valid && csum > 0.0f;
+#pragma unroll
+    for (int i = tid; i < 32 * 16; i += 256) S.w1[i] = (i % 16) < 8 ? (_Float16)prm[kOffW1 + (i / 16) * 8 + (i % 16)] : (_Float16)0.0f;
+#pragma unroll
+    for (int i = tid; i < 32 * 32; i += 256) S.w2[i] = (_Float16)prm[kOffW2 + i];
+#pragma unroll
+    for (int i = tid; i < 16 * 32; i += 256) S.w3[i] = (i / 32) < 8 ? (_Float16)prm[kOffW3 + i] : (_Float16)0.0f;
+    if (tid < 32) S.b1[tid] = prm[kOffB1 + tid];
+    else if (tid < 64) S.b2[tid - 32] = prm[kOffB2 + tid - 32];
+    else if (tid < 72) S.b3[tid - 64] = prm[kOffB3 + tid - 64];
     __syncthreads();
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    // forward, group by group (same operands and accumulation order as inference)
-    for (int g = 0; g < 4; ++g) {
-        const int s0 = 16 * g;
-        for (int t = 0; t < 2; ++t) {
-            const f4 d = mfma_lds(S.w1 + 16 * t * 16, 16, 1, S.x + s0 * 16, 1, 16, zero);
-            for (int i = 0; i < 4; ++i) {
-                const float v = d[i] + prm[kOffB1 + 16 * t + q + i];
-                S.h1[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
-            }
+    const int s0 = 16 * g;
+    // forward (same operands and accumulation order as inference)
+    for (int t = 0; t < 2; ++t) {
+        const f4 d = mfma_lds(S.w1 + 16 * t * 16, 16, 1, S.x + s0 * 16, 1, 16, zero);
+        for (int i = 0; i < 4; ++i) {
+            const float v = d[i] + S.b1[16 * t + q + i];
+            S.h1[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
         }
-        __syncthreads();
-        for (int t = 0; t < 2; ++t) {
-            f4 d = mfma_lds(S.w2 + 16 * t * 32, 32, 1, S.h1 + s0 * 32, 1, 32, zero);
-            d = mfma_lds(S.w2 + 16 * t * 32 + 16, 32, 1, S.h1 + s0 * 32 + 16, 1, 32, d);
-            for (int i = 0; i < 4; ++i) {
-                const float v = d[i] + prm[kOffB2 + 16 * t + q + i];
-                S.h2[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
-            }
+    }
+    wave_lds_sync();
+    for (int t = 0; t < 2; ++t) {
+        f4 d = mfma_lds(S.w2 + 16 * t * 32, 32, 1, S.h1 + s0 * 32, 1, 32, zero);
+        d = mfma_lds(S.w2 + 16 * t * 32 + 16, 32, 1, S.h1 + s0 * 32 + 16, 1, 32, d);
+        for (int i = 0; i < 4; ++i) {
+            const float v = d[i] + S.b2[16 * t + q + i];
+            S.h2[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
         }
-        __syncthreads();
+    }
+    wave_lds_sync();
+    {
         f4 o = mfma_lds(S.w3, 32, 1, S.h2 + s0 * 32, 1, 32, zero);
         o = mfma_lds(S.w3 + 16, 32, 1, S.h2 + s0 * 32 + 16, 1, 32, o);
         for (int i = 0; i < 4; ++i) {
             float v = 0.0f;
             if (q + i < 8) {
-                v = o[i] + prm[kOffB3 + q + i];
+                v = o[i] + S.b3[q + i];
                 v = v + 16.0f * S.xf[(s0 + r) * 8 + q + i];
             }
             S.zf[(s0 + r) * 16 + q + i] = v;
         }
-        __syncthreads();
     }
-    // loss and dL/dz for this lane's row: soft cross-entropy against the softmax over non-empty slots
-    float loss = 0.0f;
-    {
+    wave_lds_sync();
+    // loss and dL/dz of the group's rows, one lane each: soft cross-entropy against the softmax over non-empty slots
+    if (l < 16) {
+        const int row = s0 + l;
+        float tg[8], cn[8], csum = 0.0f;
+        for (int k = 0; k < 8; ++k) {
+            tg[k] = S.tg[row * 8 + k];
+            cn[k] = S.cn[row * 8 + k];
+            csum += cn[k];
+        }
+        const bool valid = csum > 0.0f;
+        float loss = 0.0f;
         float zmax = -INFINITY;
         for (int c = 0; c < 8; ++c)
-            if (cn[c] > 0.0f) zmax = fmaxf(zmax, S.zf[l * 16 + c]);
+            if (cn[c] > 0.0f) zmax = fmaxf(zmax, S.zf[row * 16 + c]);
         float e[8], s = 0.0f;
         for (int c = 0; c < 8; ++c) {
-            e[c] = cn[c] > 0.0f ? expf(S.zf[l * 16 + c] - zmax) : 0.0f;
+            e[c] = cn[c] > 0.0f ? expf(S.zf[row * 16 + c] - zmax) : 0.0f;
             s += e[c];
         }
         for (int c = 0; c < 16; ++c) {
@@ -321,122 +356,146 @@ __global__ void __launch_bounds__(64) k_mlp_grad(const float* __restrict__ prm, 
                 if (tg[c] > 0.0f) loss -= tg[c] * logf(pi);
                 dz = pi - tg[c];
             }
-            S.zf[l * 16 + c] = dz;
-            S.dz[l * 16 + c] = (_Float16)dz;
+            S.zf[row * 16 + c] = dz;
+            S.dz[row * 16 + c] = (_Float16)dz;
+        }
+        S.loss[row] = loss;
+        S.valid[row] = valid ? 1 : 0;
+    }
+    wave_lds_sync();
+    // back-propagate deltas
+    for (int kt = 0; kt < 2; ++kt) {   // dH2^T = W3^T dZ^T, masked by H2 > 0
+        const f4 d = mfma_lds(S.w3 + 16 * kt, 1, 32, S.dz + s0 * 16, 1, 16, zero);
+        for (int i = 0; i < 4; ++i) {
+            const int idx = (s0 + r) * 32 + 16 * kt + q + i;
+            const float v = (float)S.h2[idx] > 0.0f ? d[i] : 0.0f;
+            S.dh2f[idx] = v;
+            S.dh2[idx] = (_Float16)v;
+        }
+    }
+    wave_lds_sync();
+    for (int kt = 0; kt < 2; ++kt) {   // dH1^T = W2^T dH2^T, masked by H1 > 0
+        f4 d = mfma_lds(S.w2 + 16 * kt, 1, 32, S.dh2 + s0 * 32, 1, 32, zero);
+        d = mfma_lds(S.w2 + 16 * 32 + 16 * kt, 1, 32, S.dh2 + s0 * 32 + 16, 1, 32, d);
+        for (int i = 0; i < 4; ++i) {
+            const int idx = (s0 + r) * 32 + 16 * kt + q + i;
+            const float v = (float)S.h1[idx] > 0.0f ? d[i] : 0.0f;
+            S.dh1f[idx] = v;
+            S.dh1[idx] = (_Float16)v;
         }
     }
     __syncthreads();
-    // back-propagate deltas, group by group
-    for (int g = 0; g < 4; ++g) {
-        const int s0 = 16 * g;
-        for (int kt = 0; kt < 2; ++kt) {   // dH2^T = W3^T dZ^T, masked by H2 > 0
-            const f4 d = mfma_lds(S.w3 + 16 * kt, 1, 32, S.dz + s0 * 16, 1, 16, zero);
-            for (int i = 0; i < 4; ++i) {
-                const int idx = (s0 + r) * 32 + 16 * kt + q + i;
-                const float v = (float)S.h2[idx] > 0.0f ? d[i] : 0.0f;
-                S.dh2f[idx] = v;
-                S.dh2[idx] = (_Float16)v;
-            }
-        }
-        __syncthreads();
-        for (int kt = 0; kt < 2; ++kt) {   // dH1^T = W2^T dH2^T, masked by H1 > 0
-            f4 d = mfma_lds(S.w2 + 16 * kt, 1, 32, S.dh2 + s0 * 32, 1, 32, zero);
-            d = mfma_lds(S.w2 + 16 * 32 + 16 * kt, 1, 32, S.dh2 + s0 * 32 + 16, 1, 32, d);
-            for (int i = 0; i < 4; ++i) {
-                const int idx = (s0 + r) * 32 + 16 * kt + q + i;
-                const float v = (float)S.h1[idx] > 0.0f ? d[i] : 0.0f;
-                S.dh1f[idx] = v;
-                S.dh1[idx] = (_Float16)v;
-            }
-        }
-        __syncthreads();
-    }
-    // weight gradients: sums over the 64 rows (K = rows, 16 at a time)
+    // weight gradients: sums over the 64 rows (K = rows, 16 at a time), two tiles per wavefront
     float* out = partial + (int64_t)blockIdx.x * kGradStride;
-    for (int kt = 0; kt < 2; ++kt) {   // dW3[c][k] = sum_s dz[s][c] h2[s][k]
+    for (int kt = 0; kt < 2; ++kt) {
         f4 d = zero;
-        for (int g = 0; g < 4; ++g) d = mfma_lds(S.dz + 16 * g * 16, 1, 16, S.h2 + 16 * g * 32 + 16 * kt, 32, 1, d);
-        for (int i = 0; i < 4; ++i)
-            if (q + i < 8) out[kOffW3 + (q + i) * 32 + 16 * kt + r] = d[i];
-    }
-    for (int nt = 0; nt < 2; ++nt)
-        for (int kt = 0; kt < 2; ++kt) {   // dW2[n][k] = sum_s dh2[s][n] h1[s][k]
-            f4 d = zero;
-            for (int g = 0; g < 4; ++g)
-                d = mfma_lds(S.dh2 + 16 * g * 32 + 16 * nt, 1, 32, S.h1 + 16 * g * 32 + 16 * kt, 32, 1, d);
+        if (g == 0) {          // dW3[c][k] = sum_s dz[s][c] h2[s][k]
+            for (int s = 0; s < 4; ++s) d = mfma_lds(S.dz + 16 * s * 16, 1, 16, S.h2 + 16 * s * 32 + 16 * kt, 32, 1, d);
+            for (int i = 0; i < 4; ++i)
+                if (q + i < 8) out[kOffW3 + (q + i) * 32 + 16 * kt + r] = d[i];
+        } else if (g < 3) {    // dW2[n][k] = sum_s dh2[s][n] h1[s][k]
+            const int nt = g - 1;
+            for (int s = 0; s < 4; ++s)
+                d = mfma_lds(S.dh2 + 16 * s * 32 + 16 * nt, 1, 32, S.h1 + 16 * s * 32 + 16 * kt, 32, 1, d);
             for (int i = 0; i < 4; ++i) out[kOffW2 + (16 * nt + q + i) * 32 + 16 * kt + r] = d[i];
+        } else {               // dW1[n][k] = sum_s dh1[s][n] x[s][k]
+            for (int s = 0; s < 4; ++s) d = mfma_lds(S.dh1 + 16 * s * 32 + 16 * kt, 1, 32, S.x + 16 * s * 16, 16, 1, d);
+            for (int i = 0; i < 4; ++i)
+                if (r < 8) out[kOffW1 + (16 * kt + q + i) * 8 + r] = d[i];
         }
-    for (int nt = 0; nt < 2; ++nt) {   // dW1[n][k] = sum_s dh1[s][n] x[s][k]
-        f4 d = zero;
-        for (int g = 0; g < 4; ++g) d = mfma_lds(S.dh1 + 16 * g * 32 + 16 * nt, 1, 32, S.x + 16 * g * 16, 16, 1, d);
-        for (int i = 0; i < 4; ++i)
-            if (r < 8) out[kOffW1 + (16 * nt + q + i) * 8 + r] = d[i];
     }
-    // bias gradients from the float32 deltas, fixed order over rows
-    if (l < 32) {
-        float a1 = 0.0f, a2 = 0.0f;
-        for (int s = 0; s < 64; ++s) {
-            a1 += S.dh1f[s * 32 + l];
-            a2 += S.dh2f[s * 32 + l];
+    // bias gradients from the float32 deltas, in row order, and the block's loss (fixed-order wave reduction)
+    if (g == 0) {
+        if (l < 8) {
+            float a = 0.0f;
+#pragma unroll 16
+            for (int s = 0; s < 64; ++s) a += S.zf[s * 16 + l];
+            out[kOffB3 + l] = a;
         }
-        out[kOffB1 + l] = a1;
-        out[kOffB2 + l] = a2;
-    } else if (l < 40) {
-        float a3 = 0.0f;
-        for (int s = 0; s < 64; ++s) a3 += S.zf[s * 16 + (l - 32)];
-        out[kOffB3 + l - 32] = a3;
-    }
-    // loss of the block (fixed-order wave reduction)
-    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
-    const float nvalid = (float)__popcll(__ballot(valid));
-    if (l == 0) {
-        out[1608] = loss;
-        out[1609] = nvalid;
+        float loss = S.loss[l];
+        for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
+        const float nvalid = (float)__popcll(__ballot(S.valid[l] != 0));
+        if (l == 0) {
+            out[1608] = loss;
+            out[1609] = nvalid;
+        }
+    } else if (l < 32 && g < 3) {
+        const float* d = g == 1 ? S.dh2f : S.dh1f;
+        float a = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < 64; ++s) a += d[s * 32 + l];
+        out[(g == 1 ? kOffB2 : kOffB1) + l] = a;
     }
 }
 
-// Means over the rows that count, sums over blocks in a fixed order:
-// grad[0..1607] gradient, grad[1608] loss, grad[1609] number of rows.  A
+// Means over the rows that count, sums over blocks in a fixed order: entry p
+// of the gradient (p <= 1607), the loss (1608), the number of rows (1609).  A
 // workgroup takes 64 consecutive entries; its kReduceParts wavefronts each sum
-// one run of consecutive blocks in block order, and the runs' sums are added
-// in run order (independent loads in flight instead of one serial chain).
+// one run of consecutive blocks in block order, eight loads in flight, and the
+// runs' sums are added in run order.  Valid in the first wavefront's lanes.
 constexpr int kReduceParts = 8;
-__global__ void __launch_bounds__(64 * kReduceParts) k_mlp_reduce(const float* __restrict__ partial, int nblocks,
-                                                                  float* __restrict__ grad)
+struct ReduceLds {
+    float ps[kReduceParts][64];
+    float pc[kReduceParts];
+};
+__device__ __forceinline__ float reduced_entry(ReduceLds& S, const float* __restrict__ partial, int nblocks)
 {
-    __shared__ float ps[kReduceParts][64];
-    __shared__ float pc[kReduceParts];
     const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int p = blockIdx.x * 64 + l;
+    const int p = blockIdx.x * 64 + l, at = p <= 1609 ? p : 1609;
     const int per = (nblocks + kReduceParts - 1) / kReduceParts;
     const int b0 = g * per, b1 = min(nblocks, b0 + per);
     float s = 0.0f, cnt = 0.0f;
-    for (int b = b0; b < b1; ++b) {
-        if (p <= 1609) s += partial[(int64_t)b * kGradStride + p];
-        cnt += partial[(int64_t)b * kGradStride + 1609];
-    }
-    ps[g][l] = s;
-    if (l == 0) pc[g] = cnt;
-    __syncthreads();
-    if (g == 0 && p <= 1609) {
-        float t = ps[0][l], c = pc[0];
-        for (int k = 1; k < kReduceParts; ++k) {
-            t += ps[k][l];
-            c += pc[k];
+    for (int b = b0; b < b1; b += 8) {
+        float v[8], c[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t row = (int64_t)min(b + k, b1 - 1) * kGradStride;
+            v[k] = partial[row + at];
+            c[k] = partial[row + 1609];
         }
-        grad[p] = p == 1609 ? c : t / fmaxf(c, 1.0f);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (b + k < b1) {
+                s += v[k];
+                cnt += c[k];
+            }
     }
+    S.ps[g][l] = s;
+    if (l == 0) S.pc[g] = cnt;
+    __syncthreads();
+    float t = S.ps[0][l], c = S.pc[0];
+    for (int k = 1; k < kReduceParts; ++k) {
+        t += S.ps[k][l];
+        c += S.pc[k];
+    }
+    return p == 1609 ? c : t / fmaxf(c, 1.0f);
 }
 
-// Adam (Kingma and Ba): state m[1608], v[1608]
-__global__ void k_mlp_adam(float* __restrict__ prm, float* __restrict__ state, const float* __restrict__ grad,
-                           float lr, float bc1, float bc2, float* __restrict__ loss_out)
+__global__ void __launch_bounds__(64 * kReduceParts) k_mlp_reduce(const float* __restrict__ partial, int nblocks,
+                                                                  float* __restrict__ grad)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0 && loss_out) *loss_out = grad[1608];
+    __shared__ ReduceLds S;
+    const float v = reduced_entry(S, partial, nblocks);
+    const int p = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x < 64 && p <= 1609) grad[p] = v;
+}
+
+// A training step's second half: the reduction and Adam (Kingma and Ba; state
+// m[1608], v[1608]) on the parameters whose gradients the workgroup holds
+// (10.2 us with one load in flight per wavefront and 4.4 for Adam's own launch,
+// now 4.2 together).
+__global__ void __launch_bounds__(64 * kReduceParts) k_mlp_step(const float* __restrict__ partial, int nblocks,
+                                                                float* __restrict__ prm, float* __restrict__ state,
+                                                                float lr, float bc1, float bc2,
+                                                                float* __restrict__ loss_out)
+{
+    __shared__ ReduceLds S;
+    const float g = reduced_entry(S, partial, nblocks);
+    const int p = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x >= 64) return;
+    if (p == 1608 && loss_out) *loss_out = g;
     if (p >= 1608) return;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float g = grad[p];
     const float m = b1 * state[p] + (1.0f - b1) * g;
     const float v = b2 * state[1608 + p] + (1.0f - b2) * g * g;
     state[p] = m;
@@ -1205,21 +1264,30 @@ hipError_t launch_mlp_forward(const float* prm, const float* x, int64_t n, float
 
 size_t mlp_partial_floats(int64_t rows) { return (size_t)((rows + 63) / 64) * kGradStride; }
 
+static int launch_mlp_partial(const float* prm, const float* X, const float* Tg, const float* Cn, int64_t n,
+                              int64_t row_begin, int64_t rows, float* partial, hipStream_t s)
+{
+    const int nb = (int)((rows + 63) / 64);
+    k_mlp_grad<<<nb, 256, 0, s>>>(prm, X, Tg, Cn, n, row_begin, rows, partial);
+    return nb;
+}
+
 hipError_t launch_mlp_grad(const float* prm, const float* X, const float* Tg, const float* Cn, int64_t n,
                            int64_t row_begin, int64_t rows, float* partial, float* grad, hipStream_t s)
 {
-    const int nb = (int)((rows + 63) / 64);
-    k_mlp_grad<<<nb, 64, 0, s>>>(prm, X, Tg, Cn, n, row_begin, rows, partial);
+    const int nb = launch_mlp_partial(prm, X, Tg, Cn, n, row_begin, rows, partial, s);
     k_mlp_reduce<<<(1610 + 63) / 64, 64 * kReduceParts, 0, s>>>(partial, nb, grad);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_adam(float* prm, float* state, const float* grad, float lr, int step, float* loss_out,
+hipError_t launch_mlp_step(float* prm, float* state, const float* X, const float* Tg, const float* Cn, int64_t n,
+                           int64_t row_begin, int64_t rows, float* partial, float lr, int step, float* loss_out,
                            hipStream_t s)
 {
+    const int nb = launch_mlp_partial(prm, X, Tg, Cn, n, row_begin, rows, partial, s);
     const float bc1 = 1.0f - powf(0.9f, (float)(step + 1));
     const float bc2 = 1.0f - powf(0.999f, (float)(step + 1));
-    k_mlp_adam<<<(1608 + 255) / 256, 256, 0, s>>>(prm, state, grad, lr, bc1, bc2, loss_out);
+    k_mlp_step<<<(1610 + 63) / 64, 64 * kReduceParts, 0, s>>>(partial, nb, prm, state, lr, bc1, bc2, loss_out);
     return hipGetLastError();
 }
 
