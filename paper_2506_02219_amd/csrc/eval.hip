@@ -22,10 +22,10 @@
 //   leaf          a leaf with several points uses its points as virtual
 //                 children (|B| / d) and ends the path after one step.
 //
-// k_bh: Barnes-Hut (Eq. (2), Algorithm 1) with wavefront voting: a
-// wavefront walks one depth-first traversal for its 64 queries; a child is
-// opened when any lane's far-field test fails; leaves that are opened are
-// summed exactly.  The traversal stack is wavefront-uniform and lives in LDS.
+// k_bh: Barnes-Hut (Eq. (2), Algorithm 1) voted over 64 consecutive queries:
+// a workgroup walks one cut for its 64 queries; a child is opened when any
+// lane's far-field test fails; leaves that are opened are summed exactly.  The
+// nodes to open are wavefront-uniform lists in LDS.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -307,6 +307,8 @@ __device__ __forceinline__ float h16(uint32_t bits) { return (float)__builtin_bi
 typedef uint32_t sbh_u32x4v __attribute__((ext_vector_type(4)));
 // 16 bytes (16-byte aligned): adjacent loads of a block merge into one wide scalar load
 __device__ __forceinline__ sbh_u32x4v gld4u(const uint32_t* p) { return *(const SBH_GLOBAL sbh_u32x4v*)p; }
+
+__device__ __forceinline__ sbh_u32x4v cld4u(const uint32_t* p) { return *(const SBH_CONSTANT sbh_u32x4v*)(uintptr_t)p; }
 
 template <int D, int K, bool TRACE, bool CMP = false>
 __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __restrict__ queries, int64_t nq,
@@ -2099,9 +2101,30 @@ constexpr int bh_stack_depth()
     return D == 2 ? (8 - 1) * 20 + 2 : (64 - 1) * 10 + 2;
 }
 
-template <int D, int K, bool O64>
-__global__ void __launch_bounds__(256) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
-                                            float* __restrict__ out)
+// One tile of 64 consecutive queries per workgroup, whose W wavefronts share
+// its opened nodes: level by level, the blocks to open are listed in LDS,
+// entry f goes to wavefront f mod W, and each wavefront lists the children it
+// finds near; a wavefront whose part of the next list is full walks the child
+// depth-first instead, on a stack of its own (always wavefront-uniform).  The
+// wavefronts' sums are added in order at the end, so a value depends on the
+// tree, the tile and beta alone.
+// Instruction issue bounds it, scalar as much as vector.  Before, a wavefront
+// walked a whole tile depth-first, one scalar round trip per child after
+// another; a tile near the sources opens several times as many nodes as the
+// others, and the launch waited for those with half its wavefront slots empty.
+// Counts and first points now come from one vector load and a scan, a block's
+// aggregates and four points of a leaf from one batch of scalar loads each, and
+// a child costs a bit test, its distance and one branch.  10^6 queries on 2^20
+// surface samples at beta = 2, d = 2: winding 956 -> 586 us (627 with two
+// wavefronts a tile), potential 813 -> 445, smooth distance 1249 -> 737; at
+// beta = 0.5 109 -> 77 (73), 94 -> 62 (58), 120 -> 109 (92).  d = 4 has fewer
+// and larger blocks, and two wavefronts a tile are faster there: winding
+// 3105 -> 1211 (1306 with four), at beta = 0.5 302 -> 132 (182).
+constexpr int kBhList = 64;   // entries of a wavefront's part of a list
+
+template <int D, int K, bool O64, int W>
+__global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
+                                               float* __restrict__ out)
 {
 #pragma clang fp contract(off)
     constexpr int D3 = D * D * D;
@@ -2110,11 +2133,13 @@ __global__ void __launch_bounds__(256) k_bh(TreeView tv, const float* __restrict
     constexpr int MAXS = bh_stack_depth<D>();
     // an entry is a child block to open: {block id, first point} and, apart, the level of its
     // node (block ids take all 32 bits; levels are below 64)
-    __shared__ int2 stack[256 / 64][MAXS];
-    __shared__ uint8_t stack_lvl[256 / 64][MAXS];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (((int64_t)blockIdx.x * blockDim.x + wv * 64) >= nq) return;
+    __shared__ int2 stack[W][MAXS];
+    __shared__ uint8_t stack_lvl[W][MAXS];
+    __shared__ int2 list[2][W][kBhList];   // the level's blocks and the next level's
+    __shared__ int n_list[2][W];
+    __shared__ float part[W][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
     const bool valid = j < nq;
     float qx = 0.f, qy = 0.f, qz = 0.f;
     if (valid) {
@@ -2123,81 +2148,174 @@ __global__ void __launch_bounds__(256) k_bh(TreeView tv, const float* __restrict
         qz = queries[3 * j + 2];
     }
     // a query with a non-finite coordinate has no value (NaN) and takes no part in the vote, so
-    // the cut its wavefront neighbours get is the one they would get without it
+    // the cut its wavefront neighbours get is the one they would get without it: it walks from the
+    // origin with a far-field limit below every distance
     const bool votes = valid && __builtin_isfinite(qx) && __builtin_isfinite(qy) && __builtin_isfinite(qz);
+    if (!votes) qx = qy = qz = 0.0f;
+    const float reach = votes ? a.beta : -1.0f;
+    auto limit2 = [&](float diam) -> float {   // |q - com| / |B| >= beta, squared
+        const float lim = reach * diam;
+        return votes ? lim * lim : -1.0f;
+    };
     KParams kp{a.eps2, a.alpha, 1.0f};
     float logwbar = 0.f, r0 = 0.f;
     if constexpr (K == SBH_SMOOTHDIST) {
         smooth_setup(tv, kp.wscale, logwbar);
-        r0 = smooth_shift<D>(tv, qx, qy, qz, a.alpha);
+        if (wv == 0) part[0][lane] = smooth_shift<D>(tv, qx, qy, qz, a.alpha);
     }
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     float acc = 0.0f;
-    int sp = 0;
+    if (threadIdx.x < W) n_list[0][threadIdx.x] = 0;
+    __syncthreads();
+    if constexpr (K == SBH_SMOOTHDIST) r0 = part[0][lane];
     // root: accepted when every lane passes the far-field test
     {
-        const float4 g = tv.nagg[0];
+        const float4 g = cld4(tv.nagg);
         const float dx = g.x - qx, dy = g.y - qy, dz = g.z - qz;
-        const float lim = a.beta * tv.diam0;   // |q - com| / |B| >= beta, squared
-        const bool near = votes && !(norm2(dx, dy, dz) >= lim * lim);
-        if (__ballot(near) == 0ull) {
-            acc = term<K>(g, (K == SBH_WINDING) ? tv.ndip[0] : zero4, qx, qy, qz, kp, r0);
+        if (__ballot(!(norm2(dx, dy, dz) >= limit2(tv.diam0))) == 0ull) {
+            if (wv == 0) acc = term<K>(g, (K == SBH_WINDING) ? cld4(tv.ndip) : zero4, qx, qy, qz, kp, r0);
         } else if (!tv.root_internal) {
-            for (int i = 0; i < tv.n_points; ++i)
-                acc = term_acc<K>(tv.pts[i], (K == SBH_WINDING) ? tv.pdip[i] : zero4, qx, qy, qz, kp, r0, acc);
-        } else {
-            if (lane == 0) {
-                stack[wv][0] = make_int2(0, 0);   // block 0, first point 0
-                stack_lvl[wv][0] = 0;             // the root's level
-            }
-            sp = 1;
+            if (wv == 0)
+                for (int i = 0; i < tv.n_points; ++i)
+                    acc = term_acc<K>(cld4(tv.pts + i), (K == SBH_WINDING) ? cld4(tv.pdip + i) : zero4, qx, qy, qz, kp, r0,
+                                      acc);
+        } else if (threadIdx.x == 0) {
+            list[0][0][0] = make_int2(0, 0);   // block 0, first point 0
+            n_list[0][0] = 1;
         }
     }
-    __builtin_amdgcn_wave_barrier();
-    while (sp > 0) {
-        --sp;
-        const int2 e = stack[wv][sp];
-        const int32_t blk = __builtin_amdgcn_readfirstlane(e.x);
-        const int level = __builtin_amdgcn_readfirstlane((int)stack_lvl[wv][sp]);
-        uint32_t pre = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
-        __builtin_amdgcn_wave_barrier();
-        const float diamC = ldexpf(tv.diam0, -(level + 1) * (D == 2 ? 1 : 2));
-        const float limC = a.beta * diamC;
-        const Off boff = (Off)(uint32_t)blk * (Off)(D3 * 16);
-        const float4* __restrict__ ba = at_off(tv.bagg, boff);
-        const float4* __restrict__ bd = at_off(tv.bdip, boff);
-        const uint32_t* __restrict__ bt = at_off(tv.btopo, (Off)(uint32_t)blk * (Off)(TS * 4));
-        const int32_t base = (int32_t)bt[D3];
-        int32_t nint = 0;
-        for (int c = 0; c < D3; ++c) {
-            const uint32_t cnt = bt[c];
-            if (cnt == 0u) continue;
-            const bool internal_c = (int)cnt > tv.leaf_size && level + 1 < tv.max_level;
-            const float4 g = ba[c];
-            const float dx = g.x - qx, dy = g.y - qy, dz = g.z - qz;
-            const float r2 = norm2(dx, dy, dz);
-            const bool near = votes && !(r2 >= limC * limC);
-            if (__ballot(near) == 0ull) {
-                acc = term_r2_acc<K>(g, (K == SBH_WINDING) ? bd[c] : zero4, dx, dy, dz, r2, kp, r0, acc);
-            } else if (internal_c) {
-                if (lane == 0) {
-                    stack[wv][sp] = make_int2(base + nint, (int32_t)pre);
-                    stack_lvl[wv][sp] = (uint8_t)(level + 1);
+    __syncthreads();
+    int cur = 0;
+    for (int depth = 0;; ++depth) {
+        int cum[W + 1];   // the level's entries by wavefront that listed them
+        cum[0] = 0;
+#pragma unroll
+        for (int v = 0; v < W; ++v) cum[v + 1] = cum[v] + __builtin_amdgcn_readfirstlane(n_list[cur][v]);
+        if (cum[W] == 0) break;
+        int pushed = 0;
+        for (int f = wv; f < cum[W]; f += W) {
+            int src = 0, at = f;
+#pragma unroll
+            for (int v = 1; v < W; ++v)
+                if (f >= cum[v]) {
+                    src = v;
+                    at = f - cum[v];
                 }
-                ++sp;
-            } else {
-                for (uint32_t i = pre; i < pre + cnt; ++i) {
-                    const Off po = (Off)i * (Off)16;
-                    acc = term_acc<K>(*at_off(tv.pts, po), (K == SBH_WINDING) ? *at_off(tv.pdip, po) : zero4, qx, qy,
-                                      qz, kp, r0, acc);
+            const int2 e0 = list[cur][src][at];
+            int32_t blk = __builtin_amdgcn_readfirstlane(e0.x);
+            uint32_t pre = (uint32_t)__builtin_amdgcn_readfirstlane(e0.y);
+            int level = depth;
+            int sp = 0;
+            for (;;) {
+                const float lim2 = limit2(ldexpf(tv.diam0, -(level + 1) * (D == 2 ? 1 : 2)));
+                const Off boff = (Off)(uint32_t)blk * (Off)(D3 * 16);
+                const float4* __restrict__ ba = at_off(tv.bagg, boff);
+                const float4* __restrict__ bd = at_off(tv.bdip, boff);
+                const uint32_t* __restrict__ bt = at_off(tv.btopo, (Off)(uint32_t)blk * (Off)(TS * 4));
+                // the counts, one slot a lane (d = 2: lanes 8..63 read the row's zero padding word), and
+                // their prefix sums; the scalar instructions set the time as much as the vector ones
+                const uint32_t cl = gld(bt + (D == 2 ? (lane < D3 ? lane : TS - 1) : lane));
+                const int32_t base = (int32_t)cld(bt + D3);
+                uint32_t inc = cl;
+                inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false);   // row_shr:1
+                inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false);   // row_shr:2
+                inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false);   // row_shr:4
+                if constexpr (D == 4) {
+                    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false);   // row_shr:8
+                    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);   // row_bcast:15
+                    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);   // row_bcast:31
                 }
+                const uint32_t first = pre + inc - cl;   // each slot's first point
+                using Mask = std::conditional_t<D == 2, uint32_t, uint64_t>;
+                const Mask some = (Mask)__ballot(cl != 0u);
+                const Mask inner = level + 1 < tv.max_level ? (Mask)__ballot((int)cl > tv.leaf_size) : (Mask)0;
+                Mask nearm = 0;   // children that some query sees as near
+#pragma unroll
+                for (int c0 = 0; c0 < D3; c0 += 8) {
+                    if (D == 4 && ((some >> c0) & 0xFF) == 0) continue;
+                    float4 g8[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) g8[i] = cld4(ba + c0 + i);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if (!((some >> (c0 + i)) & 1)) continue;
+                        const float4 g = g8[i];
+                        const float dx = g.x - qx, dy = g.y - qy, dz = g.z - qz;
+                        const float r2 = norm2(dx, dy, dz);
+                        if (__ballot(!(r2 >= lim2)) == 0ull)
+                            acc = term_r2_acc<K>(g, (K == SBH_WINDING) ? cld4(bd + c0 + i) : zero4, dx, dy, dz, r2, kp, r0,
+                                                 acc);
+                        else
+                            nearm |= (Mask)1 << (c0 + i);
+                    }
+                }
+                // near internal children: to the next level's list, or, when it is full, to the stack
+                Mask opened = nearm & inner;
+                const int n_open = D == 2 ? __popc((uint32_t)opened) : (int)__popcll((uint64_t)opened);
+                if (n_open > 0) {
+                    const bool mine = ((uint64_t)opened >> lane) & 1ull;
+                    const Mask below = (Mask)(((uint64_t)1 << lane) - 1ull);
+                    const int at = D == 2 ? __popc((uint32_t)(opened & below)) : (int)__popcll((uint64_t)(opened & below));
+                    const int32_t cb = base + (D == 2 ? __popc((uint32_t)(inner & below)) : (int)__popcll((uint64_t)(inner & below)));
+                    if (level == depth && pushed + n_open <= kBhList) {
+                        if (mine) list[cur ^ 1][wv][pushed + at] = make_int2(cb, (int32_t)first);
+                        pushed += n_open;
+                    } else {
+                        if (mine) {
+                            stack[wv][sp + at] = make_int2(cb, (int32_t)first);
+                            stack_lvl[wv][sp + at] = (uint8_t)(level + 1);
+                        }
+                        sp += n_open;
+                    }
+                }
+                // near leaves: their points, four loaded at a time (past the array's end the load reads what
+                // follows in the same allocation, unused)
+                for (Mask leaves = nearm & ~inner; leaves != 0; leaves &= leaves - 1) {
+                    const int c = D == 2 ? (int)__builtin_ctz((uint32_t)leaves) : (int)__builtin_ctzll((uint64_t)leaves);
+                    uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)cl, c);
+                    Off po = (Off)(uint32_t)__builtin_amdgcn_readlane((int)first, c) * (Off)16;
+                    for (;;) {
+                        float4 pt[4], pd[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            pt[u] = cld4(at_off(tv.pts, po) + u);
+                            if constexpr (K == SBH_WINDING) pd[u] = cld4(at_off(tv.pdip, po) + u);
+                        }
+#pragma unroll
+                        for (int u = 1; u < 4; ++u) {   // (keeps the four loads together)
+                            asm volatile("" : "+s"(pt[u].x), "+s"(pt[u].y), "+s"(pt[u].z), "+s"(pt[u].w));
+                            if constexpr (K == SBH_WINDING) asm volatile("" : "+s"(pd[u].x), "+s"(pd[u].y), "+s"(pd[u].z));
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            if (u > 0 && left <= (uint32_t)u) break;
+                            acc = term_acc<K>(pt[u], (K == SBH_WINDING) ? pd[u] : zero4, qx, qy, qz, kp, r0, acc);
+                        }
+                        if (left <= 4u) break;
+                        left -= 4u;
+                        po += 64;
+                    }
+                }
+                if (sp == 0) break;
+                __builtin_amdgcn_wave_barrier();
+                --sp;
+                const int2 e = stack[wv][sp];
+                blk = __builtin_amdgcn_readfirstlane(e.x);
+                level = __builtin_amdgcn_readfirstlane((int)stack_lvl[wv][sp]);
+                pre = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
+                __builtin_amdgcn_wave_barrier();
             }
-            nint += internal_c ? 1 : 0;
-            pre += cnt;
         }
-        __builtin_amdgcn_wave_barrier();
+        if (lane == 0) n_list[cur ^ 1][wv] = pushed;
+        __syncthreads();
+        cur ^= 1;
     }
-    if (valid) out[j] = query_value<K>(acc, r0, logwbar, a.alpha, qx, qy, qz);
+    part[wv][lane] = acc;
+    __syncthreads();
+    if (wv != 0) return;
+#pragma unroll
+    for (int v = 1; v < W; ++v) acc += part[v][lane];
+    if (valid) out[j] = votes ? query_value<K>(acc, r0, logwbar, a.alpha, qx, qy, qz) : __builtin_nanf("");
 }
 
 // Stratification by a Barnes-Hut cut (Section 3.3.1 names the contribution
@@ -2524,8 +2642,10 @@ static hipError_t launch_bh_dk(const TreeView& tv, const float* q, int64_t nq, c
                                hipStream_t s)
 {
     BhArgs a{e.beta, e.eps * e.eps, e.alpha};
-    if (tv.wide) k_bh<D, K, true><<<(unsigned)((nq + 255) / 256), 256, 0, s>>>(tv, q, nq, a, out);
-    else k_bh<D, K, false><<<(unsigned)((nq + 255) / 256), 256, 0, s>>>(tv, q, nq, a, out);
+    constexpr int W = D == 2 ? 4 : 2;   // wavefronts per tile
+    const unsigned tiles = (unsigned)((nq + 63) / 64);
+    if (tv.wide) k_bh<D, K, true, W><<<tiles, 64 * W, 0, s>>>(tv, q, nq, a, out);
+    else k_bh<D, K, false, W><<<tiles, 64 * W, 0, s>>>(tv, q, nq, a, out);
     return hipGetLastError();
 }
 

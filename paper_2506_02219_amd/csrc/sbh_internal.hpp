@@ -69,6 +69,17 @@ __device__ __forceinline__ float4 gld4(const float4* p)
 }
 __device__ __forceinline__ float gld(const float* p) { return *(const SBH_GLOBAL float*)p; }
 __device__ __forceinline__ uint32_t gld(const uint32_t* p) { return *(const SBH_GLOBAL uint32_t*)p; }
+// The same from the constant address space: a tree does not change while a
+// kernel reads it, so these stay scalar loads in kernels with workgroup
+// barriers too (after a barrier the compiler must take other memory as
+// written, and reads it with vector loads).
+#define SBH_CONSTANT __attribute__((address_space(4)))
+__device__ __forceinline__ float4 cld4(const float4* p)
+{
+    const sbh_f32x4 v = *(const SBH_CONSTANT sbh_f32x4*)(uintptr_t)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint32_t cld(const uint32_t* p) { return *(const SBH_CONSTANT uint32_t*)(uintptr_t)p; }
 __device__ __forceinline__ void gst(float* p, float v) { *(SBH_GLOBAL float*)p = v; }
 
 // Device memory of the library: one allocator pair (sbh_set_allocator), or
