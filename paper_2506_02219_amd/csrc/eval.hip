@@ -1119,6 +1119,21 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
 // roulette are those of wave_path.
 // ---------------------------------------------------------------------------
 
+// The smooth-distance shifts of a tile's queries into LDS, by one of the
+// wavefronts that share the tile (2^20 queries on 2^22 sources, S = 4: 546 ->
+// 522 us).
+template <int D>
+__device__ __forceinline__ void tile_shift(const TreeView& tv, const float* __restrict__ queries, int64_t nq,
+                                           int64_t tile, float alpha, float* shift)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t j = tile * 64 + lane;
+    if (tile * 64 >= nq) return;
+    const bool valid = j < nq;
+    shift[lane] = smooth_shift<D>(tv, valid ? gld(queries + 3 * j) : 0.0f, valid ? gld(queries + 3 * j + 1) : 0.0f,
+                                  valid ? gld(queries + 3 * j + 2) : 0.0f, alpha);
+}
+
 template <int K, bool TRACE, bool O64, int VM>
 __device__ __forceinline__ float wave_path_q(const TreeView& tv, float qx, float qy, float qz, float r0,
                                              const KParams& kp, bool valid, uint32_t n_a, uint32_t begin_a,
@@ -1299,7 +1314,7 @@ __device__ __forceinline__ float wave_path_q(const TreeView& tv, float qx, float
 template <int K, bool TRACE, int P, bool O64, int VM>
 __device__ __forceinline__ void sbh_wave_tile_q(const TreeView& tv, const float* __restrict__ queries, int64_t nq,
                                                 const SbhArgs& a, float* __restrict__ out, int64_t wave, int part,
-                                                int w, float (*part_f)[64], uint32_t* done)
+                                                int w, float (*part_f)[64], uint32_t* done, const float* shift)
 {
 #pragma clang fp contract(off)
     constexpr int D3 = 8;
@@ -1318,7 +1333,7 @@ __device__ __forceinline__ void sbh_wave_tile_q(const TreeView& tv, const float*
     float logwbar = 0.f, r0 = 0.f;
     if constexpr (K == SBH_SMOOTHDIST) {
         smooth_setup(tv, kp.wscale, logwbar);
-        r0 = smooth_shift<2>(tv, qx, qy, qz, a.alpha);
+        r0 = shift[lane];
     }
     const uint32_t stream = (uint32_t)(j0 / a.group);
     const uint32_t* __restrict__ rt = tv.btopo;
@@ -1392,13 +1407,14 @@ k_sbh_wave_q(TreeView tv, const float* __restrict__ queries, int64_t nq, SbhArgs
     constexpr int P = kWaveParts, TPB = 4 / P;
     __shared__ float part_f[4][64];
     __shared__ uint32_t done[TPB];
-    if constexpr (P > 1) {
-        if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
-        __syncthreads();
-    }
+    __shared__ float shift[K == SBH_SMOOTHDIST ? TPB : 1][64];
+    if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile = (int64_t)blockIdx.x * TPB + w / P;
-    sbh_wave_tile_q<K, TRACE, P, O64, VM>(tv, queries, nq, a, out, tile, w % P, w, part_f, done);
+    if (K == SBH_SMOOTHDIST && w % P == 0) tile_shift<2>(tv, queries, nq, tile, a.alpha, shift[w / P]);
+    __syncthreads();
+    sbh_wave_tile_q<K, TRACE, P, O64, VM>(tv, queries, nq, a, out, tile, w % P, w, part_f, done,
+                                          shift[K == SBH_SMOOTHDIST ? w / P : 0]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1926,8 +1942,8 @@ __device__ __forceinline__ float wave_path_tile(const TreeView& tv, float qx, fl
 // split.  (A run-time choice: one inlined walk serves both splits.)
 template <int D, int K, bool TRACE, bool TILE = false, int P = 1, bool O64 = false, int VM = 2, bool SPLIT = false>
 __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* __restrict__ queries, int64_t nq,
-                                              const SbhArgs& a, float* __restrict__ out, int64_t wave, int part = 0,
-                                              int w = 0, float (*part_f)[64] = nullptr, uint32_t* done = nullptr,
+                                              const SbhArgs& a, float* __restrict__ out, int64_t wave, int part,
+                                              int w, float (*part_f)[64], uint32_t* done, const float* shift,
                                               bool four = false)
 {
 #pragma clang fp contract(off)
@@ -1950,7 +1966,7 @@ __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* _
     float logwbar = 0.f, r0 = 0.f;
     if constexpr (K == SBH_SMOOTHDIST) {
         smooth_setup(tv, kp.wscale, logwbar);
-        r0 = smooth_shift<D>(tv, qx, qy, qz, a.alpha);
+        r0 = shift[lane];   // (tile_shift)
     }
     const uint32_t stream = (uint32_t)(j0 / a.group);   // a.group is a multiple of 64
     const float inv_valid = 1.0f / (float)__popcll(__ballot(valid));
@@ -2047,14 +2063,17 @@ k_sbh_wave(TreeView tv, const float* __restrict__ queries, int64_t nq, SbhArgs a
     static_assert(P == 2, "the tail split assumes two parts per tile");
     __shared__ float part_f[D == 2 ? 8 : 4][64];
     __shared__ uint32_t done[TPB];
+    __shared__ float shift[K == SBH_SMOOTHDIST ? TPB : 1][64];
     if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
-    __syncthreads();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nb2 = split_tile / TPB;
     const bool four = D == 2 && (int64_t)blockIdx.x >= nb2;
     const int64_t tile = four ? split_tile + ((int64_t)blockIdx.x - nb2) : (int64_t)blockIdx.x * TPB + w / P;
+    const int row = K == SBH_SMOOTHDIST && !four ? w / P : 0;
+    if (K == SBH_SMOOTHDIST && (four ? w : w % P) == 0) tile_shift<D>(tv, queries, nq, tile, a.alpha, shift[row]);
+    __syncthreads();
     sbh_wave_tile<D, K, TRACE, false, P, O64, VM, true>(tv, queries, nq, a, out, tile, four ? w : w % P, w, part_f,
-                                                        done, four);
+                                                        done, shift[row], four);
 }
 
 // Tiles of the launch's four-part tail (d = 2): kTailTiles, or SBH_TAIL_TILES
@@ -2078,13 +2097,14 @@ k_sbh_wave_tile(TreeView tv, const float* __restrict__ queries, int64_t nq, SbhA
     constexpr int P = kWaveParts, TPB = 4 / P;   // as k_sbh_wave
     __shared__ float part_f[4][64];
     __shared__ uint32_t done[TPB];
-    if constexpr (P > 1) {
-        if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
-        __syncthreads();
-    }
+    __shared__ float shift[K == SBH_SMOOTHDIST ? TPB : 1][64];
+    if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile = (int64_t)blockIdx.x * TPB + w / P;
-    sbh_wave_tile<2, K, TRACE, true, P, O64>(tv, queries, nq, a, out, tile, w % P, w, part_f, done);
+    if (K == SBH_SMOOTHDIST && w % P == 0) tile_shift<2>(tv, queries, nq, tile, a.alpha, shift[w / P]);
+    __syncthreads();
+    sbh_wave_tile<2, K, TRACE, true, P, O64>(tv, queries, nq, a, out, tile, w % P, w, part_f, done,
+                                             shift[K == SBH_SMOOTHDIST ? w / P : 0]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2503,15 +2523,16 @@ k_sbh_batch(const BatchItem* __restrict__ items, const int2* __restrict__ wg, co
     static_assert(kBatchMaxTileWaves * P <= 4, "the walk keeps one LDS row per wavefront, four per workgroup");
     __shared__ float part_f[kBatchMaxTileWaves * P][64];
     __shared__ uint32_t done[kBatchMaxTileWaves];
-    if constexpr (P > 1) {
-        if (threadIdx.x < kBatchMaxTileWaves) done[threadIdx.x] = 0u;
-        __syncthreads();
-    }
+    __shared__ float shift[K == SBH_SMOOTHDIST ? kBatchMaxTileWaves : 1][64];
+    if (threadIdx.x < kBatchMaxTileWaves) done[threadIdx.x] = 0u;
     const int2 g = wg[blockIdx.x];
     const BatchItem* __restrict__ it = items + __builtin_amdgcn_readfirstlane(g.x);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t wave = (int64_t)__builtin_amdgcn_readfirstlane(g.y) + w / P;   // the tile
     const int64_t nq = it->nq;
+    const int row = K == SBH_SMOOTHDIST ? w / P : 0;
+    if (K == SBH_SMOOTHDIST && w % P == 0) tile_shift<D>(it->tv, it->queries, nq, wave, base.alpha, shift[row]);
+    __syncthreads();
     if (wave * 64 >= nq) return;
     SbhArgs a = base;
     a.key0 = st->key0;
@@ -2521,10 +2542,10 @@ k_sbh_batch(const BatchItem* __restrict__ items, const int2* __restrict__ wg, co
     // (scalar loads), as kernel arguments are
     if (it->tv.wide)
         sbh_wave_tile<D, K, false, false, P, true, VM>(it->tv, it->queries, nq, a, it->out, wave, w % P, w, part_f,
-                                                       done);
+                                                       done, shift[row]);
     else
         sbh_wave_tile<D, K, false, false, P, false, VM>(it->tv, it->queries, nq, a, it->out, wave, w % P, w, part_f,
-                                                        done);
+                                                        done, shift[row]);
 }
 
 // Clouds whose root is a leaf are summed exactly, as sbh_eval does, in launches

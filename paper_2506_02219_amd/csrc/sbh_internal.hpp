@@ -187,6 +187,18 @@ __device__ __forceinline__ double rsqrt64(double x)
 // give bit-identical results).
 __device__ __forceinline__ float norm2(float dx, float dy, float dz) { return fmaf(dz, dz, fmaf(dx, dx, dy * dy)); }
 
+// r2^(-3/2), at most the largest finite value it can take (where it would
+// overflow, and at r2 = 0, where the dipole's dot product is 0 and so the term).
+__device__ __forceinline__ float inv_cube(float r2)
+{
+#pragma clang fp contract(off)
+    const float inv = fminf(__builtin_amdgcn_rsqf(r2), 6.98e12f);
+    return inv * inv * inv;
+}
+
+// The winding number's terms and sums leave out its constant 1 / (4 pi), which
+// query_value puts in: they are linear in it, and a term takes 13 vector
+// instructions so instead of 16.
 template <int K>
 __device__ __forceinline__ float term_r2(float4 a, float4 dp, float dx, float dy, float dz, float r2,
                                          const KParams& kp, float r0)
@@ -195,9 +207,7 @@ __device__ __forceinline__ float term_r2(float4 a, float4 dp, float dx, float dy
     if constexpr (K == SBH_POTENTIAL) {
         return a.w * __builtin_amdgcn_rsqf(r2 + kp.eps2);
     } else if constexpr (K == SBH_WINDING) {
-        const float inv = __builtin_amdgcn_rsqf(r2);
-        const float v = fmaf(dp.z, dz, fmaf(dp.x, dx, dp.y * dy)) * (inv * inv * inv) * kInv4Pi;
-        return r2 > 0.0f ? v : 0.0f;
+        return fmaf(dp.z, dz, fmaf(dp.x, dx, dp.y * dy)) * inv_cube(r2);
     } else {
         const float r = fsqrt(r2);
         return a.w * kp.wscale * __expf(-kp.alpha * (r - r0));
@@ -222,9 +232,7 @@ __device__ __forceinline__ float term_r2_acc(float4 a, float4 dp, float dx, floa
     if constexpr (K == SBH_POTENTIAL) {
         return fmaf(a.w, __builtin_amdgcn_rsqf(r2 + kp.eps2), acc);
     } else if constexpr (K == SBH_WINDING) {
-        const float inv = __builtin_amdgcn_rsqf(r2);
-        const float s = r2 > 0.0f ? (inv * inv * inv) * kInv4Pi : 0.0f;   // 0 at r = 0, where the dot is 0 too
-        return fmaf(fmaf(dp.z, dz, fmaf(dp.x, dx, dp.y * dy)), s, acc);
+        return fmaf(fmaf(dp.z, dz, fmaf(dp.x, dx, dp.y * dy)), inv_cube(r2), acc);
     } else {
         const float r = fsqrt(r2);
         return fmaf(a.w * kp.wscale, __expf(-kp.alpha * (r - r0)), acc);
@@ -350,12 +358,13 @@ __device__ __forceinline__ float nan_unless_finite(float v, float qx, float qy, 
 }
 
 // The value written for query q from the estimated (or summed) F: the smooth
-// distance r0 - (log F + log wbar) / alpha, or F itself.
+// distance r0 - (log F + log wbar) / alpha, the winding number F / (4 pi), or F
+// itself.
 template <int K>
 __device__ __forceinline__ float query_value(float F, float r0, float logwbar, float alpha, float qx, float qy,
                                              float qz)
 {
-    const float v = (K == SBH_SMOOTHDIST) ? r0 - (logf(F) + logwbar) / alpha : F;
+    const float v = (K == SBH_SMOOTHDIST) ? r0 - (logf(F) + logwbar) / alpha : (K == SBH_WINDING) ? F * kInv4Pi : F;
     return nan_unless_finite(v, qx, qy, qz);
 }
 
