@@ -1934,23 +1934,25 @@ __device__ __forceinline__ float wave_path_tile(const TreeView& tv, float qx, fl
 // (the launch's floor on its duration) at the price of one more Philox
 // evaluation per part.  LDS: part_f [wavefronts of the block][64] and one
 // counter per tile of the block in `done`, zeroed before the block's first
-// barrier.  four (P = 2, d = 2: the last tiles of a launch): the tile is
-// split over four wavefronts of two slots each, which store each slot's
-// total in part_f [slot][64]; the last of them adds the totals in the
-// association of two parts (slots 0-3 in order, slots 4-7 in order, then
-// the two sums), so a query's value does not depend on how its tile was
-// split.  (A run-time choice: one inlined walk serves both splits.)
-template <int D, int K, bool TRACE, bool TILE = false, int P = 1, bool O64 = false, int VM = 2, bool SPLIT = false>
+// barrier.  split (P = 2, d = 2, SPLIT 4 or 8: the last tiles of a launch, and
+// small launches): the tile is split over four wavefronts of two
+// slots or eight of one, which store each slot's total in part_f [slot][64];
+// the last of them adds the totals in the association of two parts (slots 0-3
+// in order, slots 4-7 in order, then the two sums), so a query's value does
+// not depend on how its tile was split.  (A run-time choice between none and
+// SPLIT: one inlined walk serves both.)
+template <int D, int K, bool TRACE, bool TILE = false, int P = 1, bool O64 = false, int VM = 2, int SPLIT = 0>
 __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* __restrict__ queries, int64_t nq,
                                               const SbhArgs& a, float* __restrict__ out, int64_t wave, int part,
                                               int w, float (*part_f)[64], uint32_t* done, const float* shift,
-                                              bool four = false)
+                                              bool split = false)
 {
 #pragma clang fp contract(off)
     constexpr int D3 = D * D * D;
     static_assert(D3 % P == 0, "parts must split the root slots evenly");
-    constexpr bool kFour = SPLIT && D == 2 && P == 2;   // the four-way split is compiled in
-    if constexpr (!kFour) four = false;
+    constexpr bool kSplit = SPLIT != 0 && D == 2 && P == 2;   // the split is compiled in
+    if constexpr (!kSplit) split = false;
+    if constexpr (kSplit && SPLIT == 8) split = true;
     const int lane = threadIdx.x & 63;
     const int64_t j0 = wave * 64;
     if (j0 >= nq) return;
@@ -1973,7 +1975,7 @@ __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* _
     (void)inv_valid;
     const uint32_t* __restrict__ rt = tv.btopo;
     const int32_t base_root = (int32_t)gld(rt + D3);
-    const int nslots = four ? 2 : D3 / P;
+    const int nslots = kSplit && split ? D3 / (SPLIT ? SPLIT : 1) : D3 / P;
     const int slot_lo = part * nslots, slot_hi = slot_lo + nslots;
     uint32_t begin_a = 0u;
     int32_t nint = 0;
@@ -2016,16 +2018,16 @@ __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* _
             }
         }
         const float vs = cv + fa / (float)a.samples;
-        if (kFour && four) part_f[slot][lane] = vs;
+        if (kSplit && split) part_f[slot][lane] = vs;
         else F += vs;
         begin_a += n_a;
         nint += ((int)n_a > tv.leaf_size && 1 < tv.max_level) ? 1 : 0;
     }
-    if (kFour && four) {
+    if (kSplit && split) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         uint32_t prev = 0u;
         if (lane == 0) prev = __hip_atomic_fetch_add(&done[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (__builtin_amdgcn_readfirstlane(prev) != 3u) return;   // another part finishes the tile
+        if (__builtin_amdgcn_readfirstlane(prev) != (uint32_t)(SPLIT - 1)) return;   // another part finishes the tile
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         float fa_lo = 0.0f, fa_hi = 0.0f;
 #pragma unroll
@@ -2052,10 +2054,11 @@ __device__ __forceinline__ void sbh_wave_tile(const TreeView& tv, const float* _
 
 // Tiles below split_tile: TPB tiles per block, each over kWaveParts wavefronts;
 // from split_tile on (d = 2, the end of the launch, where the last wavefronts
-// run on a partly idle chip): one tile per block over all four wavefronts,
-// which halves the chain of steps each of them walks.
-template <int D, int K, bool TRACE, bool O64, int VM>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+// run on a partly idle chip): one tile per block over all its wavefronts, four,
+// which halves the chain of steps each of them walks, or eight (a launch of
+// kEightTiles tiles or fewer, which leaves the chip partly idle as a whole).
+template <int D, int K, bool TRACE, bool O64, int VM, int SPLIT = 4>
+__global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(8)))
 k_sbh_wave(TreeView tv, const float* __restrict__ queries, int64_t nq, SbhArgs a, float* __restrict__ out,
            int64_t split_tile)
 {
@@ -2067,18 +2070,27 @@ k_sbh_wave(TreeView tv, const float* __restrict__ queries, int64_t nq, SbhArgs a
     if (threadIdx.x < TPB) done[threadIdx.x] = 0u;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nb2 = split_tile / TPB;
-    const bool four = D == 2 && (int64_t)blockIdx.x >= nb2;
-    const int64_t tile = four ? split_tile + ((int64_t)blockIdx.x - nb2) : (int64_t)blockIdx.x * TPB + w / P;
-    const int row = K == SBH_SMOOTHDIST && !four ? w / P : 0;
-    if (K == SBH_SMOOTHDIST && (four ? w : w % P) == 0) tile_shift<D>(tv, queries, nq, tile, a.alpha, shift[row]);
+    const bool split = D == 2 && (SPLIT == 8 || (int64_t)blockIdx.x >= nb2);
+    const int64_t tile = split ? split_tile + ((int64_t)blockIdx.x - nb2) : (int64_t)blockIdx.x * TPB + w / P;
+    const int part = split ? w : w % P;
+    const int row = K == SBH_SMOOTHDIST && !split ? w / P : 0;
+    if (K == SBH_SMOOTHDIST && part == 0) tile_shift<D>(tv, queries, nq, tile, a.alpha, shift[row]);
     __syncthreads();
-    sbh_wave_tile<D, K, TRACE, false, P, O64, VM, true>(tv, queries, nq, a, out, tile, four ? w : w % P, w, part_f,
-                                                        done, shift[row], four);
+    sbh_wave_tile<D, K, TRACE, false, P, O64, VM, SPLIT>(tv, queries, nq, a, out, tile, part, w, part_f, done, shift[row],
+                                                        split);
 }
 
 // Tiles of the launch's four-part tail (d = 2): kTailTiles, or SBH_TAIL_TILES
 // from the environment (a tuning override; values are the same for any split).
+// A launch of at most kEightTiles tiles, which all its wavefronts fit on the chip
+// at once, takes eight wavefronts per tile instead: the chain of one slot's
+// steps is what it waits for (4,096 queries on 2^22 samples, four -> eight:
+// potential 13.5 -> 9.7 us a call, which is the call's host time, winding 16.3 ->
+// 11.0, smooth distance 23.5 -> 18.6; 65,536 queries 16.5 -> 13.2, 19.5 -> 15.9,
+// 27.3 -> 24.3).  It is a kernel of its own: chosen at run time in the other one
+// it cost the 10^6-query walk 0.7%.
 constexpr int64_t kTailTiles = 1024;
+constexpr int64_t kEightTiles = 1024;
 static int64_t tail_tiles()
 {
     const char* e = std::getenv("SBH_TAIL_TILES");
@@ -2600,15 +2612,22 @@ static hipError_t launch_sbh_dk(const TreeView& tv, const float* q, int64_t nq, 
         constexpr int64_t TPB = 4 / kWaveParts;
         int64_t split = (tiles + TPB - 1) / TPB * TPB;
         unsigned blocks = wblocks;
+        bool eight = false;
         if constexpr (D == 2) {
             split = std::max<int64_t>(0, tiles - std::min(tail_tiles(), tiles)) / TPB * TPB;
             blocks = (unsigned)(split / TPB + (tiles - split));
+            eight = split == 0 && tiles <= kEightTiles && !e.paths;
         }
         // each roulette is a kernel of its own (Eq. (5), voted, and the run-time ablation modes),
         // so that the default walk carries no test of rr_mode
 #define SBH_WAVE(VV)                                                                                        \
     do {                                                                                                    \
-        if (tv.wide) {                                                                                      \
+        if (eight) {                                                                                        \
+            if constexpr (D == 2) {                                                                         \
+                if (tv.wide) k_sbh_wave<2, K, false, true, VV, 8><<<blocks, 512, 0, s>>>(tv, q, nq, a, out, 0);  \
+                else k_sbh_wave<2, K, false, false, VV, 8><<<blocks, 512, 0, s>>>(tv, q, nq, a, out, 0);         \
+            }                                                                                               \
+        } else if (tv.wide) {                                                                                      \
             if (e.paths) k_sbh_wave<D, K, true, true, VV><<<blocks, 256, 0, s>>>(tv, q, nq, a, out, split);  \
             else k_sbh_wave<D, K, false, true, VV><<<blocks, 256, 0, s>>>(tv, q, nq, a, out, split);         \
         } else {                                                                                            \
