@@ -310,7 +310,8 @@ __device__ __forceinline__ sbh_u32x4v gld4u(const uint32_t* p) { return *(const 
 
 __device__ __forceinline__ sbh_u32x4v cld4u(const uint32_t* p) { return *(const SBH_CONSTANT sbh_u32x4v*)(uintptr_t)p; }
 
-template <int D, int K, bool TRACE, bool CMP = false>
+// SOFT: the potential with eps > 0.
+template <int D, int K, bool TRACE, bool CMP = false, bool SOFT = false>
 __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __restrict__ queries, int64_t nq,
                                                   SbhArgs a, float* __restrict__ out)
 {
@@ -491,23 +492,49 @@ __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __re
                     }
                     // child selection from the point counts alone
                     uint32_t pre = 0u, preC = 0u;
-                    int32_t nint = 0, nintC = 0;
+                    int32_t nintC = 0;
                     int csel = 0;
                     uint32_t w0 = 0u, w1 = 0u;
-#pragma unroll
-                    for (int c = 0; c < D3; ++c) {
-                        const uint32_t cnt = count(c);
-                        const bool hit = (r - pre) < cnt;
-                        csel = hit ? c : csel;
-                        preC = hit ? pre : preC;
-                        nintC = hit ? nint : nintC;
-                        nC = hit ? cnt : nC;
+                    if constexpr (D == 2) {
+                        const uint32_t leaf_max = level + 1 < tv.max_level ? (uint32_t)tv.leaf_size : 0x7FFFFFFFu;
+                        // the last slot whose first point is at most r; a slot and the internal slots before
+                        // it travel in one register (16 c + nint)
+                        uint32_t meta = 16u + (cn[0] > leaf_max ? 1u : 0u), metaC = 0u;
+                        pre = nC = cn[0];
                         if constexpr (CMP) {
-                            w0 = hit ? ((c & 1) ? cb[c >> 1].z : cb[c >> 1].x) : w0;
-                            w1 = hit ? ((c & 1) ? cb[c >> 1].w : cb[c >> 1].y) : w1;
+                            w0 = cb[0].x;
+                            w1 = cb[0].y;
                         }
-                        nint += ((int)cnt > tv.leaf_size && level + 1 < tv.max_level) ? 1 : 0;
-                        pre += cnt;
+#pragma unroll
+                        for (int c = 1; c < D3; ++c) {
+                            const bool at = r >= pre;
+                            preC = at ? pre : preC;
+                            metaC = at ? meta : metaC;
+                            nC = at ? cn[KEEPN ? c : 0] : nC;
+                            if constexpr (CMP) {
+                                w0 = at ? ((c & 1) ? cb[c >> 1].z : cb[c >> 1].x) : w0;
+                                w1 = at ? ((c & 1) ? cb[c >> 1].w : cb[c >> 1].y) : w1;
+                            }
+                            if (c + 1 < D3) {
+                                meta += 16u + (cn[KEEPN ? c : 0] > leaf_max ? 1u : 0u);
+                                pre += cn[KEEPN ? c : 0];
+                            }
+                        }
+                        csel = (int)(metaC >> 4);
+                        nintC = (int32_t)(metaC & 15u);
+                    } else {
+                        int32_t nint = 0;
+#pragma unroll
+                        for (int c = 0; c < D3; ++c) {
+                            const uint32_t cnt = count(c);
+                            const bool hit = (r - pre) < cnt;
+                            csel = hit ? c : csel;
+                            preC = hit ? pre : preC;
+                            nintC = hit ? nint : nintC;
+                            nC = hit ? cnt : nC;
+                            nint += ((int)cnt > tv.leaf_size && level + 1 < tv.max_level) ? 1 : 0;
+                            pre += cnt;
+                        }
                     }
                     if constexpr (CMP) {
                         // the selected child decoded: offset o s_c + (com^q_T - q), mass m^q_T f
@@ -564,10 +591,11 @@ __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __re
                     } else if (internal) {
 #pragma unroll
                         for (int c = 0; c < D3; ++c) {
-                            const uint32_t cnt = count(c);
                             const float4 gd = (K == SBH_WINDING) ? gld4(bd + c) : zero4;
                             const float v = term_acc<K>(gld4(ba + c), gd, qx, qy, qz, kp, r0, sumc);
-                            sumc = cnt ? v : sumc;
+                            // (an empty slot is all zeros: with eps > 0 its potential adds exactly nothing)
+                            if constexpr (SOFT) sumc = v;
+                            else sumc = count(c) ? v : sumc;
                         }
                     } else {
                         for (uint32_t i = 0; i < nT; ++i) {
@@ -2649,6 +2677,8 @@ static hipError_t launch_sbh_dk(const TreeView& tv, const float* q, int64_t nq, 
         const int64_t waves = (nq + qpw - 1) / qpw;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
         if (e.paths) k_sbh_pool<D, K, true><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
+        else if (K == SBH_POTENTIAL && a.eps2 > 0.0f)
+            k_sbh_pool<D, K, false, false, K == SBH_POTENTIAL><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
         else k_sbh_pool<D, K, false><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
         return hipGetLastError();
     } else {
