@@ -824,8 +824,8 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     // d = 4: each wavefront's row for the child block of the step; every kernel that walks
     // paths runs at most four wavefronts per workgroup (256 threads), one row each
-    __shared__ float4 sblk[D == 4 ? 4 : 1][64];
-    __shared__ float4 sblkd[D == 4 && K == SBH_WINDING ? 4 : 1][64];
+    // (aggregates, then dipoles: one LDS address serves both)
+    __shared__ float4 sblk[D == 4 ? 4 : 1][K == SBH_WINDING ? 2 : 1][64];
     // wavefront-uniform walk state
     uint32_t nT = n_a, beginT = begin_a;
     int32_t blk = blk_a;
@@ -1032,8 +1032,8 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
                 // turn, each read back by every lane as one broadcast LDS load
                 const int ln = threadIdx.x & 63;
                 const int wv = (threadIdx.x >> 6) & 3;
-                sblk[wv][ln] = gld4(ba + ln);
-                if constexpr (K == SBH_WINDING) sblkd[wv][ln] = gld4(bd + ln);
+                sblk[wv][0][ln] = gld4(ba + ln);
+                if constexpr (K == SBH_WINDING) sblk[wv][1][ln] = gld4(bd + ln);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1041,9 +1041,10 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
                 while (rest) {
                     const int c = (int)__builtin_ctzll(rest);
                     rest &= rest - 1ull;
-                    const float4 g = sblk[wv][c];
+                    const float4* row = &sblk[wv][0][c];
+                    const float4 g = row[0];
                     float4 gd = zero4;
-                    if constexpr (K == SBH_WINDING) gd = make_float4(sblkd[wv][c].x, sblkd[wv][c].y, sblkd[wv][c].z, 0.0f);
+                    if constexpr (K == SBH_WINDING) gd = make_float4(row[64].x, row[64].y, row[64].z, 0.0f);
                     sumc = term_acc<K>(g, gd, qx, qy, qz, kp, r0, sumc);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the row is reused next step
