@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(kBboxThreads) k_bbox_partial(const float* __re
     }
 }
 
-// params: lo[3], side, inv_side, bad.  One workgroup: each thread folds a
+// params: lo[3], side, inv_side, bad, and a cleared word.  One workgroup: each thread folds a
 // stride of the partials, then the wavefronts and the workgroup combine
 // (min and max are exact, so the order does not change the result).
 __global__ void __launch_bounds__(kBboxThreads) k_bbox_final(const float* __restrict__ partial, int nb,
@@ -143,6 +143,7 @@ __global__ void __launch_bounds__(kBboxThreads) k_bbox_final(const float* __rest
     params[3] = side;
     params[4] = __fdiv_rn(1.0f, side);
     params[5] = bad;
+    params[6] = 0.0f;   // set by k_rs_finish
 }
 
 static hipError_t launch_bbox(const float* src, const float* w, const float* nrm, int64_t n, float* params_dev,
@@ -225,8 +226,12 @@ __global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* 
 }
 
 // ---------------------------------------------------------------------------
-// 3. Stable LSD radix sort of (uint64 code, uint32 index), six passes of
-// 10-bit digits over the 60 bits.  A workgroup owns a tile of 8192
+// 3. Stable LSD radix sort of (uint64 code, uint32 index) in 10-bit digits.
+// The passes run over the codes' top bits alone (four of the six digits, three
+// in k_sort_small): few codes share these, and a pass over the result puts
+// such short runs in order.  Where a longer run is out of order, as in a cloud
+// of clusters far smaller than its cube, the six passes over all bits follow;
+// they start from codes whose equals are in input order already.  A workgroup owns a tile of 8192
 // consecutive keys, its wavefront v the v-th sixteenth, which it walks in
 // eight chunks of 64 in order: a key's rank among the tile's equal digits is
 // (wavefronts before) + (chunks of this wavefront before) + (lanes of the
@@ -234,9 +239,10 @@ __global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* 
 // kernels: the tiles' histograms; their prefix sums over a chunk of tiles,
 // with the chunk's totals; and the scatter, which adds up the chunks before
 // its own, sorts the tile in LDS and writes each digit's keys as one run.
-// Memory traffic and the scatter's latency bound it.  Six passes against the
-// former eight of 8-bit digits, whose scatter wrote every key on its own:
-// 657 -> 345 us for 2^22 keys (the scatter 45 us a pass, 2.2 TB/s).
+// Memory traffic and the scatter's latency bound it: 57 us a pass for 2^22
+// keys (the scatter 45, 2.2 TB/s).  Eight passes of 8-bit digits whose scatter
+// wrote every key on its own took 657 us, six passes 345, four and the runs 240;
+// k_sort_small with 5,003 points 61 us over all bits, 37 now.
 // ---------------------------------------------------------------------------
 constexpr int kRsBits = 10;
 constexpr int kRsBins = 1 << kRsBits;
@@ -245,8 +251,14 @@ constexpr int kRsThreads = 1024;
 constexpr int kRsWaves = kRsThreads / 64;
 constexpr int kRsItems = 8;
 constexpr int kRsTile = kRsThreads * kRsItems;
+constexpr int kRsTopPasses = 4;        // 40 bits: 13 levels of the octree
+constexpr int kRsTopPassesSmall = 3;   // of at most kRsTile codes
+constexpr int kRsRun = 16;             // longest run of equal top bits that is put in order by one thread
+// Points of a surface fill some 4^13 cells of the top bits, so that runs stay
+// short up to this many; beyond, all passes run at once.
+constexpr int64_t kRsTopMax = (int64_t)1 << 26;
 constexpr int kRsMaxChunks = 64;   // chunks of tiles (every scatter workgroup reads a row of each)
-static_assert(kRsPasses * kRsBits >= 60 && kRsPasses % 2 == 0 && kRsBins == kRsThreads, "radix sort layout");
+static_assert(kRsPasses * kRsBits >= 60 && kRsPasses % 2 == 0 && kRsTopPasses % 2 == 0 && kRsBins == kRsThreads, "radix sort layout");
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane)
 {
@@ -426,6 +438,48 @@ __global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __res
     }
 }
 
+// Codes sorted by their bits from `shift` up, equals in input order: puts the run of equal such bits
+// that starts at i in full order if it has at most kRsRun codes, and returns true where a longer
+// run descends at i.  Other threads reorder their own runs meanwhile, which changes no code's top
+// bits, and nothing but these decides where a run ends.
+template <class V>
+__device__ __forceinline__ bool rs_finish_run(uint64_t* keys, V* vals, int64_t n, int64_t i, int shift)
+{
+    const uint64_t k = keys[i], p = i > 0 ? keys[i - 1] : ~0ull, top = k >> shift;   // (a code has 60 bits)
+    if ((p >> shift) != top) {
+        int len = 1;
+        while (len <= kRsRun && i + len < n && (keys[i + len] >> shift) == top) ++len;
+        if (len > kRsRun) return false;
+        for (int a = 1; a < len; ++a) {
+            const uint64_t x = keys[i + a];
+            int b = a;
+            while (b > 0 && keys[i + b - 1] > x) --b;
+            if (b == a) continue;
+            const V v = vals[i + a];
+            for (int c = a; c > b; --c) {
+                keys[i + c] = keys[i + c - 1];
+                vals[i + c] = vals[i + c - 1];
+            }
+            keys[i + b] = x;
+            vals[i + b] = v;
+        }
+        return false;
+    }
+    if (k >= p) return false;
+    int len = 1;
+    for (int64_t j = i; len <= kRsRun && j > 0 && (keys[j - 1] >> shift) == top; --j) ++len;
+    for (int64_t j = i + 1; len <= kRsRun && j < n && (keys[j] >> shift) == top; ++j) ++len;
+    return len > kRsRun;
+}
+
+// again: set to 1 where the passes over all bits have to follow
+__global__ void k_rs_finish(uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, int64_t n, int shift,
+                            float* __restrict__ again)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && rs_finish_run(keys, vals, n, i, shift)) *again = 1.0f;
+}
+
 // At most one tile: codes, the whole sort in LDS and the gather in one
 // workgroup, where the passes' launches would cost more than their work.
 __global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restrict__ src, const float* __restrict__ w,
@@ -437,6 +491,7 @@ __global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restri
     __shared__ RsLds S;
     __shared__ uint64_t kbuf[kRsTile];
     __shared__ uint16_t vbuf[kRsTile];
+    __shared__ int again;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     uint64_t kk[kRsItems];
     uint32_t vv[kRsItems], rank[kRsItems];
@@ -446,7 +501,8 @@ __global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restri
         kk[c] = p < n ? morton_code(load3(src, p), params) : 0ull;
         vv[c] = (uint32_t)p;
     }
-    for (int pass = 0; pass < kRsPasses; ++pass) {
+    bool all = false;
+    for (int pass = kRsPasses - kRsTopPassesSmall; pass < kRsPasses; ++pass) {
         const int shift = pass * kRsBits;
         rs_rank(S, kk, rank, n, shift);
 #pragma unroll
@@ -459,7 +515,17 @@ __global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restri
                 vbuf[l] = (uint16_t)vv[c];
             }
         }
+        if (threadIdx.x == 0) again = 0;
         __syncthreads();
+        if (pass == kRsPasses - 1 && !all) {
+            for (int p = threadIdx.x; p < n; p += kRsThreads)
+                if (rs_finish_run(kbuf, vbuf, n, p, (kRsPasses - kRsTopPassesSmall) * kRsBits)) again = 1;
+            __syncthreads();
+            if (again) {
+                all = true;
+                pass = -1;
+            }
+        }
 #pragma unroll
         for (int c = 0; c < kRsItems; ++c) {
             const int p = wv * (64 * kRsItems) + c * 64 + lane;
@@ -485,19 +551,20 @@ __global__ void __launch_bounds__(kRsThreads) k_sort_small(const float* __restri
 static int rs_tiles(int64_t n) { return (int)((n + kRsTile - 1) / kRsTile); }
 static int rs_per_chunk(int tiles) { return std::max(32, (tiles + kRsMaxChunks - 1) / kRsMaxChunks); }
 
-// codes (in keys) and indices 0 .. n - 1 sorted into keys and vals
+// The codes in keys sorted in place by their digits from `first` on, with their values in vals
+// (an even number of passes); fresh: their values are their indices 0 .. n - 1.
 static hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_tmp, uint32_t* vals_tmp, int64_t n,
-                                   uint32_t* hist, uint32_t* ctot, hipStream_t s)
+                                   int first, bool fresh, uint32_t* hist, uint32_t* ctot, hipStream_t s)
 {
     const int tiles = rs_tiles(n), per = rs_per_chunk(tiles), chunks = (tiles + per - 1) / per;
     const unsigned grid = (unsigned)((tiles + 7) / 8 * 8);
-    for (int pass = 0; pass < kRsPasses; ++pass) {
-        const int shift = pass * kRsBits;
+    for (int pass = 0; pass < kRsPasses - first; ++pass) {
+        const int shift = (first + pass) * kRsBits;
         const bool even = pass % 2 == 0;
         const uint64_t* ks = even ? keys : keys_tmp;
         k_rs_hist<<<grid, kRsThreads, 0, s>>>(ks, n, shift, hist, tiles);
         k_rs_prefix<<<dim3(kRsBins / 256, (unsigned)chunks), 256, 0, s>>>(hist, tiles, per, ctot);
-        k_rs_scatter<<<grid, kRsThreads, 0, s>>>(ks, pass == 0 ? nullptr : even ? vals : vals_tmp, n, shift, hist, tiles,
+        k_rs_scatter<<<grid, kRsThreads, 0, s>>>(ks, fresh && pass == 0 ? nullptr : even ? vals : vals_tmp, n, shift, hist, tiles,
                                                  per, chunks, ctot, even ? keys_tmp : keys, even ? vals_tmp : vals);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1140,9 +1207,21 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
     uint16_t* marks = tmp.alloc<uint16_t>(n);
     uint32_t* counts = tmp.alloc<uint32_t>(nblocks * channels);
     SBH_ALLOC_OK("allocating topology buffers");
+    BuildInfo h;
+    // marks and counts of the sorted codes, then the sizes
+    auto read_sizes = [&]() -> sbh_status {
+        k_topo_mark<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(t->codes, n, bits, leaf_size, max_level, marks, counts);
+        SBH_TRY(hipGetLastError(), "topology mark kernel");
+        k_topo_scan<<<channels, 1024, 0, s>>>(counts, (int)nblocks, info->totals);
+        SBH_TRY(hipGetLastError(), "topology scan kernel");
+        SBH_TRY(hipMemcpyAsync(&h, info, sizeof(h), hipMemcpyDeviceToHost, s), "sizes copy");
+        SBH_TRY(hipStreamSynchronize(s), "sizes sync");
+        return SBH_OK;
+    };
     if (n <= kRsTile) {
         k_sort_small<<<1, kRsThreads, 0, s>>>(src, w, nrm, (int)n, params, t->codes, t->perm, t->pts, t->pdip);
         SBH_TRY(hipGetLastError(), "sort kernel");
+        if (const sbh_status st = read_sizes(); st != SBH_OK) return st;
     } else {
         const int64_t tiles = rs_tiles(n);
         uint64_t* keys2 = tmp.alloc<uint64_t>(n);
@@ -1153,20 +1232,23 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
         SBH_ALLOC_OK("allocating sort buffers");
         k_morton<<<nblk(n), 256, 0, s>>>(src, w, nrm, n, params, t->codes, rec);
         SBH_TRY(hipGetLastError(), "morton kernel");
-        SBH_TRY(radix_sort_pairs(t->codes, t->perm, keys2, vals2, n, hist, ctot, s), "radix sort");
-        k_gather_points<<<nblk(n), 256, 0, s>>>(rec, t->perm, n, t->pts, t->pdip);
-        SBH_TRY(hipGetLastError(), "gather kernel");
+        bool top = n <= kRsTopMax;   // the top bits first; the host learns with the sizes if that was not enough
+        for (bool fresh = true;; fresh = top = false) {
+            const int first = top ? kRsPasses - kRsTopPasses : 0;
+            SBH_TRY(radix_sort_pairs(t->codes, t->perm, keys2, vals2, n, first, fresh, hist, ctot, s), "radix sort");
+            if (top) {
+                k_rs_finish<<<nblk(n), 256, 0, s>>>(t->codes, t->perm, n, first * kRsBits, params + 6);
+                SBH_TRY(hipGetLastError(), "sort finish kernel");
+            }
+            k_gather_points<<<nblk(n), 256, 0, s>>>(rec, t->perm, n, t->pts, t->pdip);
+            SBH_TRY(hipGetLastError(), "gather kernel");
+            if (const sbh_status st = read_sizes(); st != SBH_OK) return st;
+            if (!top || h.params[6] == 0.0f || h.params[5] != 0.0f) break;
+        }
     }
     const uint64_t* codes = t->codes;
 
-    // 4. topology: the marks and counts, then the sizes
-    k_topo_mark<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(codes, n, bits, leaf_size, max_level, marks, counts);
-    SBH_TRY(hipGetLastError(), "topology mark kernel");
-    k_topo_scan<<<channels, 1024, 0, s>>>(counts, (int)nblocks, info->totals);
-    SBH_TRY(hipGetLastError(), "topology scan kernel");
-    BuildInfo h;
-    SBH_TRY(hipMemcpyAsync(&h, info, sizeof(h), hipMemcpyDeviceToHost, s), "sizes copy");
-    SBH_TRY(hipStreamSynchronize(s), "sizes sync");
+    // 4. topology
     if (h.params[5] != 0.0f) {
         *msg = "sbh_build: non-finite coordinate or normal, or weight not finite and > 0";
         return SBH_EINVAL;

@@ -49,3 +49,19 @@ def test_large_sort_is_stable(n):
     step = np.diff(code)
     assert (step >= 0).all()
     assert (np.diff(perm)[step == 0] > 0).all()
+
+
+@pytest.mark.parametrize("n", [8160, 20400])
+@pytest.mark.parametrize("copies", [2, 16, 17])
+@pytest.mark.parametrize("scale", [-17, -21])
+def test_runs_of_equal_top_bits(n, copies, scale):
+    """Groups of points that differ in the low bits of their codes alone: runs that one thread puts in
+    order, the longest such run, and runs that take the passes over all bits."""
+    from gpu_helpers import build_both, compare_trees
+    rng = np.random.Generator(np.random.PCG64(n + copies))
+    cells = (rng.permutation(64 ** 3)[:n // copies, None] // np.array([1, 64, 4096]) % 64 + 0.5) / 64.0
+    src = (np.repeat(cells, copies, 0) + rng.integers(0, 16, (n // copies * copies, 3)) * 2.0 ** scale)
+    src = src[rng.permutation(len(src))].astype(np.float32)
+    w = np.ones(len(src), np.float32)
+    gt, ot = build_both(src, w, None, d=2, leaf_size=8)
+    compare_trees(gt, ot)
