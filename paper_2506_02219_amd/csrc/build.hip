@@ -576,11 +576,12 @@ static hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* key
 // 4. Topology
 // ---------------------------------------------------------------------------
 // Level of the deepest node that holds both codes: their common leading digits
-// (60 / bits for equal codes).
-__device__ __forceinline__ int common_level(uint64_t a, uint64_t b, int bits)
+// (60 / bits for equal codes).  recip: ceil(2^16 / bits), by which the division
+// of at most 60 is a product.
+__device__ __forceinline__ int common_level(uint64_t a, uint64_t b, uint32_t recip)
 {
     const uint64_t x = a ^ b;
-    return x == 0ull ? 60 / bits : (__clzll((long long)x) - 4) / bits;
+    return (int)(((x == 0ull ? 60u : (uint32_t)__clzll((long long)x) - 4u) * recip) >> 16);
 }
 
 // Marks of point i: the nodes that start at it are those of levels s .. e, the
@@ -593,7 +594,7 @@ __device__ __forceinline__ int common_level(uint64_t a, uint64_t b, int bits)
 //      around i share its prefix.
 constexpr int kTopoLevels = 22;    // levels of a tree: at most 60 / 3 + 1 = 21
 constexpr int kTopoThreads = 256;
-constexpr int kTopoChunks = 4;     // groups of 64 consecutive points per wavefront
+constexpr int kTopoChunks = 2;     // groups of 64 consecutive points per wavefront
 constexpr int kTopoPoints = kTopoThreads * kTopoChunks;
 struct Mark {
     int s, e, w;
@@ -627,8 +628,9 @@ __device__ __forceinline__ void count_levels(Mark m, int lane, uint32_t& cn, uin
 // nodes (channel 2 l) and internal nodes (2 l + 1) of each level that start in
 // it: counts[channel * gridDim.x + block].  One ballot per level and wavefront
 // chunk, lane l keeping level l's counts.
-__global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __restrict__ codes, int64_t n, int bits,
-                                                            int leaf, int max_level, uint16_t* __restrict__ marks,
+__global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __restrict__ codes, int64_t n,
+                                                            uint32_t recip, int leaf, int max_level,
+                                                            uint16_t* __restrict__ marks,
                                                             uint32_t* __restrict__ counts)
 {
     __shared__ int8_t win[kTopoPoints + 64];   // w of the block's points and of the leaf_size points before them
@@ -637,7 +639,7 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __re
     for (int k = threadIdx.x; k < kTopoPoints + leaf; k += kTopoThreads) {
         const int64_t i = base - leaf + k;
         int w = -1;
-        if (i >= 0 && i + leaf < n) w = min(common_level(codes[i], codes[i + leaf], bits), max_level - 1);
+        if (i >= 0 && i + leaf < n) w = min(common_level(codes[i], codes[i + leaf], recip), max_level - 1);
         win[k] = (int8_t)w;
     }
     __syncthreads();
@@ -649,11 +651,11 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __re
         Mark m{31, 0, -1};
         if (i < n) {
             m.w = win[k + leaf];
-            const int up = i == 0 ? -1 : common_level(codes[i - 1], codes[i], bits);   // the parent's level
-            bool starts = i == 0;
-            if (i > 0 && up < max_level)
-                for (int t = 0; t < leaf && !starts; ++t) starts = win[k + t] >= up;   // windows from i - leaf to i - 1
-            if (starts) {
+            const int up = i == 0 ? -1 : common_level(codes[i - 1], codes[i], recip);   // the parent's level
+            int deepest = -1;   // of the windows from i - leaf to i - 1
+#pragma unroll 8
+            for (int t = 0; t < leaf; ++t) deepest = max(deepest, (int)win[k + t]);
+            if (i == 0 || (up < max_level && deepest >= up)) {
                 m.s = up + 1;
                 m.e = max(m.s, m.w + 1);
             } else {
@@ -762,18 +764,37 @@ __device__ __forceinline__ void aggregate_leaf(const BuildArrays& a, int32_t g, 
 {
 #pragma clang fp contract(off)
     double m = 0.0, sx = 0.0, sy = 0.0, sz = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
-    for (int32_t s = b; s < e; ++s) {
-        const float4 p = pts[s];
-        const double w = p.w;
-        m += w; sx += w * (double)p.x; sy += w * (double)p.y; sz += w * (double)p.z;
-        if (pdip) { const float4 q = pdip[s]; dx += q.x; dy += q.y; dz += q.z; }
+    float4 p[8];   // eight points' loads in flight together
+    for (int32_t s = b; s < e; s += 8) {
+        float4 q[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (s + t >= e) continue;
+            p[t] = pts[s + t];
+            if (pdip) q[t] = pdip[s + t];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (s + t >= e) continue;
+            const double w = p[t].w;
+            m += w; sx += w * (double)p[t].x; sy += w * (double)p[t].y; sz += w * (double)p[t].z;
+            if (pdip) { dx += q[t].x; dy += q[t].y; dz += q[t].z; }
+        }
     }
     const double cx = sx / m, cy = sy / m, cz = sz / m;
     double s2 = 0.0;
-    for (int32_t s = b; s < e; ++s) {
-        const float4 p = pts[s];
-        const double ex = (double)p.x - cx, ey = (double)p.y - cy, ez = (double)p.z - cz;
-        s2 += (double)p.w * (ex * ex + ey * ey + ez * ez);
+    for (int32_t s = b; s < e; s += 8) {
+        if (e - b > 8) {   // this group's again
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (s + t < e) p[t] = pts[s + t];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (s + t >= e) continue;
+            const double ex = (double)p[t].x - cx, ey = (double)p[t].y - cy, ez = (double)p[t].z - cz;
+            s2 += (double)p[t].w * (ex * ex + ey * ey + ez * ez);
+        }
     }
     s2 /= m;
     if (a.quad64) {
@@ -806,10 +827,10 @@ __device__ __forceinline__ void aggregate_block(const BuildArrays& a, int32_t k,
         int32_t nc[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const int32_t x = c + t < e ? c + t : e - 1;   // (past the end: the last child, unused)
-            q[t] = a.agg64[x];
-            sp[t] = a.spr64[x];
-            nc[t] = a.ncount[x];
+            if (c + t >= e) continue;
+            q[t] = a.agg64[c + t];
+            sp[t] = a.spr64[c + t];
+            nc[t] = a.ncount[c + t];
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -824,9 +845,9 @@ __device__ __forceinline__ void aggregate_block(const BuildArrays& a, int32_t k,
         if (e - f > 8) {   // d = 4 and 8: this group's again
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const int32_t x = c + t < e ? c + t : e - 1;
-                q[t] = a.agg64[x];
-                sp[t] = a.spr64[x];
+                if (c + t >= e) continue;
+                q[t] = a.agg64[c + t];
+                sp[t] = a.spr64[c + t];
             }
         }
 #pragma unroll
@@ -841,7 +862,8 @@ __device__ __forceinline__ void aggregate_block(const BuildArrays& a, int32_t k,
         for (int32_t c = f; c < e; c += 4) {
             double4 d[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] = a.dip64[c + t < e ? c + t : e - 1];
+            for (int t = 0; t < 4; ++t)
+                if (c + t < e) d[t] = a.dip64[c + t];
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 if (c + t < e) { dx += d[t].x; dy += d[t].y; dz += d[t].z; }
@@ -1007,8 +1029,10 @@ __global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __re
             const Mark m = unpack_mark(marks[lf.w]);
             const int shift = 60 - bits * m.e;
             const uint64_t pre = codes[lf.w] >> shift;
-            int64_t hi = n;
+            int64_t step = 1;   // most leaves end a few points on
             end = (int64_t)lf.w + 1;
+            for (; end + step <= n && (codes[end + step - 1] >> shift) == pre; step <<= 1) end += step;
+            int64_t hi = end + step - 1 < n ? end + step - 1 : n;
             while (end < hi) {
                 const int64_t mid = end + ((hi - end) >> 1);
                 if ((codes[mid] >> shift) == pre) end = mid + 1;
@@ -1210,7 +1234,8 @@ sbh_status build_tree_impl(const float* src, const float* w, const float* nrm, i
     BuildInfo h;
     // marks and counts of the sorted codes, then the sizes
     auto read_sizes = [&]() -> sbh_status {
-        k_topo_mark<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(t->codes, n, bits, leaf_size, max_level, marks, counts);
+        k_topo_mark<<<(unsigned)nblocks, kTopoThreads, 0, s>>>(t->codes, n, (65536u + bits - 1) / bits, leaf_size,
+                                                               max_level, marks, counts);
         SBH_TRY(hipGetLastError(), "topology mark kernel");
         k_topo_scan<<<channels, 1024, 0, s>>>(counts, (int)nblocks, info->totals);
         SBH_TRY(hipGetLastError(), "topology scan kernel");

@@ -1,5 +1,5 @@
 """Trees at the edges of the build's tiles, blocks and level ranges, bit for bit against the oracle:
-one and several sort tiles (8192 points), several chunks of tiles (32), blocks of 1024 points, the
+one and several sort tiles (8192 points), several chunks of tiles (32), blocks of 512 points, the
 smallest and largest leaves, shallow trees, heavy duplicates and clusters deeper than the levels
 that one workgroup aggregates."""
 import numpy as np
@@ -65,3 +65,13 @@ def test_runs_of_equal_top_bits(n, copies, scale):
     w = np.ones(len(src), np.float32)
     gt, ot = build_both(src, w, None, d=2, leaf_size=8)
     compare_trees(gt, ot)
+
+
+@pytest.mark.parametrize("n", [511, 512, 513])
+@pytest.mark.parametrize("leaf,max_level", [(1, 0), (8, 0), (8, 1)])
+def test_topology_block_edges(n, leaf, max_level):
+    """One block of points and its neighbour, leaves that end in the next block among them."""
+    from gpu_helpers import build_both, compare_trees
+    rng = np.random.Generator(np.random.PCG64(n))
+    src = rng.random((n, 3)).astype(np.float32)
+    compare_trees(*build_both(src, np.ones(n, np.float32), src, d=2, leaf_size=leaf, max_level=max_level))
