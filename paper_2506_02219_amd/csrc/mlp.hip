@@ -214,31 +214,37 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ p
 }
 
 // ---------------------------------------------------------------------------
-// Training: forward + backward for 64 rows per wavefront (one wavefront per
-// block), operand fragments staged through LDS.  Per-wave partial gradients
-// are summed in a fixed order by k_mlp_reduce (deterministic).
+// Training: forward + backward for 64 rows per workgroup, operand fragments
+// staged through LDS.  The workgroups' partial gradients are summed in a fixed
+// order by reduced_entry (deterministic).
 // ---------------------------------------------------------------------------
-// D(16x16) = A(16x16) * B(16x16) + C; A(m, k) at a[m*am + k*ak], B(k, n) at b[k*bk + n*bn]
-__device__ __forceinline__ f4 mfma_lds(const _Float16* a, int am, int ak, const _Float16* b, int bk, int bn, f4 c)
+// A fragment of a 16 x 16 operand, four consecutive k a lane: stored with k along the rows (one
+// 8-byte read), or down the columns.
+__device__ __forceinline__ h4 frag_row(const _Float16* p, int stride)
 {
     const int l = threadIdx.x & 63, r = l & 15, q = (l >> 4) * 4;
-    h4 av, bv;
-    for (int j = 0; j < 4; ++j) {
-        av[j] = a[r * am + (q + j) * ak];
-        bv[j] = b[(q + j) * bk + r * bn];
-    }
-    return mfma(av, bv, c);
+    return *reinterpret_cast<const h4*>(p + r * stride + q);
+}
+__device__ __forceinline__ h4 frag_col(const _Float16* p, int stride)
+{
+    const int l = threadIdx.x & 63, r = l & 15, q = (l >> 4) * 4;
+    h4 v;
+    for (int j = 0; j < 4; ++j) v[j] = p[(q + j) * stride + r];
+    return v;
 }
 
+// Row strides: whole 8-byte (16 for float32) units whose 16 rows start in different banks.
+constexpr int kN16 = 16 + 4, kN32 = 32 + 4, kN8 = 8 + 4;
 struct TrainLds {
-    _Float16 w1[32 * 16];   // W1 padded to 16 inputs
-    _Float16 w2[32 * 32];
-    _Float16 w3[16 * 32];   // W3 padded to 16 outputs
-    _Float16 x[64 * 16], h1[64 * 32], h2[64 * 32], dz[64 * 16], dh2[64 * 32], dh1[64 * 32];
-    float zf[64 * 16], dh2f[64 * 32], dh1f[64 * 32];
-    float xf[64 * 8];   // float32 features (skip term)
-    float tg[64 * 8], cn[64 * 8];
-    float b1[32], b2[32], b3[8];
+    alignas(16) _Float16 w1[32 * kN16];   // W1 padded to 16 inputs
+    alignas(16) _Float16 w2[32 * kN32];
+    alignas(16) _Float16 w3[16 * kN32];   // W3 padded to 16 outputs
+    alignas(16) _Float16 x[64 * kN16], dz[64 * kN16];
+    alignas(16) _Float16 h1[64 * kN32], h2[64 * kN32], dh2[64 * kN32], dh1[64 * kN32];
+    alignas(16) float zf[64 * kN8], dh2f[64 * kN32], dh1f[64 * kN32];
+    alignas(16) float xf[64 * kN8];   // float32 features (skip term)
+    alignas(16) float tg[64 * kN8], cn[64 * kN8];
+    alignas(16) float b1[32], b2[32], b3[16];
     float loss[64];
     int valid[64];
 };
@@ -253,14 +259,42 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// a hidden layer's activations max(d + b, 0), four consecutive units of a row
+__device__ __forceinline__ void store_relu(_Float16* h, const float* b, f4 d)
+{
+    const f4 bv = *reinterpret_cast<const f4*>(b);
+    h4 v;
+    for (int i = 0; i < 4; ++i) {
+        const float x = d[i] + bv[i];
+        v[i] = x > 0.0f ? (_Float16)x : (_Float16)0.0f;
+    }
+    *reinterpret_cast<h4*>(h) = v;
+}
+
+// a hidden layer's deltas, d where the unit was active, in float32 and binary16
+__device__ __forceinline__ void store_delta(float* df, _Float16* dh, const _Float16* h, f4 d)
+{
+    const h4 a = *reinterpret_cast<const h4*>(h);
+    f4 v;
+    h4 w;
+    for (int i = 0; i < 4; ++i) {
+        v[i] = (float)a[i] > 0.0f ? d[i] : 0.0f;
+        w[i] = (_Float16)v[i];
+    }
+    *reinterpret_cast<f4*>(df) = v;
+    *reinterpret_cast<h4*>(dh) = w;
+}
+
 // Rows [row_begin + 64 b, row_begin + 64 b + 64) for block b; rows >= n or
 // with all counts 0 contribute nothing.  Sums (not means) over the rows:
 // the deltas stay O(1) in binary16; k_mlp_reduce divides by the row count.
 // The chain of dependent layers bounds it, not the matrix units: wavefront g
 // takes the 16 rows of group g through both directions on its own, and then a
 // quarter of the weight gradients' tiles over all 64 rows (one wavefront for
-// all groups in turn took 21.5 us for 8192 rows, now 12.0; four lanes a row in
-// the softmax made no difference).
+// all groups in turn took 21.5 us for 8192 rows, four 12.5).  Every global load
+// is issued before the first is waited for, the loss is taken from the output
+// tile's registers by two lanes a row, four slots each, and rows of LDS start in
+// different banks: 6.0.
 __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm, const float* __restrict__ X,
                                                   const float* __restrict__ Tg, const float* __restrict__ Cn, int64_t n,
                                                   int64_t row_begin, int64_t rows, float* __restrict__ partial)
@@ -268,120 +302,127 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
     __shared__ TrainLds S;
     const int tid = threadIdx.x, l = tid & 63, r = l & 15, q = (l >> 4) * 4;
     const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
-    {   // thread t: two columns of row t / 4
+    {   // thread t: two columns of row t / 4, and its share of the parameters
         const int row = tid >> 2, k = (tid & 3) * 2;
         const int64_t rel = (int64_t)blockIdx.x * 64 + row, at = 8 * (row_begin + rel) + k;
         const bool in = rel < rows && row_begin + rel < n;
-        const float2 zero2 = make_float2(0.f, 0.f);
-        const float2 x = in ? make_float2(X[at], X[at + 1]) : zero2;
-        const float2 t = in ? make_float2(Tg[at], Tg[at + 1]) : zero2;
-        const float2 c = in ? make_float2(Cn[at], Cn[at + 1]) : zero2;
-        S.xf[row * 8 + k] = x.x;
-        S.xf[row * 8 + k + 1] = x.y;
-        S.x[row * 16 + k] = (_Float16)x.x;
-        S.x[row * 16 + k + 1] = (_Float16)x.y;
-        S.x[row * 16 + 8 + k] = (_Float16)0.0f;
-        S.x[row * 16 + 9 + k] = (_Float16)0.0f;
-        S.tg[row * 8 + k] = t.x;
-        S.tg[row * 8 + k + 1] = t.y;
-        S.cn[row * 8 + k] = c.x;
-        S.cn[row * 8 + k + 1] = c.y;
+        float2 x = make_float2(0.f, 0.f), t = x, c = x;
+        if (in) {
+            x = make_float2(X[at], X[at + 1]);
+            t = make_float2(Tg[at], Tg[at + 1]);
+            c = make_float2(Cn[at], Cn[at + 1]);
+        }
+        const float w1 = prm[kOffW1 + tid], w3 = prm[kOffW3 + tid];
+        float w2[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w2[i] = prm[kOffW2 + i * 256 + tid];
+        const int bi = tid < 32 ? kOffB1 + tid : tid < 64 ? kOffB2 + tid - 32 : kOffB3 + (tid & 7);
+        const float b = prm[bi];
+        *reinterpret_cast<float2*>(S.xf + row * kN8 + k) = x;
+        *reinterpret_cast<float2*>(S.tg + row * kN8 + k) = t;
+        *reinterpret_cast<float2*>(S.cn + row * kN8 + k) = c;
+        S.x[row * kN16 + k] = (_Float16)x.x;
+        S.x[row * kN16 + k + 1] = (_Float16)x.y;
+        S.x[row * kN16 + 8 + k] = (_Float16)0.0f;
+        S.x[row * kN16 + 9 + k] = (_Float16)0.0f;
+        S.w1[(tid >> 3) * kN16 + (tid & 7)] = (_Float16)w1;
+        S.w1[(tid >> 3) * kN16 + 8 + (tid & 7)] = (_Float16)0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S.w2[(8 * i + (tid >> 5)) * kN32 + (tid & 31)] = (_Float16)w2[i];
+        S.w3[(tid >> 5) * kN32 + (tid & 31)] = (_Float16)w3;
+        S.w3[(8 + (tid >> 5)) * kN32 + (tid & 31)] = (_Float16)0.0f;
+        if (tid < 32) S.b1[tid] = b;
+        else if (tid < 64) S.b2[tid - 32] = b;
+        else if (tid < 72) S.b3[tid - 64] = b;
     }
-#pragma unroll
-    for (int i = tid; i < 32 * 16; i += 256) S.w1[i] = (i % 16) < 8 ? (_Float16)prm[kOffW1 + (i / 16) * 8 + (i % 16)] : (_Float16)0.0f;
-#pragma unroll
-    for (int i = tid; i < 32 * 32; i += 256) S.w2[i] = (_Float16)prm[kOffW2 + i];
-#pragma unroll
-    for (int i = tid; i < 16 * 32; i += 256) S.w3[i] = (i / 32) < 8 ? (_Float16)prm[kOffW3 + i] : (_Float16)0.0f;
-    if (tid < 32) S.b1[tid] = prm[kOffB1 + tid];
-    else if (tid < 64) S.b2[tid - 32] = prm[kOffB2 + tid - 32];
-    else if (tid < 72) S.b3[tid - 64] = prm[kOffB3 + tid - 64];
     __syncthreads();
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     const int s0 = 16 * g;
+    const int hr = (s0 + r) * kN32 + q;   // the lane's row and units in the arrays of a hidden layer
     // forward (same operands and accumulation order as inference)
-    for (int t = 0; t < 2; ++t) {
-        const f4 d = mfma_lds(S.w1 + 16 * t * 16, 16, 1, S.x + s0 * 16, 1, 16, zero);
-        for (int i = 0; i < 4; ++i) {
-            const float v = d[i] + S.b1[16 * t + q + i];
-            S.h1[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
-        }
-    }
-    wave_lds_sync();
-    for (int t = 0; t < 2; ++t) {
-        f4 d = mfma_lds(S.w2 + 16 * t * 32, 32, 1, S.h1 + s0 * 32, 1, 32, zero);
-        d = mfma_lds(S.w2 + 16 * t * 32 + 16, 32, 1, S.h1 + s0 * 32 + 16, 1, 32, d);
-        for (int i = 0; i < 4; ++i) {
-            const float v = d[i] + S.b2[16 * t + q + i];
-            S.h2[(s0 + r) * 32 + 16 * t + q + i] = v > 0.0f ? (_Float16)v : (_Float16)0.0f;
-        }
+    {
+        const h4 x = frag_row(S.x + s0 * kN16, kN16);
+        for (int t = 0; t < 2; ++t)
+            store_relu(S.h1 + hr + 16 * t, S.b1 + 16 * t + q, mfma(frag_row(S.w1 + 16 * t * kN16, kN16), x, zero));
     }
     wave_lds_sync();
     {
-        f4 o = mfma_lds(S.w3, 32, 1, S.h2 + s0 * 32, 1, 32, zero);
-        o = mfma_lds(S.w3 + 16, 32, 1, S.h2 + s0 * 32 + 16, 1, 32, o);
-        for (int i = 0; i < 4; ++i) {
-            float v = 0.0f;
-            if (q + i < 8) {
-                v = o[i] + S.b3[q + i];
-                v = v + 16.0f * S.xf[(s0 + r) * 8 + q + i];
-            }
-            S.zf[(s0 + r) * 16 + q + i] = v;
+        const h4 ha = frag_row(S.h1 + s0 * kN32, kN32), hb = frag_row(S.h1 + s0 * kN32 + 16, kN32);
+        for (int t = 0; t < 2; ++t) {
+            f4 d = mfma(frag_row(S.w2 + 16 * t * kN32, kN32), ha, zero);
+            d = mfma(frag_row(S.w2 + 16 * t * kN32 + 16, kN32), hb, d);
+            store_relu(S.h2 + hr + 16 * t, S.b2 + 16 * t + q, d);
         }
     }
     wave_lds_sync();
-    // loss and dL/dz of the group's rows, one lane each: soft cross-entropy against the softmax over non-empty slots
-    if (l < 16) {
-        const int row = s0 + l;
-        float tg[8], cn[8], csum = 0.0f;
-        for (int k = 0; k < 8; ++k) {
-            tg[k] = S.tg[row * 8 + k];
-            cn[k] = S.cn[row * 8 + k];
-            csum += cn[k];
+    // the outputs of row r, slots q .. q + 3 (none from q = 8 on); loss and dL/dz: soft cross-entropy against the
+    // softmax over non-empty slots
+    {
+        f4 o = mfma(frag_row(S.w3, kN32), frag_row(S.h2 + s0 * kN32, kN32), zero);
+        o = mfma(frag_row(S.w3 + 16, kN32), frag_row(S.h2 + s0 * kN32 + 16, kN32), o);
+        const int row = s0 + r, at = row * kN8 + (q & 4);
+        const f4 x = *reinterpret_cast<const f4*>(S.xf + at);
+        const f4 b3 = *reinterpret_cast<const f4*>(S.b3 + (q & 4));
+        f4 tg = *reinterpret_cast<const f4*>(S.tg + at), cn = *reinterpret_cast<const f4*>(S.cn + at);
+        if (q >= 8) tg = cn = zero;
+        float z[4], csum = 0.0f, zmax = -INFINITY;
+        for (int i = 0; i < 4; ++i) {
+            z[i] = o[i] + b3[i];
+            z[i] = z[i] + 16.0f * x[i];
+            csum += cn[i];
+            if (cn[i] > 0.0f) zmax = fmaxf(zmax, z[i]);
         }
+        csum += __shfl_xor(csum, 16, 64);
+        zmax = fmaxf(zmax, __shfl_xor(zmax, 16, 64));
         const bool valid = csum > 0.0f;
-        float loss = 0.0f;
-        float zmax = -INFINITY;
-        for (int c = 0; c < 8; ++c)
-            if (cn[c] > 0.0f) zmax = fmaxf(zmax, S.zf[row * 16 + c]);
-        float e[8], s = 0.0f;
-        for (int c = 0; c < 8; ++c) {
-            e[c] = cn[c] > 0.0f ? expf(S.zf[row * 16 + c] - zmax) : 0.0f;
-            s += e[c];
+        // (sums run over the slots in order: the row's second lane carries on from its first)
+        float e[4], s = 0.0f, loss = 0.0f;
+        for (int i = 0; i < 4; ++i) {
+            e[i] = cn[i] > 0.0f ? expf(z[i] - zmax) : 0.0f;
+            s += e[i];
         }
-        for (int c = 0; c < 16; ++c) {
-            float dz = 0.0f;
-            if (c < 8 && valid && cn[c] > 0.0f) {
-                const float pi = e[c] / s;
-                if (tg[c] > 0.0f) loss -= tg[c] * logf(pi);
-                dz = pi - tg[c];
-            }
-            S.zf[row * 16 + c] = dz;
-            S.dz[row * 16 + c] = (_Float16)dz;
+        s = __shfl(s, r, 64);
+        if (q == 4)
+            for (int i = 0; i < 4; ++i) s += e[i];
+        s = __shfl(s, r + 16, 64);
+        f4 dz;
+        h4 dh;
+        float lp[4];
+        for (int i = 0; i < 4; ++i) {
+            const float pi = e[i] / s;
+            const bool on = valid && cn[i] > 0.0f;
+            lp[i] = on && tg[i] > 0.0f ? logf(pi) : 0.0f;
+            dz[i] = on ? pi - tg[i] : 0.0f;
+            dh[i] = (_Float16)dz[i];
+            loss -= tg[i] * lp[i];
         }
-        S.loss[row] = loss;
-        S.valid[row] = valid ? 1 : 0;
+        loss = __shfl(loss, r, 64);
+        if (q == 4)
+            for (int i = 0; i < 4; ++i) loss -= tg[i] * lp[i];
+        *reinterpret_cast<h4*>(S.dz + row * kN16 + q) = dh;
+        if (q < 8) *reinterpret_cast<f4*>(S.zf + at) = dz;
+        if (q == 4) {
+            S.loss[row] = loss;
+            S.valid[row] = valid ? 1 : 0;
+        }
     }
     wave_lds_sync();
     // back-propagate deltas
-    for (int kt = 0; kt < 2; ++kt) {   // dH2^T = W3^T dZ^T, masked by H2 > 0
-        const f4 d = mfma_lds(S.w3 + 16 * kt, 1, 32, S.dz + s0 * 16, 1, 16, zero);
-        for (int i = 0; i < 4; ++i) {
-            const int idx = (s0 + r) * 32 + 16 * kt + q + i;
-            const float v = (float)S.h2[idx] > 0.0f ? d[i] : 0.0f;
-            S.dh2f[idx] = v;
-            S.dh2[idx] = (_Float16)v;
+    {   // dH2^T = W3^T dZ^T, masked by H2 > 0
+        const h4 dz = frag_row(S.dz + s0 * kN16, kN16);
+        for (int kt = 0; kt < 2; ++kt) {
+            const int at = hr + 16 * kt;
+            store_delta(S.dh2f + at, S.dh2 + at, S.h2 + at, mfma(frag_col(S.w3 + 16 * kt, kN32), dz, zero));
         }
     }
     wave_lds_sync();
-    for (int kt = 0; kt < 2; ++kt) {   // dH1^T = W2^T dH2^T, masked by H1 > 0
-        f4 d = mfma_lds(S.w2 + 16 * kt, 1, 32, S.dh2 + s0 * 32, 1, 32, zero);
-        d = mfma_lds(S.w2 + 16 * 32 + 16 * kt, 1, 32, S.dh2 + s0 * 32 + 16, 1, 32, d);
-        for (int i = 0; i < 4; ++i) {
-            const int idx = (s0 + r) * 32 + 16 * kt + q + i;
-            const float v = (float)S.h1[idx] > 0.0f ? d[i] : 0.0f;
-            S.dh1f[idx] = v;
-            S.dh1[idx] = (_Float16)v;
+    {   // dH1^T = W2^T dH2^T, masked by H1 > 0
+        const h4 da = frag_row(S.dh2 + s0 * kN32, kN32), db = frag_row(S.dh2 + s0 * kN32 + 16, kN32);
+        for (int kt = 0; kt < 2; ++kt) {
+            const int at = hr + 16 * kt;
+            f4 d = mfma(frag_col(S.w2 + 16 * kt, kN32), da, zero);
+            d = mfma(frag_col(S.w2 + 16 * kN32 + 16 * kt, kN32), db, d);
+            store_delta(S.dh1f + at, S.dh1 + at, S.h1 + at, d);
         }
     }
     __syncthreads();
@@ -390,16 +431,18 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
     for (int kt = 0; kt < 2; ++kt) {
         f4 d = zero;
         if (g == 0) {          // dW3[c][k] = sum_s dz[s][c] h2[s][k]
-            for (int s = 0; s < 4; ++s) d = mfma_lds(S.dz + 16 * s * 16, 1, 16, S.h2 + 16 * s * 32 + 16 * kt, 32, 1, d);
+            for (int s = 0; s < 4; ++s)
+                d = mfma(frag_col(S.dz + 16 * s * kN16, kN16), frag_col(S.h2 + 16 * s * kN32 + 16 * kt, kN32), d);
             for (int i = 0; i < 4; ++i)
                 if (q + i < 8) out[kOffW3 + (q + i) * 32 + 16 * kt + r] = d[i];
         } else if (g < 3) {    // dW2[n][k] = sum_s dh2[s][n] h1[s][k]
             const int nt = g - 1;
             for (int s = 0; s < 4; ++s)
-                d = mfma_lds(S.dh2 + 16 * s * 32 + 16 * nt, 1, 32, S.h1 + 16 * s * 32 + 16 * kt, 32, 1, d);
+                d = mfma(frag_col(S.dh2 + 16 * s * kN32 + 16 * nt, kN32), frag_col(S.h1 + 16 * s * kN32 + 16 * kt, kN32), d);
             for (int i = 0; i < 4; ++i) out[kOffW2 + (16 * nt + q + i) * 32 + 16 * kt + r] = d[i];
         } else {               // dW1[n][k] = sum_s dh1[s][n] x[s][k]
-            for (int s = 0; s < 4; ++s) d = mfma_lds(S.dh1 + 16 * s * 32 + 16 * kt, 1, 32, S.x + 16 * s * 16, 16, 1, d);
+            for (int s = 0; s < 4; ++s)
+                d = mfma(frag_col(S.dh1 + 16 * s * kN32 + 16 * kt, kN32), frag_col(S.x + 16 * s * kN16, kN16), d);
             for (int i = 0; i < 4; ++i)
                 if (r < 8) out[kOffW1 + (16 * kt + q + i) * 8 + r] = d[i];
         }
@@ -408,8 +451,8 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
     if (g == 0) {
         if (l < 8) {
             float a = 0.0f;
-#pragma unroll 16
-            for (int s = 0; s < 64; ++s) a += S.zf[s * 16 + l];
+#pragma unroll
+            for (int s = 0; s < 64; ++s) a += S.zf[s * kN8 + l];
             out[kOffB3 + l] = a;
         }
         float loss = S.loss[l];
@@ -422,8 +465,8 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
     } else if (l < 32 && g < 3) {
         const float* d = g == 1 ? S.dh2f : S.dh1f;
         float a = 0.0f;
-#pragma unroll 16
-        for (int s = 0; s < 64; ++s) a += d[s * 32 + l];
+#pragma unroll
+        for (int s = 0; s < 64; ++s) a += d[s * kN32 + l];
         out[(g == 1 ? kOffB2 : kOffB1) + l] = a;
     }
 }
@@ -431,7 +474,7 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
 // Means over the rows that count, sums over blocks in a fixed order: entry p
 // of the gradient (p <= 1607), the loss (1608), the number of rows (1609).  A
 // workgroup takes 64 consecutive entries; its kReduceParts wavefronts each sum
-// one run of consecutive blocks in block order, eight loads in flight, and the
+// one run of consecutive blocks in block order, sixteen loads in flight, and the
 // runs' sums are added in run order.  Valid in the first wavefront's lanes.
 constexpr int kReduceParts = 8;
 struct ReduceLds {
@@ -445,16 +488,16 @@ __device__ __forceinline__ float reduced_entry(ReduceLds& S, const float* __rest
     const int per = (nblocks + kReduceParts - 1) / kReduceParts;
     const int b0 = g * per, b1 = min(nblocks, b0 + per);
     float s = 0.0f, cnt = 0.0f;
-    for (int b = b0; b < b1; b += 8) {
-        float v[8], c[8];
+    for (int b = b0; b < b1; b += 16) {
+        float v[16], c[16];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 16; ++k) {
             const int64_t row = (int64_t)min(b + k, b1 - 1) * kGradStride;
             v[k] = partial[row + at];
             c[k] = partial[row + 1609];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+        for (int k = 0; k < 16; ++k)
             if (b + k < b1) {
                 s += v[k];
                 cnt += c[k];
@@ -483,24 +526,30 @@ __global__ void __launch_bounds__(64 * kReduceParts) k_mlp_reduce(const float* _
 // A training step's second half: the reduction and Adam (Kingma and Ba; state
 // m[1608], v[1608]) on the parameters whose gradients the workgroup holds
 // (10.2 us with one load in flight per wavefront and 4.4 for Adam's own launch,
-// now 4.2 together).
+// now 3.8 together, sixteen loads in flight).
 __global__ void __launch_bounds__(64 * kReduceParts) k_mlp_step(const float* __restrict__ partial, int nblocks,
                                                                 float* __restrict__ prm, float* __restrict__ state,
                                                                 float lr, float bc1, float bc2,
                                                                 float* __restrict__ loss_out)
 {
     __shared__ ReduceLds S;
-    const float g = reduced_entry(S, partial, nblocks);
     const int p = blockIdx.x * 64 + threadIdx.x;
+    float m0 = 0.0f, v0 = 0.0f, x0 = 0.0f;   // loaded along with the partials
+    if (threadIdx.x < 64 && p < 1608) {
+        m0 = state[p];
+        v0 = state[1608 + p];
+        x0 = prm[p];
+    }
+    const float g = reduced_entry(S, partial, nblocks);
     if (threadIdx.x >= 64) return;
     if (p == 1608 && loss_out) *loss_out = g;
     if (p >= 1608) return;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float m = b1 * state[p] + (1.0f - b1) * g;
-    const float v = b2 * state[1608 + p] + (1.0f - b2) * g * g;
+    const float m = b1 * m0 + (1.0f - b1) * g;
+    const float v = b2 * v0 + (1.0f - b2) * g * g;
     state[p] = m;
     state[1608 + p] = v;
-    prm[p] -= lr * (m / bc1) / (sqrtf(v / bc2) + eps);
+    prm[p] = x0 - lr * (m / bc1) / (sqrtf(v / bc2) + eps);
 }
 
 // ---------------------------------------------------------------------------
