@@ -619,21 +619,23 @@ __global__ void k_mlp_pairs(TreeView tv, const float* __restrict__ queries, int6
     }
 }
 
-// float64 term of one source for the targets (no smooth-distance shift)
-template <int K>
-__device__ __forceinline__ double term64(float4 p, float4 dp, double qx, double qy, double qz, double eps2,
-                                         double alpha)
+// acc plus the float64 term of one source for the targets (no smooth-distance shift, nor the winding
+// number's constant, of which ratios of residuals are free).  SOFT: potential with eps > 0.
+template <int K, bool SOFT>
+__device__ __forceinline__ double add_term64(double acc, float4 p, float4 dp, double qx, double qy, double qz,
+                                             double eps2, double alpha)
 {
+#pragma clang fp contract(off)   // the same value for points and aggregates: a one-point child's residual is exactly 0
     const double dx = (double)p.x - qx, dy = (double)p.y - qy, dz = (double)p.z - qz;
-    const double r2 = dx * dx + dy * dy + dz * dz;
     if constexpr (K == SBH_POTENTIAL) {
-        return (double)p.w * rsqrt64<true>(r2 + eps2);
+        return fma((double)p.w, rsqrt64<!SOFT>(fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)))), acc);
     } else if constexpr (K == SBH_WINDING) {
+        const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
         const double u = rsqrt64<true>(r2);
-        const double v = ((double)dp.x * dx + (double)dp.y * dy + (double)dp.z * dz) * (u * u * u) * (0.25 / M_PI);
-        return r2 > 0.0 ? v : 0.0;
+        const double v = fma((double)dp.z, dz, fma((double)dp.y, dy, (double)dp.x * dx)) * (u * u * u);
+        return acc + (r2 > 0.0 ? v : 0.0);
     } else {
-        return (double)p.w * exp(-alpha * sqrt(r2));
+        return fma((double)p.w, exp(-alpha * sqrt(fma(dz, dz, fma(dy, dy, dx * dx)))), acc);
     }
 }
 
@@ -650,17 +652,17 @@ __device__ __forceinline__ double term64(float4 p, float4 dp, double qx, double 
 // arithmetic and those reads bound it; a workgroup per row, summing every row
 // anew with a square root, a division and eight range tests a point, left most
 // of the chip to a few rows near the root: 6.5 ms for 512 queries on 2^20
-// points, now 0.5 ms.
+// points, now 0.5 ms (17 float64 instructions a point, 76% of the issue slots).
 constexpr int kTgWaves = 8;
 constexpr int kTgMaxRows = 20;          // internal nodes on a path: at most the tree's levels
 constexpr uint32_t kTgShared = 2048;    // points from which a child is shared by the wavefronts
 
-template <int K>
+template <int K, bool SOFT>
 __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, const float* __restrict__ queries,
                                                                int lmax, const int4* __restrict__ loc, double eps2,
                                                                double alpha, float* __restrict__ Tg)
 {
-#pragma clang fp contract(off)   // one function for points and aggregates: a one-point child's residual is exactly 0
+#pragma clang fp contract(off)
     __shared__ int4 node[kTgMaxRows];                        // {children block, first point, points, level}
     __shared__ uint32_t first[kTgMaxRows][9];                // first point of each child, then the end
     __shared__ double part[kTgMaxRows * 8][kTgWaves];
@@ -696,17 +698,28 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
         const bool shared = e - b >= kTgShared;
         if (b == e || (!shared && s % kTgWaves != wv) || entered(k, c)) continue;
         const uint32_t step = shared ? 64 * kTgWaves : 64;
-        double acc = 0.0;
-        uint32_t i = b + (shared ? 64u * wv : 0u) + lane;
-        for (; i + 3 * step < e; i += 4 * step) {   // four loads in flight
-            double v[4];
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        uint32_t u = b + (shared ? 64u * wv : 0u);   // the wavefront's next 64 points
+        float4 p[4], m[4];                           // four loads in flight
+        for (; u + 3 * step + 64 <= e; u += 4 * step) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                v[t] = term64<K>(tv.pts[i + t * step], (K == SBH_WINDING) ? tv.pdip[i + t * step] : zero4, qx, qy, qz, eps2, alpha);
-            acc += (v[0] + v[1]) + (v[2] + v[3]);
+            for (int t = 0; t < 4; ++t) {
+                p[t] = (tv.pts + (u + t * step))[lane];
+                m[t] = K == SBH_WINDING ? (tv.pdip + (u + t * step))[lane] : zero4;
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
         }
-        for (; i < e; i += step)
-            acc += term64<K>(tv.pts[i], (K == SBH_WINDING) ? tv.pdip[i] : zero4, qx, qy, qz, eps2, alpha);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (u + t * step + lane >= e) continue;
+            p[t] = (tv.pts + (u + t * step))[lane];
+            m[t] = K == SBH_WINDING ? (tv.pdip + (u + t * step))[lane] : zero4;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (u + t * step + lane < e) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
+        double acc = (a[0] + a[1]) + (a[2] + a[3]);
         for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
         if (lane == 0) part[s][wv] = acc;
     }
@@ -731,7 +744,7 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
         double r = 0.0;
         if (first[k][c + 1] != first[k][c]) {
             const int64_t slot = (int64_t)node[k].x * 8 + c;
-            r = fabs(sums[k][c] - term64<K>(tv.bagg[slot], (K == SBH_WINDING) ? tv.bdip[slot] : zero4, qx, qy, qz, eps2, alpha));
+            r = fabs(sums[k][c] - add_term64<K, SOFT>(0.0, tv.bagg[slot], (K == SBH_WINDING) ? tv.bdip[slot] : zero4, qx, qy, qz, eps2, alpha));
         }
         resid[k][c] = r;
     }
@@ -1351,9 +1364,10 @@ hipError_t launch_mlp_pairs(const sbh_tree_impl* t, const float* queries, int64_
     if (e != hipSuccess) return e;
     const unsigned paths = (unsigned)(nq * 8);   // (lmax <= the tree's max_level <= kTgMaxRows)
     const double eps2 = (double)eps * (double)eps;
-    if (kernel == SBH_POTENTIAL) k_mlp_targets<SBH_POTENTIAL><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
-    else if (kernel == SBH_WINDING) k_mlp_targets<SBH_WINDING><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
-    else k_mlp_targets<SBH_SMOOTHDIST><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
+    if (kernel == SBH_POTENTIAL && eps2 > 0.0) k_mlp_targets<SBH_POTENTIAL, true><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
+    else if (kernel == SBH_POTENTIAL) k_mlp_targets<SBH_POTENTIAL, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
+    else if (kernel == SBH_WINDING) k_mlp_targets<SBH_WINDING, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
+    else k_mlp_targets<SBH_SMOOTHDIST, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
     return hipGetLastError();
 }
 

@@ -23,9 +23,9 @@ def _term(p, w, dip, q, kernel, eps, alpha):
     return w * np.exp(-alpha * np.sqrt(r2))
 
 
-@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("kernel,eps", [(0, 1e-3), (0, 0.0), (1, 1e-3), (2, 1e-3)])
 @pytest.mark.parametrize("n,side,depth", [(131072, 1.0, None), (40000, 1.0, 2), (17000, 0.02, None), (300, 1.0, 1)])
-def test_targets_match_the_points(n, side, depth, kernel):
+def test_targets_match_the_points(n, side, depth, kernel, eps):
     """Uniform cubes: 131,072 points give subdomains of about 16,384 whose children hold about 2,048."""
     import paper_2506_02219_amd as P
     rng = np.random.Generator(np.random.PCG64(n))
@@ -38,7 +38,7 @@ def test_targets_match_the_points(n, side, depth, kernel):
     dev = lambda a: torch.from_numpy(a).cuda()
     tree = P.sbh_build(dev(src), dev(w), dev(nrm))
     alpha = 5.0
-    X, Tg, Cn, where = P.sbh_mlp_pairs(tree, dev(q), kernel, seed=3, max_depth=depth, eps=1e-3, alpha=alpha)
+    X, Tg, Cn, where = P.sbh_mlp_pairs(tree, dev(q), kernel, seed=3, max_depth=depth, eps=eps, alpha=alpha)
     Tg, Cn, where = Tg.cpu().numpy(), Cn.cpu().numpy(), where.cpu().numpy()
     a = tree.export()
     perm = a["perm"].astype(np.int64)
@@ -50,7 +50,7 @@ def test_targets_match_the_points(n, side, depth, kernel):
     for row in np.nonzero(where[:, 0] >= 0)[0]:
         qq = q[row // per_query].astype(np.float64)
         b, nt, level = int(where[row, 1]), int(where[row, 2]), int(where[row, 3])
-        t = _term(pts[b:b + nt], pw[b:b + nt], dip[b:b + nt], qq, kernel, 1e-3, alpha)
+        t = _term(pts[b:b + nt], pw[b:b + nt], dip[b:b + nt], qq, kernel, eps, alpha)
         cnt = Cn[row].astype(np.int64)
         assert cnt.sum() == nt
         r, lo = np.zeros(8), 0
@@ -60,7 +60,7 @@ def test_targets_match_the_points(n, side, depth, kernel):
                 while a["level"][i] > level + 1:
                     i = a["parent"][i]
                 agg = a["agg"][i].astype(np.float64)
-                r[c] = abs(t[lo:lo + cnt[c]].sum() - _term(agg[:3], agg[3], a["dip"][i, :3].astype(np.float64), qq, kernel, 1e-3, alpha))
+                r[c] = abs(t[lo:lo + cnt[c]].sum() - _term(agg[:3], agg[3], a["dip"][i, :3].astype(np.float64), qq, kernel, eps, alpha))
             lo += cnt[c]
         e = 2.0 ** -53 * (64 + nt / 64) * np.abs(t).sum()
         if r.sum() <= 100 * e:
