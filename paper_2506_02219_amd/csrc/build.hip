@@ -239,9 +239,10 @@ __global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* 
 // kernels: the tiles' histograms; their prefix sums over a chunk of tiles,
 // with the chunk's totals; and the scatter, which adds up the chunks before
 // its own, sorts the tile in LDS and writes each digit's keys as one run.
-// Memory traffic and the scatter's latency bound it: 57 us a pass for 2^22
-// keys (the scatter 45, 2.2 TB/s).  Eight passes of 8-bit digits whose scatter
-// wrote every key on its own took 657 us, six passes 345, four and the runs 240;
+// Memory traffic and the scatter's latency bound it: 47 us a pass for 2^22
+// keys (the scatter 34, 2.9 TB/s; 45 with one workgroup a CU).  Eight passes of
+// 8-bit digits whose scatter wrote every key on its own took 657 us, six passes
+// 345, four and the runs 205;
 // k_sort_small with 5,003 points 61 us over all bits, 37 now.
 // ---------------------------------------------------------------------------
 constexpr int kRsBits = 10;
@@ -373,27 +374,31 @@ __global__ void __launch_bounds__(256) k_rs_prefix(uint32_t* __restrict__ hist, 
 }
 
 // vin == nullptr: the first pass, where a key's value is its index
-__global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __restrict__ keys,
+__global__ void __launch_bounds__(kRsThreads, 8) k_rs_scatter(const uint64_t* __restrict__ keys,
                                                            const uint32_t* __restrict__ vin, int64_t n, int shift,
                                                            const uint32_t* __restrict__ hist, int tiles, int per,
                                                            int chunks, const uint32_t* __restrict__ ctot,
                                                            uint64_t* __restrict__ kout, uint32_t* __restrict__ vout)
 {
-    __shared__ RsLds S;
-    __shared__ uint64_t buf[kRsTile];   // the tile's keys in digit order, then its values
+    // the ranks' counts, then the tile's keys in digit order, then its values: two workgroups fit a CU
+    __shared__ union {
+        RsLds rank;
+        uint64_t key[kRsTile];
+        uint32_t val[kRsTile];
+    } U;
     __shared__ uint32_t gbase[kRsBins];
+    RsLds& S = U.rank;
     const int tile = rs_tile(blockIdx.x, tiles);
     if (tile >= tiles) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t base = (int64_t)tile * kRsTile;
     const int cnt = (int)((n - base) < kRsTile ? (n - base) : kRsTile);
     uint64_t kk[kRsItems];
-    uint32_t vv[kRsItems], rank[kRsItems];
+    uint32_t rank[kRsItems];
 #pragma unroll
     for (int c = 0; c < kRsItems; ++c) {
         const int p = wv * (64 * kRsItems) + c * 64 + lane;
         kk[c] = p < cnt ? keys[base + p] : 0ull;
-        vv[c] = p < cnt ? (vin ? vin[base + p] : (uint32_t)(base + p)) : 0u;
     }
     // where this tile's keys of digit threadIdx.x go
     uint32_t total = 0u, before = hist[(int64_t)tile * kRsBins + threadIdx.x];
@@ -406,35 +411,41 @@ __global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __res
     const uint32_t first = block_exclusive_scan(total, S.ws);
     rs_rank(S, kk, rank, cnt, shift);
     gbase[threadIdx.x] = first + before - S.start[threadIdx.x];
-    uint32_t lpos[kRsItems];
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c) {   // a key's rank becomes its place in the tile
+        const uint32_t d = rs_digit(kk[c], shift);
+        rank[c] += S.start[d] + S.wcnt[wv][d];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kRsItems; ++c)
+        if (wv * (64 * kRsItems) + c * 64 + lane < cnt) U.key[rank[c]] = kk[c];
+    __syncthreads();
+    uint32_t vv[kRsItems];   // (loaded only here, when the keys' registers are free)
 #pragma unroll
     for (int c = 0; c < kRsItems; ++c) {
         const int p = wv * (64 * kRsItems) + c * 64 + lane;
-        const uint32_t d = rs_digit(kk[c], shift);
-        lpos[c] = S.start[d] + S.wcnt[wv][d] + rank[c];
-        if (p < cnt) buf[lpos[c]] = kk[c];
+        vv[c] = p < cnt ? (vin ? vin[base + p] : (uint32_t)(base + p)) : 0u;
     }
-    __syncthreads();
     uint32_t gpos[kRsItems];
 #pragma unroll
     for (int c = 0; c < kRsItems; ++c) {
         const int p = c * kRsThreads + threadIdx.x;
         if (p < cnt) {
-            const uint64_t key = buf[p];
+            const uint64_t key = U.key[p];
             gpos[c] = gbase[rs_digit(key, shift)] + (uint32_t)p;
             kout[gpos[c]] = key;
         }
     }
     __syncthreads();
-    uint32_t* vbuf = reinterpret_cast<uint32_t*>(buf);
 #pragma unroll
     for (int c = 0; c < kRsItems; ++c)
-        if (wv * (64 * kRsItems) + c * 64 + lane < cnt) vbuf[lpos[c]] = vv[c];
+        if (wv * (64 * kRsItems) + c * 64 + lane < cnt) U.val[rank[c]] = vv[c];
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kRsItems; ++c) {
         const int p = c * kRsThreads + threadIdx.x;
-        if (p < cnt) vout[gpos[c]] = vbuf[p];
+        if (p < cnt) vout[gpos[c]] = U.val[p];
     }
 }
 
@@ -445,9 +456,11 @@ __global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const uint64_t* __res
 template <class V>
 __device__ __forceinline__ bool rs_finish_run(uint64_t* keys, V* vals, int64_t n, int64_t i, int shift)
 {
-    const uint64_t k = keys[i], p = i > 0 ? keys[i - 1] : ~0ull, top = k >> shift;   // (a code has 60 bits)
+    const uint64_t k = keys[i], top = k >> shift;
+    const uint64_t p = i > 0 ? keys[i - 1] : ~0ull, q = i + 1 < n ? keys[i + 1] : ~0ull;   // (a code has 60 bits)
     if ((p >> shift) != top) {
-        int len = 1;
+        if ((q >> shift) != top) return false;   // most codes
+        int len = 2;
         while (len <= kRsRun && i + len < n && (keys[i + len] >> shift) == top) ++len;
         if (len > kRsRun) return false;
         for (int a = 1; a < len; ++a) {
