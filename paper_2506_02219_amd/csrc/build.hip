@@ -7,7 +7,8 @@
 //      fl32(1/side) (correctly rounded), plus an input validity flag;
 //   2. Morton code: cell_a = min(2^20-1, (u32) fl32(fl32(x_a - lo_a) *
 //      inv_side) * 2^20), bits of x/y/z interleaved into 60 bits;
-//   3. stable LSD radix sort of (code, index), 10-bit digits; up to 8192 points
+//   3. stable LSD radix sort of (code, index), 10-bit digits, over the codes'
+//      top bits with the few equal ones put in order after; up to 8192 points
 //      in one workgroup;
 //   4. topology in two passes over the sorted codes.  A node at level l is a
 //      maximal run of equal (bits*l)-bit prefix; it is split iff count >
