@@ -577,7 +577,7 @@ def main():
         ms_b = timed(run_brute, 2, 1)
         inter = float(cl.m) * N
         tf_b = BRUTE_FLOPS[kernel] * inter / (ms_b * 1e-3) / 1e12
-        brute = dict(kernel="k_brute32" if kernel != P.SMOOTHDIST else "k_brute<2, float>", queries=N,
+        brute = dict(kernel=f"k_brute<{kernel}, float>", queries=N,
                      sources=int(cl.m), ms=ms_b, interactions_per_s=inter / (ms_b * 1e-3),
                      flops_per_interaction=BRUTE_FLOPS[kernel], achieved_TFLOPs=tf_b,
                      frac_of_fp32_peak=tf_b / FP32_PEAK_TFLOPS, frac_of_non_packed_fp32=tf_b / (FP32_PEAK_TFLOPS / 2),

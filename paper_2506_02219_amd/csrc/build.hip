@@ -231,9 +231,9 @@ __global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* 
 // The passes run over the codes' top bits alone (four of the six digits, three
 // in k_sort_small): few codes share these, and a pass over the result puts
 // such short runs in order.  Where a longer run is out of order, as in a cloud
-// of clusters far smaller than its cube, the six passes over all bits follow;
-// they start from codes whose equals are in input order already.  A workgroup owns a tile of 8192
-// consecutive keys, its wavefront v the v-th sixteenth, which it walks in
+// of clusters far smaller than its cube, the six passes over all bits follow
+// (a build of 2^22 points 0.97 ms, of as many in clumps a 2^-15th of the cube
+// wide 1.35).  A workgroup owns a tile of 8192 consecutive keys, its wavefront v the v-th sixteenth, which it walks in
 // eight chunks of 64 in order: a key's rank among the tile's equal digits is
 // (wavefronts before) + (chunks of this wavefront before) + (lanes of the
 // chunk before), the last from one ballot per digit bit.  A pass is three
@@ -243,8 +243,8 @@ __global__ void k_gather_points(const float4* __restrict__ rec, const uint32_t* 
 // Memory traffic and the scatter's latency bound it: 47 us a pass for 2^22
 // keys (the scatter 34, 2.9 TB/s; 45 with one workgroup a CU).  Eight passes of
 // 8-bit digits whose scatter wrote every key on its own took 657 us, six passes
-// 345, four and the runs 205;
-// k_sort_small with 5,003 points 61 us over all bits, 37 now.
+// 345, four and the runs 205; k_sort_small with 5,003 points 61 over all bits,
+// 37 now.
 // ---------------------------------------------------------------------------
 constexpr int kRsBits = 10;
 constexpr int kRsBins = 1 << kRsBits;
@@ -641,7 +641,10 @@ __device__ __forceinline__ void count_levels(Mark m, int lane, uint32_t& cn, uin
 // Marks of every point, and per block of kTopoPoints points the number of
 // nodes (channel 2 l) and internal nodes (2 l + 1) of each level that start in
 // it: counts[channel * gridDim.x + block].  One ballot per level and wavefront
-// chunk, lane l keeping level l's counts.
+// chunk, lane l keeping level l's counts.  Latency and vector issue bound it
+// (2^22 points: 34 -> 27 us without a division by `bits` and with all of a
+// point's windows read at once; blocks of 512 points, where 1,024 left a few
+// thousand points to a handful of workgroups: 5,003 points 8.2 -> 4.9 us).
 __global__ void __launch_bounds__(kTopoThreads) k_topo_mark(const uint64_t* __restrict__ codes, int64_t n,
                                                             uint32_t recip, int leaf, int max_level,
                                                             uint16_t* __restrict__ marks,
@@ -932,8 +935,11 @@ __global__ void __launch_bounds__(kTopThreads) k_aggregate_top(BuildArrays a, To
 // its parent, and the first child of a node that starts at the point is its
 // node of the next level.  A point with nodes has one leaf (its deepest node);
 // the block collects its leaves in LDS and takes their aggregates with every
-// lane busy.  Vector issue (the levels' ballots, the float64 divisions) and the
-// writes, about 180 bytes a node, bound it.
+// lane busy.  Writes of about 180 bytes a node, in parts of lines over a dozen
+// arrays, bound it (2^22 surface points: 0.30 GB in 160 us, 65 of them without
+// the leaves; 180 with a bisection over all points for the block's last leaf;
+// 5,003 points 18 -> 9.5 us).  Gathering the nodes in LDS so that every store is
+// a full one (a quarter of the store instructions) gave 157.
 __global__ void __launch_bounds__(kTopoThreads) k_topo_emit(const uint64_t* __restrict__ codes,
                                                             const uint16_t* __restrict__ marks, int64_t n,
                                                             const uint32_t* __restrict__ counts, TopoOff off,
