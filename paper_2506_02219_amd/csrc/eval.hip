@@ -2162,13 +2162,14 @@ constexpr int bh_stack_depth()
     return D == 2 ? (8 - 1) * 20 + 2 : (64 - 1) * 10 + 2;
 }
 
-// One tile of 64 consecutive queries per workgroup, whose W wavefronts share
-// its opened nodes: level by level, the blocks to open are listed in LDS,
-// entry f goes to wavefront f mod W, and each wavefront lists the children it
-// finds near; a wavefront whose part of the next list is full walks the child
-// depth-first instead, on a stack of its own (always wavefront-uniform).  The
-// wavefronts' sums are added in order at the end, so a value depends on the
-// tree, the tile and beta alone.
+// One tile of 64 consecutive queries per workgroup, whose opened nodes are
+// shared by W parts: level by level, the blocks to open are listed in LDS,
+// entry f goes to part f mod W, and each part lists the children it finds near;
+// a part whose share of the next list is full walks the child depth-first
+// instead, on its wavefront's stack (always wavefront-uniform).  The parts' sums
+// are added in order at the end, so a value depends on the tree, the tile and
+// beta alone.  PW of W wavefronts take the parts, each its own or several in
+// turn, with the same sums (the rule is at bh_waves).
 // Instruction issue bounds it, scalar as much as vector.  Before, a wavefront
 // walked a whole tile depth-first, one scalar round trip per child after
 // another; a tile near the sources opens several times as many nodes as the
@@ -2183,8 +2184,8 @@ constexpr int bh_stack_depth()
 // 3105 -> 1211 (1306 with four), at beta = 0.5 302 -> 132 (182).
 constexpr int kBhList = 64;   // entries of a wavefront's part of a list
 
-template <int D, int K, bool O64, int W>
-__global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
+template <int D, int K, bool O64, int W, int PW>
+__global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
                                                float* __restrict__ out)
 {
 #pragma clang fp contract(off)
@@ -2194,11 +2195,11 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
     constexpr int MAXS = bh_stack_depth<D>();
     // an entry is a child block to open: {block id, first point} and, apart, the level of its
     // node (block ids take all 32 bits; levels are below 64)
-    __shared__ int2 stack[W][MAXS];
-    __shared__ uint8_t stack_lvl[W][MAXS];
+    __shared__ int2 stack[PW][MAXS];
+    __shared__ uint8_t stack_lvl[PW][MAXS];
     __shared__ int2 list[2][W][kBhList];   // the level's blocks and the next level's
     __shared__ int n_list[2][W];
-    __shared__ float part[W][64];
+    __shared__ float part[PW > 1 ? W : 1][64];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t j = (int64_t)blockIdx.x * 64 + lane;
     const bool valid = j < nq;
@@ -2225,8 +2226,16 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
         if (wv == 0) part[0][lane] = smooth_shift<D>(tv, qx, qy, qz, a.alpha);
     }
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float acc = 0.0f;
-    if (threadIdx.x < W) n_list[0][threadIdx.x] = 0;
+    // sums of the wavefront's parts wv, wv + PW ..., and what each has listed for the next level
+    constexpr int R = W / PW;
+    float accs[R];
+    int listed[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        accs[i] = 0.0f;
+        listed[i] = 0;
+    }
+    if (PW > 1 && threadIdx.x < W) n_list[0][threadIdx.x] = 0;
     __syncthreads();
     if constexpr (K == SBH_SMOOTHDIST) r0 = part[0][lane];
     // root: accepted when every lane passes the far-field test
@@ -2234,16 +2243,17 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
         const float4 g = cld4(tv.nagg);
         const float dx = g.x - qx, dy = g.y - qy, dz = g.z - qz;
         if (__ballot(!(norm2(dx, dy, dz) >= limit2(tv.diam0))) == 0ull) {
-            if (wv == 0) acc = term<K>(g, (K == SBH_WINDING) ? cld4(tv.ndip) : zero4, qx, qy, qz, kp, r0);
+            if (wv == 0) accs[0] = term<K>(g, (K == SBH_WINDING) ? cld4(tv.ndip) : zero4, qx, qy, qz, kp, r0);
         } else if (!tv.root_internal) {
             if (wv == 0)
                 for (int i = 0; i < tv.n_points; ++i)
-                    acc = term_acc<K>(cld4(tv.pts + i), (K == SBH_WINDING) ? cld4(tv.pdip + i) : zero4, qx, qy, qz, kp, r0,
-                                      acc);
+                    accs[0] = term_acc<K>(cld4(tv.pts + i), (K == SBH_WINDING) ? cld4(tv.pdip + i) : zero4, qx, qy, qz, kp,
+                                          r0, accs[0]);
         } else if (threadIdx.x == 0) {
             list[0][0][0] = make_int2(0, 0);   // block 0, first point 0
-            n_list[0][0] = 1;
+            if (PW > 1) n_list[0][0] = 1;
         }
+        if (PW == 1 && tv.root_internal && __ballot(!(norm2(dx, dy, dz) >= limit2(tv.diam0))) != 0ull) listed[0] = 1;
     }
     __syncthreads();
     int cur = 0;
@@ -2251,10 +2261,25 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
         int cum[W + 1];   // the level's entries by wavefront that listed them
         cum[0] = 0;
 #pragma unroll
-        for (int v = 0; v < W; ++v) cum[v + 1] = cum[v] + __builtin_amdgcn_readfirstlane(n_list[cur][v]);
+        for (int v = 0; v < W; ++v)
+            cum[v + 1] = cum[v] + (PW == 1 ? listed[PW == 1 ? v : 0] : __builtin_amdgcn_readfirstlane(n_list[cur][v]));
         if (cum[W] == 0) break;
-        int pushed = 0;
-        for (int f = wv; f < cum[W]; f += W) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) listed[i] = 0;
+        auto next_part = [&](float acc, int pushed) {   // the parts take turns: the one at hand goes last
+#pragma unroll
+            for (int i = 0; i + 1 < R; ++i) {
+                accs[i] = accs[i + 1];
+                listed[i] = listed[i + 1];
+            }
+            accs[R - 1] = acc;
+            listed[R - 1] = pushed;
+        };
+        int f = wv;
+        for (; f < cum[W]; f += PW) {
+            const int pv = f % W;
+            float acc = accs[0];
+            int pushed = listed[0];
             int src = 0, at = f;
 #pragma unroll
             for (int v = 1; v < W; ++v)
@@ -2319,7 +2344,7 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
                     const int at = D == 2 ? __popc((uint32_t)(opened & below)) : (int)__popcll((uint64_t)(opened & below));
                     const int32_t cb = base + (D == 2 ? __popc((uint32_t)(inner & below)) : (int)__popcll((uint64_t)(inner & below)));
                     if (level == depth && pushed + n_open <= kBhList) {
-                        if (mine) list[cur ^ 1][wv][pushed + at] = make_int2(cb, (int32_t)first);
+                        if (mine) list[cur ^ 1][pv][pushed + at] = make_int2(cb, (int32_t)first);
                         pushed += n_open;
                     } else {
                         if (mine) {
@@ -2366,16 +2391,29 @@ __global__ void __launch_bounds__(64 * W) k_bh(TreeView tv, const float* __restr
                 pre = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
                 __builtin_amdgcn_wave_barrier();
             }
+            next_part(acc, pushed);
         }
-        if (lane == 0) n_list[cur ^ 1][wv] = pushed;
+        for (; f % W != wv; f += PW) next_part(accs[0], listed[0]);   // until the first part is at hand again
+        if constexpr (PW > 1) {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (lane == 0) n_list[cur ^ 1][wv + i * PW] = listed[i];
+        }
         __syncthreads();
         cur ^= 1;
     }
-    part[wv][lane] = acc;
-    __syncthreads();
-    if (wv != 0) return;
+    float acc = accs[0];
+    if constexpr (PW == 1) {
 #pragma unroll
-    for (int v = 1; v < W; ++v) acc += part[v][lane];
+        for (int v = 1; v < W; ++v) acc += accs[v];
+    } else {
+#pragma unroll
+        for (int i = 0; i < R; ++i) part[wv + i * PW][lane] = accs[i];
+        __syncthreads();
+        if (wv != 0) return;
+#pragma unroll
+        for (int v = 1; v < W; ++v) acc += part[v][lane];
+    }
     if (valid) out[j] = votes ? query_value<K>(acc, r0, logwbar, a.alpha, qx, qy, qz) : __builtin_nanf("");
 }
 
@@ -2708,15 +2746,50 @@ static hipError_t launch_cut_dk(const TreeView& tv, const float* q, int64_t nq, 
     return hipGetLastError();
 }
 
+// Wavefronts per tile.  As many as the tile has parts while the launch leaves
+// wavefront slots empty, which it does up to some 1,024 tiles, and where tiles
+// are so unequal that the last ones set its time: at a large beta.  Where a
+// launch of many tiles opens few nodes in each, wavefronts that wait for one
+// another cost more than they save.  10^6 queries (15,625 tiles) in pixel order,
+// d = 2, us with one / two / four: 2^22 surface samples, winding, beta 0.2
+// 14.8 / 15.2 / 16.9, 0.5 125 / 89 / 86, 1 374 / 262 / 222; 2^16 samples, smooth
+// distance, 0.2 27 / 33 / 53, 0.5 71 / 67 / 89, 1 212 / 173 / 180.  200,000
+// queries on 2^22 samples, smooth distance, 0.2 16 / 16 / 21, 0.5 140 / 82 / 55.
+// d = 4, two parts: 10^6 on 2^16 samples, smooth distance, 0.2 79 / 110, 1 409 /
+// 381; winding, 0.2 20 / 26, 1 265 / 232.
+template <int D>
+static int bh_waves(int64_t tiles, float beta, int64_t n)
+{
+    const bool many = tiles > 4096;
+    if (tiles <= 1024) return D == 2 ? 4 : 2;
+    if (D == 2) {
+        if (beta < 0.4f) return many ? 1 : 2;
+        const float four = n < (1 << 14) ? 1.5f : n < (1 << 17) ? 1.0f : 0.6f;
+        return many && beta < four ? 2 : 4;
+    }
+    return beta < (!many ? 0.15f : n < (1 << 17) ? 0.6f : 0.25f) ? 1 : 2;
+}
+
+template <int D, int K, int W, int PW>
+static void launch_bh_pw(const TreeView& tv, const float* q, int64_t nq, unsigned tiles, const BhArgs& a, float* out,
+                         hipStream_t s)
+{
+    if (tv.wide) k_bh<D, K, true, W, PW><<<tiles, 64 * PW, 0, s>>>(tv, q, nq, a, out);
+    else k_bh<D, K, false, W, PW><<<tiles, 64 * PW, 0, s>>>(tv, q, nq, a, out);
+}
+
 template <int D, int K>
 static hipError_t launch_bh_dk(const TreeView& tv, const float* q, int64_t nq, const EvalLaunch& e, float* out,
                                hipStream_t s)
 {
     BhArgs a{e.beta, e.eps * e.eps, e.alpha};
-    constexpr int W = D == 2 ? 4 : 2;   // wavefronts per tile
-    const unsigned tiles = (unsigned)((nq + 63) / 64);
-    if (tv.wide) k_bh<D, K, true, W><<<tiles, 64 * W, 0, s>>>(tv, q, nq, a, out);
-    else k_bh<D, K, false, W><<<tiles, 64 * W, 0, s>>>(tv, q, nq, a, out);
+    constexpr int W = D == 2 ? 4 : 2;
+    const int64_t tiles = (nq + 63) / 64;
+    switch (bh_waves<D>(tiles, e.beta, tv.n_points)) {
+    case 1: launch_bh_pw<D, K, W, 1>(tv, q, nq, (unsigned)tiles, a, out, s); break;
+    case 2: launch_bh_pw<D, K, W, 2>(tv, q, nq, (unsigned)tiles, a, out, s); break;
+    default: launch_bh_pw<D, K, W, W>(tv, q, nq, (unsigned)tiles, a, out, s); break;
+    }
     return hipGetLastError();
 }
 

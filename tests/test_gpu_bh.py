@@ -49,3 +49,22 @@ def test_bh_non_finite_queries_stay_out_of_the_vote(d):
         assert np.isnan(b[[5, 70]]).all()
         # the others' cut can only be coarser by what queries 5 and 70 opened: every query here is far away
         assert np.allclose(a[keep], b[keep], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("d", [2, 4])
+@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("beta", [0.1, 0.3, 0.5, 2.0])
+def test_same_values_for_any_number_of_wavefronts(d, kernel, beta):
+    """Launches of 1,024 tiles and fewer, of up to 4,096, and of more take different numbers of wavefronts
+    a tile; a query's value is the same bit for bit."""
+    import paper_2506_02219_amd as P
+    rng = np.random.Generator(np.random.PCG64(5))
+    n, nq = 20000, 64 * 4200 - 17
+    src = torch.from_numpy(rng.random((n, 3)).astype(np.float32)).cuda()
+    nrm = torch.from_numpy(rng.standard_normal((n, 3)).astype(np.float32)).cuda()
+    q = torch.from_numpy((2 * rng.random((nq, 3)) - 0.5).astype(np.float32)).cuda()
+    tree = P.sbh_build(src, torch.ones(n, device="cuda"), nrm, branching=d)
+    whole = P.sbh_eval(tree, q, kernel, beta=beta, samples=0)
+    for size in (64 * 1024, 64 * 3000):
+        parts = torch.cat([P.sbh_eval(tree, c, kernel, beta=beta, samples=0) for c in q.split(size)])
+        assert torch.equal(whole.view(torch.int32), parts.view(torch.int32))
