@@ -298,6 +298,19 @@ __global__ void __launch_bounds__(256) k_sbh(TreeView tv, const float* __restric
 // ---------------------------------------------------------------------------
 constexpr int kPoolPaths = 256;
 
+// Queries per wavefront of a launch: as many as a pool holds, unless that leaves
+// wavefront slots empty, where smaller pools (a path a lane, or more) make each
+// wavefront's chain of steps shorter.  Below some 4,096 wavefronts: 500 to 7,671
+// queries on 2^20 surface samples 30 -> 17 us (potential; 37 -> 19 winding),
+// 30,000 30 -> 22, 100,000 50 -> 43 (49 at 2,048 wavefronts, 52 at 8,192, where
+// refilled lanes are missed).
+constexpr int64_t kPoolWaves = 4096;
+static int pool_queries(int64_t nq, int paths_per_query)
+{
+    const int most = kPoolPaths / paths_per_query, least = std::max(1, 64 / paths_per_query);
+    return (int)std::max<int64_t>(least, std::min<int64_t>(most, (nq + kPoolWaves - 1) / kPoolWaves));
+}
+
 // The uniform variate of a 32-bit random word: its top 24 bits times 2^-24
 // (exactly representable, in [0, 1)).
 __device__ __forceinline__ float unit24(uint32_t x) { return (float)(x >> 8) * 5.9604644775390625e-8f; }
@@ -313,7 +326,7 @@ __device__ __forceinline__ sbh_u32x4v cld4u(const uint32_t* p) { return *(const 
 // SOFT: the potential with eps > 0.
 template <int D, int K, bool TRACE, bool CMP = false, bool SOFT = false>
 __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __restrict__ queries, int64_t nq,
-                                                  SbhArgs a, float* __restrict__ out)
+                                                  SbhArgs a, int Q, float* __restrict__ out)
 {
 #pragma clang fp contract(off)
     static_assert(!CMP || (D == 2 && K != SBH_WINDING), "compressed aggregates: d = 2, no dipoles");
@@ -331,7 +344,6 @@ __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __re
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int S = a.samples;
-    const int Q = kPoolPaths / (D3 * S);   // queries per wavefront (the launcher keeps D^3 S <= kPoolPaths)
     const int NP = Q * D3 * S;
     const int64_t q0 = ((int64_t)blockIdx.x * 4 + wv) * Q;
     for (int c = threadIdx.x; c < D3; c += 256) {   // before the block's waves part: all reach the barrier
@@ -2712,13 +2724,13 @@ static hipError_t launch_sbh_dk(const TreeView& tv, const float* q, int64_t nq, 
         return hipErrorInvalidValue;   // branching 8: the coherent walk only (the API checks G)
     } else if ((int64_t)D * D * D * e.samples <= kPoolPaths) {
         // per-lane walks with lane refill: Q queries per wavefront, four wavefronts per block
-        const int64_t qpw = kPoolPaths / (D * D * D * e.samples);
+        const int qpw = pool_queries(nq, D * D * D * e.samples);
         const int64_t waves = (nq + qpw - 1) / qpw;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
-        if (e.paths) k_sbh_pool<D, K, true><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
+        if (e.paths) k_sbh_pool<D, K, true><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
         else if (K == SBH_POTENTIAL && a.eps2 > 0.0f)
-            k_sbh_pool<D, K, false, false, K == SBH_POTENTIAL><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
-        else k_sbh_pool<D, K, false><<<blocks, 256, 0, s>>>(tv, q, nq, a, out);
+            k_sbh_pool<D, K, false, false, K == SBH_POTENTIAL><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
+        else k_sbh_pool<D, K, false><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
         return hipGetLastError();
     } else {
         const int64_t waves = (nq + QPW - 1) / QPW;
@@ -2840,14 +2852,14 @@ hipError_t launch_sbh_eval(const sbh_tree_impl* t, const float* queries, int64_t
                   e.eps * e.eps, e.alpha, e.paths};
         if (e.group % 64 != 0) {   // per-query streams: the per-lane walk with lane refill
             if (8 * e.samples > kPoolPaths) return hipErrorInvalidValue;   // the API checks S
-            const int64_t qpw = kPoolPaths / (8 * e.samples);
+            const int qpw = pool_queries(nq, 8 * e.samples);
             const unsigned blocks = (unsigned)(((nq + qpw - 1) / qpw + 3) / 4);
             if (e.kernel == SBH_POTENTIAL) {
-                if (e.paths) k_sbh_pool<2, SBH_POTENTIAL, true, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, out);
-                else k_sbh_pool<2, SBH_POTENTIAL, false, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, out);
+                if (e.paths) k_sbh_pool<2, SBH_POTENTIAL, true, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, qpw, out);
+                else k_sbh_pool<2, SBH_POTENTIAL, false, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, qpw, out);
             } else {
-                if (e.paths) k_sbh_pool<2, SBH_SMOOTHDIST, true, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, out);
-                else k_sbh_pool<2, SBH_SMOOTHDIST, false, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, out);
+                if (e.paths) k_sbh_pool<2, SBH_SMOOTHDIST, true, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, qpw, out);
+                else k_sbh_pool<2, SBH_SMOOTHDIST, false, true><<<blocks, 256, 0, s>>>(tv, queries, nq, a, qpw, out);
             }
             return hipGetLastError();
         }

@@ -21,3 +21,20 @@ def test_streams_match_oracle(n, d, leaf, max_level, eps):
     q[0] = 0.0
     gt, ot = build_both(src, w, d=d, leaf_size=leaf, max_level=max_level)
     check_sbh(gt, ot, q, 0, samples=2, seed=7, group=1, eps=eps)
+
+
+@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("d,samples", [(2, 1), (2, 3), (2, 32), (4, 1)])
+def test_same_values_for_any_pool(d, samples, kernel):
+    """Small launches give a wavefront fewer queries: a query's value is the same bit for bit."""
+    import paper_2506_02219_amd as P
+    rng = np.random.Generator(np.random.PCG64(9))
+    n, nq = 9000, 140001 if samples < 32 else 9001
+    src = torch.from_numpy(rng.random((n, 3)).astype(np.float32)).cuda()
+    nrm = torch.from_numpy(rng.standard_normal((n, 3)).astype(np.float32)).cuda()
+    q = torch.from_numpy((2 * rng.random((nq, 3)) - 0.5).astype(np.float32)).cuda()
+    tree = P.sbh_build(src, torch.ones(n, device="cuda"), nrm, branching=d)
+    whole = P.sbh_eval(tree, q, kernel, samples=samples, seed=3, group=1)
+    for m in (33, 30001):   # streams are keyed by the query's index, so the first ones are the same
+        part = P.sbh_eval(tree, q[:m].contiguous(), kernel, samples=samples, seed=3, group=1)
+        assert torch.equal(whole[:m].view(torch.int32), part.view(torch.int32))
