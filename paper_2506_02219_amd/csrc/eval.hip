@@ -28,6 +28,7 @@
 // nodes to open are wavefront-uniform lists in LDS.
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <cmath>
 #include <cstdlib>
 #include <type_traits>
@@ -323,7 +324,7 @@ __device__ __forceinline__ sbh_u32x4v gld4u(const uint32_t* p) { return *(const 
 
 __device__ __forceinline__ sbh_u32x4v cld4u(const uint32_t* p) { return *(const SBH_CONSTANT sbh_u32x4v*)(uintptr_t)p; }
 
-// SOFT: the potential with eps > 0.
+// SOFT: the potential with eps^2 >= FLT_MIN.
 template <int D, int K, bool TRACE, bool CMP = false, bool SOFT = false>
 __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __restrict__ queries, int64_t nq,
                                                   SbhArgs a, int Q, float* __restrict__ out)
@@ -605,7 +606,8 @@ __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __re
                         for (int c = 0; c < D3; ++c) {
                             const float4 gd = (K == SBH_WINDING) ? gld4(bd + c) : zero4;
                             const float v = term_acc<K>(gld4(ba + c), gd, qx, qy, qz, kp, r0, sumc);
-                            // (an empty slot is all zeros: with eps > 0 its potential adds exactly nothing)
+                            // (an empty slot is all zeros: softened, its potential adds exactly nothing; a subnormal eps^2
+                            // softens nothing, the hardware's square root takes it for 0)
                             if constexpr (SOFT) sumc = v;
                             else sumc = count(c) ? v : sumc;
                         }
@@ -2728,7 +2730,7 @@ static hipError_t launch_sbh_dk(const TreeView& tv, const float* q, int64_t nq, 
         const int64_t waves = (nq + qpw - 1) / qpw;
         const unsigned blocks = (unsigned)((waves + 3) / 4);
         if (e.paths) k_sbh_pool<D, K, true><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
-        else if (K == SBH_POTENTIAL && a.eps2 > 0.0f)
+        else if (K == SBH_POTENTIAL && a.eps2 >= FLT_MIN)
             k_sbh_pool<D, K, false, false, K == SBH_POTENTIAL><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
         else k_sbh_pool<D, K, false><<<blocks, 256, 0, s>>>(tv, q, nq, a, qpw, out);
         return hipGetLastError();

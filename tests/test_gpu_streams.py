@@ -38,3 +38,19 @@ def test_same_values_for_any_pool(d, samples, kernel):
     for m in (33, 30001):   # streams are keyed by the query's index, so the first ones are the same
         part = P.sbh_eval(tree, q[:m].contiguous(), kernel, samples=samples, seed=3, group=1)
         assert torch.equal(whole[:m].view(torch.int32), part.view(torch.int32))
+
+
+@pytest.mark.parametrize("d", [2, 4])
+@pytest.mark.parametrize("eps", [1e-22, 1e-20, 1e-19, 1.08e-19, 1.2e-19])
+def test_softening_with_a_subnormal_square(d, eps):
+    """eps^2 below float32's smallest normal number (1.18e-38) is 0 to the hardware's square root: an empty
+    slot, at the origin like the query, still adds nothing, and the values are those of eps = 0."""
+    import paper_2506_02219_amd as P
+    rng = np.random.Generator(np.random.PCG64(11))
+    src = torch.from_numpy((rng.random((4000, 3)) + 0.5).astype(np.float32)).cuda()
+    q = np.zeros((70, 3), np.float32)
+    q[20:] = 1e-20 * rng.random((50, 3))
+    tree = P.sbh_build(src, torch.ones(4000, device="cuda"), branching=d)
+    got, want = (P.sbh_eval(tree, torch.from_numpy(q).cuda(), 0, samples=2, seed=7, group=1, eps=e) for e in (eps, 0.0))
+    assert torch.isfinite(want).all()
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
