@@ -391,9 +391,11 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ prm,
         for (int i = 0; i < 4; ++i) {
             const float pi = e[i] / s;
             const bool on = valid && cn[i] > 0.0f;
-            lp[i] = on && tg[i] > 0.0f ? logf(pi) : 0.0f;
+            const bool counts = on && tg[i] > 0.0f;
+            lp[i] = counts ? logf(pi) : 0.0f;
             dz[i] = on ? pi - tg[i] : 0.0f;
             dh[i] = (_Float16)dz[i];
+            if (!counts) tg[i] = 0.0f;   // (a target without a count may hold anything)
             loss -= tg[i] * lp[i];
         }
         loss = __shfl(loss, r, 64);

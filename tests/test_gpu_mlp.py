@@ -397,3 +397,25 @@ def test_non_finite_network_falls_back_to_the_score_proposal():
     zero = host(P.sbh_eval(gt, q, P.POTENTIAL, samples=2, seed=3, mlp=T(np.zeros(P.MLP_NPARAM, np.float32))))
     assert np.all(np.isfinite(a))
     assert np.array_equal(a, zero)
+
+
+def test_targets_without_a_count_are_not_read():
+    """Targets of empty slots, and of rows without a count, do not enter the loss or the gradient whatever
+    they hold (rows of memory that nobody wrote, for instance)."""
+    rng = np.random.Generator(np.random.PCG64(21))
+    n = 300
+    x = -rng.random((n, 8)).astype(np.float32)
+    c = rng.integers(0, 5, (n, 8)).astype(np.float32)
+    c[rng.random(n) < 0.3] = 0.0
+    t = np.where(c > 0, rng.random((n, 8)) + 0.1, 0.0)
+    t = (t / np.maximum(t.sum(1, keepdims=True), 1e-9)).astype(np.float32)
+    prm = (0.2 * rng.standard_normal(P.MLP_NPARAM)).astype(np.float32)
+    want = host(P.sbh_mlp_loss_grad(T(prm), T(x), T(t), T(c)))
+    assert np.isfinite(want).all() and want[1609] == (c.sum(1) > 0).sum()
+    for junk in (np.nan, np.inf, -np.inf):
+        got = host(P.sbh_mlp_loss_grad(T(prm), T(x), T(np.where(c > 0, t, junk).astype(np.float32)), T(c)))
+        assert np.array_equal(got.view(np.int32), want.view(np.int32)), junk
+        p, st, loss = T(prm), torch.zeros(2 * P.MLP_NPARAM, device=DEV), torch.zeros(1, device=DEV)
+        P.sbh_mlp_train(p, st, T(x), T(np.where(c > 0, t, junk).astype(np.float32)), T(c), steps=1, batch_rows=n,
+                        losses=loss)
+        assert float(loss[0]) == want[1608]
