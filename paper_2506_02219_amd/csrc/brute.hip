@@ -26,6 +26,7 @@
 // against the 3.9e13 lane operations a second of the chip.
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -73,6 +74,8 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
                                                          R alpha, R* __restrict__ out)
 {
     constexpr bool WN = K == SBH_WINDING, SM = K == SBH_SMOOTHDIST;
+    // (finite, so that a source at infinity weighs 0 beside it and a NaN stays one)
+    constexpr R kFar = std::is_same_v<R, double> ? R(DBL_MAX) : R(FLT_MAX);
     // Sources a loop iteration.  The float32 winding number issues faster one by one (5.5 against 6.7 ms
     // for 2^14 sources x 10^6 queries): unrolled, the compiler sends every term's comparison through
     // the one vcc register.
@@ -91,7 +94,7 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
         qy[u] = valid ? (R)queries[3 * j + 1] : R(0);
         qz[u] = valid ? (R)queries[3 * j + 2] : R(0);
         total[u] = R(0);
-        rmin[u] = R(INFINITY);
+        rmin[u] = kFar;
     }
     // the wavefront's next tile travels in registers while the current one is summed
     float gx = 0.f, gy = 0.f, gz = 0.f, gw = 0.f, hx = 0.f, hy = 0.f, hz = 0.f;
@@ -203,13 +206,13 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
     const int s = threadIdx.x;   // this thread's query of the workgroup
     const int64_t j = (int64_t)blockIdx.x * (64 * U) + s;
     if (j >= nq) return;
-    R sum = R(0), m = R(INFINITY);
+    R sum = R(0), m = kFar;
     if constexpr (SM) {
         for (int v = 0; v < kBruteWaves; ++v) m = pmin[v][s] < m ? pmin[v][s] : m;
     }
     for (int v = 0; v < kBruteWaves; ++v) {
         const R x = reinterpret_cast<const R*>(&tile[v][0])[s];
-        if constexpr (SM) sum += pmin[v][s] < R(INFINITY) ? x * exp(-alpha * (pmin[v][s] - m)) : R(0);
+        if constexpr (SM) sum += x * exp(-alpha * (pmin[v][s] - m));
         else sum += x;
     }
     if constexpr (WN) sum *= R(1.0 / (4.0 * M_PI));

@@ -80,3 +80,15 @@ def test_brute_unsoftened_and_non_finite(fp64):
         rest = np.r_[1:3, 5:70]
         assert (np.abs(got[rest] - val[rest]) <= tol[rest] * (2.0 ** -53 if fp64 else 2.0 ** -24)).all()
         assert np.isposinf(got[0]) if kernel == 0 else np.isfinite(got[0])
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("bad", [(64, 128), (0, 64), (100, 101), (0, 200)])
+def test_smooth_distance_of_nan_sources(bad, fp64):
+    """A NaN source makes every smooth distance NaN, also where all of a wavefront's sources are."""
+    import paper_2506_02219_amd as P
+    s, w, nm, q = _cloud(200, 70, 6)
+    s[bad[0]:bad[1], 1] = np.nan
+    dev = lambda a: torch.from_numpy(a).cuda()
+    got = P.sbh_brute(dev(s), dev(w), None, dev(q), 2, alpha=20.0, fp64=fp64).cpu().numpy()
+    assert np.isnan(got).all()
