@@ -26,6 +26,7 @@
 // against the 3.9e13 lane operations a second of the chip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -257,6 +258,7 @@ static hipError_t launch_brute_k(const float* src, const float* w, const float* 
 hipError_t launch_brute(const float* src, const float* w, const float* nrm, int64_t n, const float* queries,
                         int64_t nq, int kernel, float eps, float alpha, int fp64, void* out, hipStream_t s)
 {
+    alpha = std::min(alpha, FLT_MAX);   // (infinite: the distance to the nearest source, which infinity times 0 would lose)
 #define SBH_BRUTE(KK)                                                                                             \
     (fp64 ? launch_brute_k<KK, double>(src, w, nrm, n, queries, nq, (double)eps * (double)eps, (double)alpha, out, \
                                        s)                                                                         \

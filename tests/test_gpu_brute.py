@@ -92,3 +92,15 @@ def test_smooth_distance_of_nan_sources(bad, fp64):
     dev = lambda a: torch.from_numpy(a).cuda()
     got = P.sbh_brute(dev(s), dev(w), None, dev(q), 2, alpha=20.0, fp64=fp64).cpu().numpy()
     assert np.isnan(got).all()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("n", [1, 70, 1500])
+def test_smooth_distance_at_infinite_sharpness(n, fp64):
+    """alpha = infinity: the distance to the nearest source (three roundings)."""
+    import paper_2506_02219_amd as P
+    s, w, nm, q = _cloud(n, 70, 7)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    got = P.sbh_brute(dev(s), dev(w), None, dev(q), 2, alpha=np.inf, fp64=fp64).cpu().numpy().astype(np.float64)
+    r = np.sqrt(((s[None].astype(np.float64) - q[:, None].astype(np.float64)) ** 2).sum(-1)).min(1)
+    assert (np.abs(got - r) <= 4 * r * (2.0 ** -53 if fp64 else 2.0 ** -24)).all()
