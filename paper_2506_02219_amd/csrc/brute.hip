@@ -61,7 +61,14 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Z: the potential's eps is 0, so a source at the query gives an infinite term.
+__device__ __forceinline__ bool infinitely_far(float x, float y, float z)
+{
+    return (__builtin_isinf(x) || __builtin_isinf(y) || __builtin_isinf(z)) &&
+           !(__builtin_isnan(x) || __builtin_isnan(y) || __builtin_isnan(z));
+}
+
+// Z: the potential's eps is 0 or infinite, so that the squares under the root
+// reach 0 (a source at the query gives an infinite term) or infinity.
 // The smooth-distance sum is kept relative to the nearest source seen so far
 // (s = sum w exp(-alpha (r - rmin))), so that it neither underflows nor
 // overflows; the result is rmin - log(s) / alpha.  Sources are taken kSmGroup
@@ -81,6 +88,8 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
     // for 2^14 sources x 10^6 queries): unrolled, the compiler sends every term's comparison through
     // the one vcc register.
     constexpr int kUnroll = WN && std::is_same_v<R, float> ? 1 : 4;
+    // rsqrt64<false> takes no infinity: a source there adds its weight times 0 at a finite place instead
+    constexpr bool kNoInf = K == SBH_POTENTIAL && std::is_same_v<R, double> && !Z;
     __shared__ Vec4<R> tile[kBruteWaves][64];
     __shared__ Vec4<R> tdip[WN ? kBruteWaves : 1][WN ? 64 : 1];
     const int lane = threadIdx.x & 63;
@@ -118,6 +127,7 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
     for (; t0 < n; t0 += kStride) {
         // (the smooth distance takes whole groups of sources: lanes past the end hold one infinitely far away)
         if (SM && t0 + lane >= n) tile[wv][lane] = {R(INFINITY), R(0), R(0), R(0)};
+        else if (kNoInf && infinitely_far(gx, gy, gz)) tile[wv][lane] = {R(0), R(0), R(0), R(0) * (R)gw};
         else tile[wv][lane] = {(R)gx, (R)gy, (R)gz, (R)gw};
         if constexpr (WN) tdip[wv][lane] = {(R)gw * (R)hx, (R)gw * (R)hy, (R)gw * (R)hz, R(0)};
         load(t0 + kStride);
@@ -246,7 +256,7 @@ static hipError_t launch_brute_k(const float* src, const float* w, const float* 
                                  int64_t nq, R eps2, R alpha, void* out, hipStream_t s)
 {
     if constexpr (K == SBH_POTENTIAL && std::is_same_v<R, double>) {
-        if (eps2 == R(0)) {
+        if (eps2 == R(0) || eps2 == R(INFINITY)) {
             launch_brute_u<K, R, true>(src, w, nrm, n, q, nq, eps2, alpha, out, s);
             return hipGetLastError();
         }

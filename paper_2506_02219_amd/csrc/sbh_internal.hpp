@@ -168,7 +168,7 @@ constexpr float kInv4Pi = 0.0795774715459476679f;
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// x^(-1/2), x > 0 (Z: or x = 0, which gives infinity).  float64: the hardware
+// x^(-1/2), x > 0 and finite (Z: also 0, which gives infinity, and infinity, which gives 0).  float64: the hardware
 // approximation (relative error below 2^-20) and one third-order correction,
 // y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2, whose remainder is below 2^-60;
 // roundings leave about one unit in the last place, as a correctly rounded
@@ -178,7 +178,7 @@ __device__ __forceinline__ double rsqrt64(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
     double e = fma(-x * y, y, 1.0);
-    if constexpr (Z) e = fmin(e, 0.5);   // x = 0: y is infinite and e NaN, of which fmin keeps 0.5
+    if constexpr (Z) e = fmin(e, 0.5);   // x = 0 or infinity: e is NaN, of which fmin keeps 0.5, and y the value
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 // The evaluation code is compiled with floating-point contraction off and

@@ -104,3 +104,23 @@ def test_smooth_distance_at_infinite_sharpness(n, fp64):
     got = P.sbh_brute(dev(s), dev(w), None, dev(q), 2, alpha=np.inf, fp64=fp64).cpu().numpy().astype(np.float64)
     r = np.sqrt(((s[None].astype(np.float64) - q[:, None].astype(np.float64)) ** 2).sum(-1)).min(1)
     assert (np.abs(got - r) <= 4 * r * (2.0 ** -53 if fp64 else 2.0 ** -24)).all()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("eps", [0.0, 1e-3])
+def test_potential_of_infinitely_far_sources(eps, fp64):
+    """A source at infinity, and every source under an infinite softening, adds 0 to the potential."""
+    import paper_2506_02219_amd as P
+    s, w, nm, q = _cloud(300, 70, 8)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    near = np.ones(300, bool)
+    near[[5, 64, 130]] = False
+    s[5, 0], s[64], s[130, 2] = np.inf, -np.inf, -np.inf
+    got = P.sbh_brute(dev(s), dev(w), None, dev(q), 0, eps=eps, fp64=fp64).cpu().numpy().astype(np.float64)
+    val, tol = _reference(s[near], w[near], nm[near], q, 0, eps, 20.0)
+    fin = np.isfinite(val)   # (without softening a source at the query is infinite)
+    assert (np.abs(got[fin] - val[fin]) <= tol[fin] * (2.0 ** -53 if fp64 else 2.0 ** -24)).all()
+    assert np.isposinf(got[~fin]).all()
+    s[5, 1] = np.nan
+    assert np.isnan(P.sbh_brute(dev(s), dev(w), None, dev(q), 0, eps=eps, fp64=fp64).cpu().numpy()).all()
+    assert (P.sbh_brute(dev(s[near]), dev(w[near]), None, dev(q), 0, eps=np.inf, fp64=fp64).cpu().numpy() == 0.0).all()
