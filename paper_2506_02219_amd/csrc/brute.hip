@@ -26,7 +26,6 @@
 // against the 3.9e13 lane operations a second of the chip.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
@@ -82,6 +81,8 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
                                                          R alpha, R* __restrict__ out)
 {
     constexpr bool WN = K == SBH_WINDING, SM = K == SBH_SMOOTHDIST;
+    // (an infinite sharpness gives the distance to the nearest source, which infinity times 0 would lose)
+    const R sharp = alpha < R(FLT_MAX) ? alpha : R(FLT_MAX);
     // (finite, so that a source at infinity weighs 0 beside it and a NaN stays one)
     constexpr R kFar = std::is_same_v<R, double> ? R(DBL_MAX) : R(FLT_MAX);
     // Sources a loop iteration.  The float32 winding number issues faster one by one (5.5 against 6.7 ms
@@ -168,13 +169,13 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
 #pragma unroll
                     for (int i = 1; i < kSmGroup; ++i) m = fmin(m, r[i][u]);
                     if (m < rmin[u]) {   // a nearer source: the sums so far move to its distance
-                        const R f = exp(-alpha * (rmin[u] - m));
+                        const R f = exp(-sharp * (rmin[u] - m));
                         total[u] *= f;
                         acc[u] *= f;
                         rmin[u] = m;
                     }
 #pragma unroll
-                    for (int i = 0; i < kSmGroup; ++i) acc[u] = fma_r(pw[i], exp(-alpha * (r[i][u] - rmin[u])), acc[u]);
+                    for (int i = 0; i < kSmGroup; ++i) acc[u] = fma_r(pw[i], exp(-sharp * (r[i][u] - rmin[u])), acc[u]);
                 }
             }
         } else
@@ -223,7 +224,7 @@ __global__ void __launch_bounds__(kBruteThreads) k_brute(const float* __restrict
     }
     for (int v = 0; v < kBruteWaves; ++v) {
         const R x = reinterpret_cast<const R*>(&tile[v][0])[s];
-        if constexpr (SM) sum += x * exp(-alpha * (pmin[v][s] - m));
+        if constexpr (SM) sum += x * exp(-sharp * (pmin[v][s] - m));
         else sum += x;
     }
     if constexpr (WN) sum *= R(1.0 / (4.0 * M_PI));
@@ -268,7 +269,6 @@ static hipError_t launch_brute_k(const float* src, const float* w, const float* 
 hipError_t launch_brute(const float* src, const float* w, const float* nrm, int64_t n, const float* queries,
                         int64_t nq, int kernel, float eps, float alpha, int fp64, void* out, hipStream_t s)
 {
-    alpha = std::min(alpha, FLT_MAX);   // (infinite: the distance to the nearest source, which infinity times 0 would lose)
 #define SBH_BRUTE(KK)                                                                                             \
     (fp64 ? launch_brute_k<KK, double>(src, w, nrm, n, queries, nq, (double)eps * (double)eps, (double)alpha, out, \
                                        s)                                                                         \
