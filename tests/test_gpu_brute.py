@@ -124,3 +124,20 @@ def test_potential_of_infinitely_far_sources(eps, fp64):
     s[5, 1] = np.nan
     assert np.isnan(P.sbh_brute(dev(s), dev(w), None, dev(q), 0, eps=eps, fp64=fp64).cpu().numpy()).all()
     assert (P.sbh_brute(dev(s[near]), dev(w[near]), None, dev(q), 0, eps=np.inf, fp64=fp64).cpu().numpy() == 0.0).all()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("n,nq", [(64, 70001), (65, 100001), (500, 524289), (1500, 262145), (4161, 262145)])
+def test_same_values_for_any_number_of_wavefronts(n, nq, kernel, fp64):
+    """One, four and sixteen wavefronts share the sources, one to four queries a lane: a query's value is the
+    same bit for bit."""
+    import paper_2506_02219_amd as P
+    s, w, nm, q = _cloud(n, nq, n)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    src, qd = (dev(s), dev(w), dev(nm)), dev(q)
+    whole = P.sbh_brute(*src, qd, kernel, alpha=20.0, fp64=fp64)
+    as_int = torch.int64 if fp64 else torch.int32
+    for first, m in ((0, 130), (nq - 40000, 40000)):
+        part = P.sbh_brute(*src, qd[first:first + m].contiguous(), kernel, alpha=20.0, fp64=fp64)
+        assert torch.equal(whole[first:first + m].view(as_int), part.view(as_int))
