@@ -376,17 +376,26 @@ static hipError_t launch_brute_k(const float* src, const float* w, const float* 
     return hipGetLastError();
 }
 
+// (a launch holds at most 2^32 - 1 work-items along a dimension, and a query takes up to eight from 2^15 on)
+constexpr int64_t kBruteQueries = (int64_t)1 << 28;
+
 hipError_t launch_brute(const float* src, const float* w, const float* nrm, int64_t n, const float* queries,
                         int64_t nq, int kernel, float eps, float alpha, int fp64, void* out, hipStream_t s)
 {
-#define SBH_BRUTE(KK)                                                                                             \
-    (fp64 ? launch_brute_k<KK, double>(src, w, nrm, n, queries, nq, (double)eps * (double)eps, (double)alpha, out, \
-                                       s)                                                                         \
-          : launch_brute_k<KK, float>(src, w, nrm, n, queries, nq, eps * eps, alpha, out, s))
-    if (kernel == SBH_POTENTIAL) return SBH_BRUTE(SBH_POTENTIAL);
-    if (kernel == SBH_WINDING) return SBH_BRUTE(SBH_WINDING);
-    return SBH_BRUTE(SBH_SMOOTHDIST);
+    hipError_t e = hipSuccess;
+    for (int64_t j0 = 0; j0 < nq && e == hipSuccess; j0 += kBruteQueries) {
+        const float* q = queries + 3 * j0;
+        const int64_t m = nq - j0 < kBruteQueries ? nq - j0 : kBruteQueries;
+        void* o = (char*)out + j0 * (fp64 ? sizeof(double) : sizeof(float));
+#define SBH_BRUTE(KK)                                                                                     \
+    (fp64 ? launch_brute_k<KK, double>(src, w, nrm, n, q, m, (double)eps * (double)eps, (double)alpha, o, s) \
+          : launch_brute_k<KK, float>(src, w, nrm, n, q, m, eps * eps, alpha, o, s))
+        if (kernel == SBH_POTENTIAL) e = SBH_BRUTE(SBH_POTENTIAL);
+        else if (kernel == SBH_WINDING) e = SBH_BRUTE(SBH_WINDING);
+        else e = SBH_BRUTE(SBH_SMOOTHDIST);
 #undef SBH_BRUTE
+    }
+    return e;
 }
 
 }  // namespace sbh
