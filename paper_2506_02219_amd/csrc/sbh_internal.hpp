@@ -187,17 +187,18 @@ __device__ __forceinline__ double rsqrt64(double x)
 // give bit-identical results).
 __device__ __forceinline__ float norm2(float dx, float dy, float dz) { return fmaf(dz, dz, fmaf(dx, dx, dy * dy)); }
 
-// r2^(-3/2), at most the largest finite value it can take (where it would
-// overflow, and at r2 = 0, where the dipole's dot product is 0 and so the term).
+// r2^(-3/2) where that is finite; below, for |d| < 1.5e-13, a smaller value that
+// falls to 0 with r2: a source whose squared distance is 0 in float32 (the
+// query itself, and any other nearer than 1e-23) adds nothing.
 __device__ __forceinline__ float inv_cube(float r2)
 {
 #pragma clang fp contract(off)
-    const float inv = fminf(__builtin_amdgcn_rsqf(r2), 6.98e12f);
+    const float inv = fminf(__builtin_amdgcn_rsqf(r2), r2 * 3.4e38f);
     return inv * inv * inv;
 }
 
 // The winding number's terms and sums leave out its constant 1 / (4 pi), which
-// query_value puts in: they are linear in it, and a term takes 13 vector
+// query_value puts in: they are linear in it, and a term takes 14 vector
 // instructions so instead of 16.
 template <int K>
 __device__ __forceinline__ float term_r2(float4 a, float4 dp, float dx, float dy, float dz, float r2,

@@ -353,3 +353,26 @@ def test_deep_tree_paths_beyond_sixteen_steps(G, rr, proposal):
     print(st, "paths with >= 17 accepted steps:", deep)
     if rr == 1:   # no roulette: every path into the cluster runs to a one-point leaf
         assert deep > 0
+
+
+@pytest.mark.parametrize("d", [2, 4])
+def test_winding_number_where_a_square_underflows(d):
+    """A query so near a source that the square of their distance is 0 in float32 (|p - q| < 1e-23) sees that
+    source as one at its own place, which adds nothing: the value is the one at the source."""
+    rng = np.random.Generator(np.random.PCG64(3))
+    src = rng.standard_normal((3000, 3)).astype(np.float32)
+    nrm = (src / np.linalg.norm(src, axis=1, keepdims=True)).astype(np.float32)
+    src[77] = 0.0
+    src[78] = [0.0, 0.0, 2.0]
+    w = np.full(3000, 1e-3, np.float32)
+    near = np.array([1e-24, -2e-25, 3e-24], np.float32)
+    for nodes in (src, src[76:79]):   # a tree, and a root that is a leaf
+        m = len(nodes)
+        gt = P.sbh_build(T(nodes), T(w[:m]), T(nrm[:m] if m > 3 else nrm[76:79]), branching=d)
+        for kw in (dict(samples=2, group=64), dict(samples=2, group=64, rr_mode=3), dict(samples=2, group=1),
+                   dict(samples=2, group=64, subdomains=1, beta=0.5), dict(samples=0, beta=2.0),
+                   dict(samples=0, beta=math.inf)):
+            at, by = (host(P.sbh_eval(gt, T(np.tile(q, (64, 1))), P.WINDING, seed=5, **kw))
+                      for q in (np.zeros(3, np.float32), near))
+            assert np.isfinite(at).all() and np.abs(at).max() < 100.0
+            assert np.array_equal(at.view(np.int32), by.view(np.int32)), (m, kw)
