@@ -196,7 +196,7 @@ hipError_t block_alloc(void** p, size_t bytes, hipStream_t s)
     return hipSuccess;
 }
 
-// false: not one of the blocks
+// false: the caller frees it (not one of the blocks, or no longer)
 bool block_free(void* p, hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(g_blocks_mu);
@@ -204,6 +204,10 @@ bool block_free(void* p, hipStream_t s)
     if (it == g_live.end()) return false;
     Block b = it->second;
     g_live.erase(it);
+    if (capturing(s)) {   // a node of the graph frees it: an event would say nothing about the graph's launches
+        (void)hipEventDestroy(b.freed);
+        return false;
+    }
     b.stream = s;
     int dev = 0;
     const bool other = s == nullptr && hipGetDevice(&dev) == hipSuccess && dev != b.device;

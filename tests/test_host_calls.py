@@ -11,6 +11,35 @@ def lib(tmp_path_factory):
     return host_calls.stand_in(tmp_path_factory)
 
 
+HELD = r'''
+held = {}
+def follow(rows):
+    """Bytes that the library holds after these calls (in use and idle)."""
+    for r in rows:
+        if r[0] == "malloc": held[r[1]] = r[2]
+        if r[0] == "free": del held[r[1]]
+    return sum(held.values())
+'''
+
+
+def test_release_on_a_stream_under_capture(lib):
+    """A tree of before the capture, freed on the capturing stream: a node of the graph releases it, and no
+    later call is given its memory (a launch of the graph may still read it)."""
+    host_calls.run(lib, r'''
+t = build()
+slabs = [r[1] for r in of(log(), "malloc")]
+H.stand_in_capture(S1)
+assert L.sbh_free_async(t, S1) == 0
+rows = log()
+assert not of(rows, "record", "wait", "eventsync"), rows
+freed = [r[1] for r in of(rows, "free")]
+assert len(freed) == 3 and set(freed) <= set(slabs) and all(r[3] == S1.value for r in of(rows, "free")), rows
+H.stand_in_capture(C.c_void_p(-1))
+u = build()
+assert len(of(log(), "malloc")) == 3   # (the build's temporaries are idle blocks, its tree's arrays new ones)
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
