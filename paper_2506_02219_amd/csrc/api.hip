@@ -121,9 +121,10 @@ Allocator allocator_current()
 // whatever their release threshold: 2.5 of the 5 ms of a 2^22-point build with its release.)  A freed block carries an
 // event recorded on the stream it was freed on; it is taken again when that event has completed, or by
 // the same stream, which waits for it (so that streams gain no dependency on one another), and for at
-// most a quarter less than its size.  Idle blocks hold at most kIdleBytes, the oldest going back to the
-// device beyond that, and all of them go back when sbh_free or sbh_batch_free releases the last block in
-// use, or when an allocation fails.  One lock guards the lists; nothing but HIP calls is made under it.
+// most a quarter less than its size.  Idle blocks hold at most kIdleBytes: beyond that the oldest go back
+// to the device, in stream order and without waiting for the GPU (a larger block is not kept at all), and
+// all of them go back when sbh_free or sbh_batch_free releases the last block in use, or when an allocation
+// fails.  One lock guards the lists; nothing but HIP calls is made under it.
 constexpr size_t kIdleBytes = (size_t)2 << 30;
 struct Block {
     void* p;
@@ -138,18 +139,34 @@ std::unordered_map<void*, Block>& g_live = *new std::unordered_map<void*, Block>
 std::list<Block>& g_idle = *new std::list<Block>;   // oldest first
 size_t g_idle_bytes = 0;
 
-// back to the device once the work that uses the block is done; the lock is held
-void release_block(const Block& b)
+// back to the device in the order of s, after the work that uses the block and without waiting for it
+void release_block(const Block& b, hipStream_t s)
 {
-    (void)hipEventSynchronize(b.freed);
+    (void)hipStreamWaitEvent(s, b.freed, 0);
     (void)hipEventDestroy(b.freed);
-    (void)hipFreeAsync(b.p, nullptr);
+    (void)hipFreeAsync(b.p, s);
 }
 void release_idle()
 {
-    for (const Block& b : g_idle) release_block(b);
+    for (const Block& b : g_idle) release_block(b, nullptr);
     g_idle.clear();
     g_idle_bytes = 0;
+}
+
+// Idle blocks down to `most` bytes, the oldest first, those alone that s need not wait for: what was
+// freed on s or whose work is done.  The lock is held.
+void limit_idle(size_t most, int device, hipStream_t s)
+{
+    for (auto it = g_idle.begin(); g_idle_bytes > most && it != g_idle.end();) {
+        if (it->device != device || (it->stream != s && hipEventQuery(it->freed) != hipSuccess)) {
+            ++it;
+            continue;
+        }
+        release_block(*it, s);
+        g_idle_bytes -= it->bytes;
+        it = g_idle.erase(it);
+    }
+    (void)hipGetLastError();   // an event that has not completed leaves hipErrorNotReady
 }
 
 bool capturing(hipStream_t s)
@@ -204,7 +221,8 @@ bool block_free(void* p, hipStream_t s)
     if (it == g_live.end()) return false;
     Block b = it->second;
     g_live.erase(it);
-    if (capturing(s)) {   // a node of the graph frees it: an event would say nothing about the graph's launches
+    // a node of the graph frees it under capture (an event would say nothing about the graph's launches)
+    if (capturing(s) || b.bytes > kIdleBytes) {
         (void)hipEventDestroy(b.freed);
         return false;
     }
@@ -215,16 +233,12 @@ bool block_free(void* p, hipStream_t s)
     if (hipEventRecord(b.freed, s) == hipSuccess) {
         g_idle.push_back(b);
         g_idle_bytes += b.bytes;
+        limit_idle(kIdleBytes, b.device, s);
     } else {   // as an allocation without a block
         (void)hipEventDestroy(b.freed);
         (void)hipFreeAsync(p, s);
     }
     if (other) (void)hipSetDevice(dev);
-    while (g_idle_bytes > kIdleBytes) {
-        g_idle_bytes -= g_idle.front().bytes;
-        release_block(g_idle.front());
-        g_idle.pop_front();
-    }
     return true;
 }
 

@@ -40,6 +40,41 @@ assert len(of(log(), "malloc")) == 3   # (the build's temporaries are idle block
 ''')
 
 
+def test_release_never_waits(lib):
+    """Beyond the limit on idle memory, sbh_free_async returns memory in stream order instead of waiting."""
+    host_calls.run(lib, HELD + r'''
+levels((1, 1), (1 << 20, 1 << 17), (1 << 23, 0))
+trees = [build(1 << 24) for _ in range(8)]          # about 1.1 GB each
+follow(log())
+H.stand_in_events_done(0)                            # the GPU is busy with them
+for i, t in enumerate(trees):
+    s = S1 if i % 2 else S2
+    assert L.sbh_free_async(t, s) == 0
+    rows = log()
+    assert not of(rows, "eventsync", "streamsync", "devicesync"), rows
+    # what goes back was freed on this stream, or waited for by it
+    waits = set()
+    for r in of(rows, "wait", "free"):
+        assert r[3] == s.value, rows
+    total = follow(rows)
+assert total <= 2 * GIB, total
+''')
+
+
+def test_one_block_beyond_the_limit_leaves_the_others(lib):
+    host_calls.run(lib, HELD + r'''
+other = build()
+assert L.sbh_free_async(build(200000), S1) == 0
+follow(log())
+assert L.sbh_mlp_loss_grad(D, D, D, D, 1 << 28, S1, D) == 0   # a workspace of 27 GB
+rows = log()
+assert max(r[2] for r in of(rows, "malloc")) > 2 * GIB
+assert follow(rows) <= 2 * GIB and not of(rows, "eventsync", "streamsync", "devicesync")
+u = build(200000)
+assert not of(log(), "malloc")                       # the tree's blocks are there still
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
