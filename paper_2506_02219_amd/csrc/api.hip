@@ -116,6 +116,22 @@ Allocator allocator_current()
     return g_alloc;
 }
 
+// the calling thread's device, while in scope: the null stream is the current device's
+struct OnDevice {
+    int back = -1;
+    explicit OnDevice(int device)
+    {
+        int cur = device;
+        if (hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess) back = cur;
+    }
+    ~OnDevice()
+    {
+        if (back >= 0) (void)hipSetDevice(back);
+    }
+    OnDevice(const OnDevice&) = delete;
+    OnDevice& operator=(const OnDevice&) = delete;
+};
+
 // The default allocator: blocks of hipMallocAsync memory, kept when they are freed and handed out again
 // in stream order.  (The pools behind hipMallocAsync unmap what is freed while the device is idle,
 // whatever their release threshold: 2.5 of the 5 ms of a 2^22-point build with its release.)  A freed block carries an
@@ -142,6 +158,7 @@ size_t g_idle_bytes = 0;
 // back to the device in the order of s, after the work that uses the block and without waiting for it
 void release_block(const Block& b, hipStream_t s)
 {
+    const OnDevice dev(b.device);
     (void)hipStreamWaitEvent(s, b.freed, 0);
     (void)hipEventDestroy(b.freed);
     (void)hipFreeAsync(b.p, s);
@@ -226,10 +243,8 @@ bool block_free(void* p, hipStream_t s)
         (void)hipEventDestroy(b.freed);
         return false;
     }
+    const OnDevice dev(b.device);
     b.stream = s;
-    int dev = 0;
-    const bool other = s == nullptr && hipGetDevice(&dev) == hipSuccess && dev != b.device;
-    if (other) (void)hipSetDevice(b.device);   // the null stream of the block's device
     if (hipEventRecord(b.freed, s) == hipSuccess) {
         g_idle.push_back(b);
         g_idle_bytes += b.bytes;
@@ -238,7 +253,6 @@ bool block_free(void* p, hipStream_t s)
         (void)hipEventDestroy(b.freed);
         (void)hipFreeAsync(p, s);
     }
-    if (other) (void)hipSetDevice(dev);
     return true;
 }
 
@@ -277,10 +291,20 @@ void dev_free(const Allocator& a, void* p, size_t bytes, hipStream_t s)
 // with no block in use, what is idle goes back to the device
 void dev_trim()
 {
-    std::lock_guard<std::mutex> lk(g_blocks_mu);
-    if (!g_live.empty() || g_idle.empty()) return;
-    release_idle();
-    (void)hipStreamSynchronize(nullptr);   // unmaps what was released
+    std::list<Block> idle;
+    {
+        std::lock_guard<std::mutex> lk(g_blocks_mu);
+        if (!g_live.empty()) return;
+        idle.swap(g_idle);
+        g_idle_bytes = 0;
+    }
+    for (const Block& b : idle) release_block(b, nullptr);
+    while (!idle.empty()) {   // waiting for the null stream unmaps what was freed on it
+        const int device = idle.front().device;
+        const OnDevice dev(device);
+        (void)hipStreamSynchronize(nullptr);
+        idle.remove_if([&](const Block& b) { return b.device == device; });
+    }
 }
 
 }  // namespace sbh
@@ -546,8 +570,11 @@ sbh_status sbh_tree_export_quadrupole(const sbh_tree* tree, float* quad)
 sbh_status sbh_free(sbh_tree* tree)
 {
     if (!tree) return SBH_OK;
-    (void)hipDeviceSynchronize();
-    free_impl(&tree->impl, 0);
+    {
+        const sbh::OnDevice dev(tree->impl.device);
+        (void)hipDeviceSynchronize();
+        free_impl(&tree->impl, 0);
+    }
     delete tree;
     sbh::dev_trim();
     return SBH_OK;
@@ -996,8 +1023,11 @@ sbh_status sbh_batch_get_config(const sbh_batch* b, sbh_batch_config* cfg)
 sbh_status sbh_batch_free(sbh_batch* b)
 {
     if (!b) return SBH_OK;
-    (void)hipDeviceSynchronize();
-    batch_release(b);
+    {
+        const sbh::OnDevice dev(b->device);
+        (void)hipDeviceSynchronize();
+        batch_release(b);
+    }
     delete b;
     sbh::dev_trim();
     return SBH_OK;

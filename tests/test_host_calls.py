@@ -75,6 +75,23 @@ assert not of(log(), "malloc")                       # the tree's blocks are the
 ''')
 
 
+def test_memory_goes_back_on_its_own_device(lib):
+    host_calls.run(lib, HELD + r'''
+t, u = build(), build()
+follow(log())
+H.hipSetDevice(1)
+assert L.sbh_free(t) == 0 and L.sbh_free(u) == 0
+rows = log()
+assert follow(rows) == 0
+assert len(of(rows, "devicesync")) >= 2
+bad = [r for r in rows if r[0] in ("record", "wait", "free", "devicesync", "streamsync") and r[3] == 0 and r[4] != "dev0"]
+assert not bad, bad
+d = C.c_int(-1)
+H.hipGetDevice(C.byref(d))
+assert d.value == 1                                  # the caller's device again
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
