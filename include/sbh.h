@@ -163,9 +163,12 @@ typedef struct sbh_tree_desc {      /* host copy of a tree's sizes */
  *     `stream` is 0 and the library has waited for the device first).
  * The default (both NULL) takes memory with hipMallocAsync on the call's
  * stream and keeps what is freed for later calls, handed out again in stream
- * order: at most 2 GiB per process, all of it returned when sbh_free or
- * sbh_batch_free releases the last object that uses it.  A PyTorch caller can
- * pass its caching allocator here.
+ * order: at most 2 GiB per process.  All of it is returned when sbh_free or
+ * sbh_batch_free releases the last object that uses it, and by
+ * sbh_set_allocator, also when that sets what is set already; it stays after
+ * sbh_free_async, for the next build.  With no tree or plan left, a call that
+ * only needed a workspace and a build that failed leave at most 64 MiB.  A
+ * PyTorch caller can pass its caching allocator here.
  */
 typedef void* (*sbh_alloc_fn)(size_t bytes, hipStream_t stream, void* ctx);
 typedef void (*sbh_free_fn)(void* ptr, size_t bytes, hipStream_t stream, void* ctx);
@@ -174,7 +177,8 @@ typedef void (*sbh_free_fn)(void* ptr, size_t bytes, hipStream_t stream, void* c
  * sbh_set_allocator - set the allocator of later allocations (process-wide).
  * Objects keep the allocator they were created with and release through it,
  * so a change does not affect trees or plans that exist.  Both NULL restores
- * the default.  Call it while no other thread is inside the library.
+ * the default.  The memory that the default allocator holds unused is returned
+ * to the device.  Call it while no other thread is inside the library.
  * Errors: SBH_EINVAL (exactly one of alloc and free NULL).
  */
 sbh_status sbh_set_allocator(sbh_alloc_fn alloc, sbh_free_fn free, void* ctx);

@@ -139,9 +139,13 @@ struct OnDevice {
 // the same stream, which waits for it (so that streams gain no dependency on one another), and for at
 // most a quarter less than its size.  Idle blocks hold at most kIdleBytes: beyond that the oldest go back
 // to the device, in stream order and without waiting for the GPU (a larger block is not kept at all), and
-// all of them go back when sbh_free or sbh_batch_free releases the last block in use, or when an allocation
-// fails.  One lock guards the lists; nothing but HIP calls is made under it.
+// all of them go back when sbh_free or sbh_batch_free releases the last block in use, when the allocator is
+// set, or when an allocation fails; where no object is left, the training calls and a failed build keep
+// kKeptBytes at most (a batch of 8,192 rows takes 0.8 MB).  (sbh_free_async of the last tree leaves them: a
+// loop of builds would otherwise pay for their mapping each time.)  One lock guards the lists; nothing but
+// HIP calls is made under it.
 constexpr size_t kIdleBytes = (size_t)2 << 30;
+constexpr size_t kKeptBytes = (size_t)64 << 20;
 struct Block {
     void* p;
     size_t bytes;
@@ -288,13 +292,13 @@ void dev_free(const Allocator& a, void* p, size_t bytes, hipStream_t s)
     if (!mine) (void)hipFreeAsync(p, s);
 }
 
-// with no block in use, what is idle goes back to the device
-void dev_trim()
+// what is idle goes back to the device (unless_used: with no block in use)
+void dev_trim(bool unless_used)
 {
     std::list<Block> idle;
     {
         std::lock_guard<std::mutex> lk(g_blocks_mu);
-        if (!g_live.empty()) return;
+        if (unless_used && !g_live.empty()) return;
         idle.swap(g_idle);
         g_idle_bytes = 0;
     }
@@ -307,6 +311,15 @@ void dev_trim()
     }
 }
 
+// At the end of a call that leaves no object behind: with no block in use, kKeptBytes stay idle.
+void dev_settle(hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    int device = 0;
+    if (g_idle_bytes <= kKeptBytes || !g_live.empty() || capturing(s) || hipGetDevice(&device) != hipSuccess) return;
+    limit_idle(kKeptBytes, device, s);
+}
+
 }  // namespace sbh
 
 extern "C" {
@@ -317,6 +330,7 @@ sbh_status sbh_set_allocator(sbh_alloc_fn alloc, sbh_free_fn free, void* ctx)
         return fail(SBH_EINVAL, "sbh_set_allocator: give both functions or neither");
     std::lock_guard<std::mutex> lk(g_alloc_mu);
     g_alloc = sbh::Allocator{alloc, free, alloc ? ctx : nullptr};
+    sbh::dev_trim(false);
     return SBH_OK;
 }
 
@@ -396,6 +410,7 @@ sbh_status sbh_build(const float* sources, const float* weights, const float* no
         (void)hipStreamSynchronize(stream);
         free_impl(&t->impl, stream);
         delete t;
+        sbh::dev_settle(stream);
         return fail(st, "sbh_build: %s", msg.c_str());
     }
     *out_tree = t;
@@ -576,7 +591,7 @@ sbh_status sbh_free(sbh_tree* tree)
         free_impl(&tree->impl, 0);
     }
     delete tree;
-    sbh::dev_trim();
+    sbh::dev_trim(true);
     return SBH_OK;
 }
 
@@ -645,6 +660,7 @@ sbh_status sbh_mlp_loss_grad(const float* params, const float* features, const f
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_loss_grad: workspace");
     e = sbh::launch_mlp_grad(params, features, targets, counts, n, 0, n, partial, grad, stream);
     sbh::dev_free(mem, partial, wbytes, stream);
+    sbh::dev_settle(stream);
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_loss_grad: kernel launch");
     return SBH_OK;
 }
@@ -674,6 +690,7 @@ sbh_status sbh_mlp_train(float* params, float* adam_state, const float* features
                                  losses ? losses + s : nullptr, stream);
     }
     sbh::dev_free(mem, work, wbytes, stream);
+    sbh::dev_settle(stream);
     if (e != hipSuccess) return hip_fail(e, "sbh_mlp_train: kernel launch");
     return SBH_OK;
 }
@@ -1029,7 +1046,7 @@ sbh_status sbh_batch_free(sbh_batch* b)
         batch_release(b);
     }
     delete b;
-    sbh::dev_trim();
+    sbh::dev_trim(true);
     return SBH_OK;
 }
 

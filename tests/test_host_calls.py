@@ -92,6 +92,49 @@ assert d.value == 1                                  # the caller's device again
 ''')
 
 
+def test_memory_goes_back(lib):
+    host_calls.run(lib, HELD + r'''
+KEEP = 64 << 20
+# a training call without a tree: its workspace of 1.7 GB is not kept
+assert L.sbh_mlp_train(D, D, D, D, D, 1 << 24, 1, 1 << 24, 1e-3, 0, S1, None) == 0
+rows = log()
+assert follow(rows) <= KEEP and not of(rows, "eventsync", "streamsync", "devicesync"), rows
+assert L.sbh_mlp_loss_grad(D, D, D, D, 1 << 24, S1, D) == 0
+assert follow(log()) <= KEEP
+# a small one is: no allocation the second time
+assert L.sbh_mlp_train(D, D, D, D, D, 8192, 1, 8192, 1e-3, 0, S1, None) == 0
+follow(log())
+assert L.sbh_mlp_train(D, D, D, D, D, 8192, 1, 8192, 1e-3, 0, S1, None) == 0
+assert not of(log(), "malloc")
+# nor what a build that failed had taken
+H.stand_in_refuse(1000)
+h = C.c_void_p()
+assert L.sbh_build(D, D, None, 1 << 22, None, S1, C.byref(h)) == -2
+H.stand_in_refuse(0)
+assert follow(log()) <= KEEP
+raw = struct.pack("8f44I", 0, 0, 0, 1, 1, 1, 0, 0, *[0] * 44)   # not finite
+H.stand_in_info(raw, len(raw))
+assert L.sbh_build(D, D, None, 1 << 22, None, S1, C.byref(h)) == -1
+assert follow(log()) <= KEEP
+# a loop of builds allocates once
+levels((1, 1), (8, 0))
+for i in range(3):
+    assert L.sbh_free_async(build(1 << 20), S1) == 0
+    rows = log()
+    follow(rows)
+    assert i == 0 or not of(rows, "malloc"), rows
+assert sum(held.values()) > KEEP
+# what it leaves goes back when the allocator is set, also to the one it is
+assert L.sbh_set_allocator(None, None, None) == 0
+assert follow(log()) == 0
+# or with the last tree that is freed
+t, u = build(1 << 20), build(1 << 20)
+follow(log())
+assert L.sbh_free_async(t, S1) == 0 and L.sbh_free(u) == 0
+assert follow(log()) == 0
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
