@@ -167,13 +167,6 @@ void release_block(const Block& b, hipStream_t s)
     (void)hipEventDestroy(b.freed);
     (void)hipFreeAsync(b.p, s);
 }
-void release_idle()
-{
-    for (const Block& b : g_idle) release_block(b, nullptr);
-    g_idle.clear();
-    g_idle_bytes = 0;
-}
-
 // Idle blocks down to `most` bytes, the oldest first, those alone that s need not wait for: what was
 // freed on s or whose work is done.  The lock is held.
 void limit_idle(size_t most, int device, hipStream_t s)
@@ -204,7 +197,7 @@ hipError_t block_alloc(void** p, size_t bytes, hipStream_t s)
     // a few sizes per factor of two, so that trees of about the same size share blocks
     const size_t unit = bytes >= ((size_t)16 << 20) ? (size_t)2 << 20 : bytes >= ((size_t)1 << 20) ? (size_t)256 << 10 : 4096;
     bytes = (bytes + unit - 1) / unit * unit;
-    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    std::unique_lock<std::mutex> lk(g_blocks_mu);
     auto best = g_idle.end();
     for (auto it = g_idle.begin(); it != g_idle.end(); ++it) {
         if (it->device != dev || it->bytes < bytes || it->bytes - bytes > it->bytes / 4) continue;
@@ -221,11 +214,20 @@ hipError_t block_alloc(void** p, size_t bytes, hipStream_t s)
     }
     Block b{nullptr, bytes, dev, nullptr, s};
     e = hipMallocAsync(&b.p, bytes, s);
-    if (e != hipSuccess && !g_idle.empty()) {
+    if (e != hipSuccess && !g_idle.empty()) {   // once more with the device's idle memory, for which s waits
         (void)hipGetLastError();
-        release_idle();
-        (void)hipStreamSynchronize(nullptr);
+        std::list<Block> idle;
+        for (auto it = g_idle.begin(); it != g_idle.end();) {
+            const auto at = it++;
+            if (at->device != dev) continue;
+            g_idle_bytes -= at->bytes;
+            idle.splice(idle.end(), g_idle, at);
+        }
+        lk.unlock();
+        for (const Block& i : idle) release_block(i, s);
+        (void)hipStreamSynchronize(s);
         e = hipMallocAsync(&b.p, bytes, s);
+        lk.lock();
     }
     if (e != hipSuccess) return e;
     *p = b.p;

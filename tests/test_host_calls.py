@@ -135,6 +135,22 @@ assert follow(log()) == 0
 ''')
 
 
+def test_idle_memory_is_used_before_an_allocation_fails(lib):
+    host_calls.run(lib, HELD + r'''
+assert L.sbh_free_async(build(1 << 20), S1) == 0
+follow(log())
+assert sum(held.values()) > 0
+before = set(held)
+H.stand_in_events_done(0)
+H.stand_in_refuse(1)
+t = build(1 << 22, stream=S2)
+rows = log()
+follow(rows)
+assert not before & set(held)                        # all of it went back, and the build went on
+assert all(r[3] == S2.value for r in of(rows, "free", "streamsync", "wait")) and not of(rows, "eventsync", "devicesync")
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
