@@ -2799,7 +2799,9 @@ static hipError_t launch_bh_dk(const TreeView& tv, const float* q, int64_t nq, c
     BhArgs a{e.beta, e.eps * e.eps, e.alpha};
     constexpr int W = D == 2 ? 4 : 2;
     const int64_t tiles = (nq + 63) / 64;
-    switch (bh_waves<D>(tiles, e.beta, tv.n_points)) {
+    int waves = bh_waves<D>(tiles, e.beta, tv.n_points);
+    while (tiles * 64 * waves > UINT32_MAX) waves /= 2;   // (a launch's limit of work-items; the values are the same)
+    switch (waves) {
     case 1: launch_bh_pw<D, K, W, 1>(tv, q, nq, (unsigned)tiles, a, out, s); break;
     case 2: launch_bh_pw<D, K, W, 2>(tv, q, nq, (unsigned)tiles, a, out, s); break;
     default: launch_bh_pw<D, K, W, W>(tv, q, nq, (unsigned)tiles, a, out, s); break;

@@ -151,6 +151,20 @@ assert all(r[3] == S2.value for r in of(rows, "free", "streamsync", "wait")) and
 ''')
 
 
+def test_barnes_hut_launches(lib):
+    host_calls.run(lib, r'''
+for d in (2, 4):
+    t = build(5000, branching=d, normals=True)
+    for nq in (1, 1 << 16, (1 << 18) + 1, (1 << 30) - 1, 1 << 30, (1 << 31) - 65, (1 << 31) - 1):
+        for beta in (0.1, 0.3, 0.5, 2.0, 1e9):
+            for kernel in (0, 1, 2):
+                log()
+                assert L.sbh_eval(t, D, nq, kernel, beta, 0, 0, None, S1, D) == 0, (d, nq, beta, L.sbh_last_error())
+                rows = of(log(), "launch")
+                assert len(rows) == 1 and rows[0][2] % ((nq + 63) // 64 * 64) == 0, rows
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
