@@ -24,6 +24,7 @@
 // fragment: inference needs no LDS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "sbh_internal.hpp"
@@ -1364,12 +1365,19 @@ hipError_t launch_mlp_pairs(const sbh_tree_impl* t, const float* queries, int64_
                                                                    (uint32_t)(seed >> 32), X, Cn, loc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned paths = (unsigned)(nq * 8);   // (lmax <= the tree's max_level <= kTgMaxRows)
+    // (lmax <= the tree's max_level <= kTgMaxRows; a launch holds at most 2^32 - 1 work-items along a dimension)
     const double eps2 = (double)eps * (double)eps;
-    if (kernel == SBH_POTENTIAL && eps2 > 0.0) k_mlp_targets<SBH_POTENTIAL, true><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
-    else if (kernel == SBH_POTENTIAL) k_mlp_targets<SBH_POTENTIAL, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
-    else if (kernel == SBH_WINDING) k_mlp_targets<SBH_WINDING, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
-    else k_mlp_targets<SBH_SMOOTHDIST, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, queries, lmax, loc, eps2, alpha, Tg);
+    constexpr int64_t kPaths = (int64_t)1 << 22;
+    for (int64_t p0 = 0; p0 < nq * 8; p0 += kPaths) {
+        const unsigned paths = (unsigned)std::min<int64_t>(nq * 8 - p0, kPaths);
+        const float* q = queries + 3 * (p0 / 8);
+        const int4* l = loc + p0 * lmax;
+        float* t = Tg + 8 * p0 * lmax;
+        if (kernel == SBH_POTENTIAL && eps2 > 0.0) k_mlp_targets<SBH_POTENTIAL, true><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+        else if (kernel == SBH_POTENTIAL) k_mlp_targets<SBH_POTENTIAL, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+        else if (kernel == SBH_WINDING) k_mlp_targets<SBH_WINDING, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+        else k_mlp_targets<SBH_SMOOTHDIST, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+    }
     return hipGetLastError();
 }
 
