@@ -1329,12 +1329,17 @@ hipError_t launch_mlp_forward(const float* prm, const float* x, int64_t n, float
 
 size_t mlp_partial_floats(int64_t rows) { return (size_t)((rows + 63) / 64) * kGradStride; }
 
+// the partial gradients of the rows' groups of 64; returns their number
 static int launch_mlp_partial(const float* prm, const float* X, const float* Tg, const float* Cn, int64_t n,
                               int64_t row_begin, int64_t rows, float* partial, hipStream_t s)
 {
-    const int nb = (int)((rows + 63) / 64);
-    k_mlp_grad<<<nb, 256, 0, s>>>(prm, X, Tg, Cn, n, row_begin, rows, partial);
-    return nb;
+    constexpr int64_t kRows = (int64_t)1 << 28;   // (four work-items a row, of 2^32 - 1 that a launch holds)
+    for (int64_t r0 = 0; r0 < rows; r0 += kRows) {
+        const int64_t m = std::min(rows - r0, kRows);
+        k_mlp_grad<<<(unsigned)((m + 63) / 64), 256, 0, s>>>(prm, X, Tg, Cn, n, row_begin + r0, m,
+                                                             partial + r0 / 64 * kGradStride);
+    }
+    return (int)((rows + 63) / 64);
 }
 
 hipError_t launch_mlp_grad(const float* prm, const float* X, const float* Tg, const float* Cn, int64_t n,

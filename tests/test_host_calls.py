@@ -186,6 +186,24 @@ for nq, depth in ((5, 3), ((1 << 20) - 1, 1), (1 << 20, 1), (1 << 21, 1), ((1 <<
 ''')
 
 
+def test_gradient_launches(lib):
+    host_calls.run(lib, r'''
+H.stand_in_copy_args(8, 256)
+for n in (1, 64, 65, (1 << 30) - 64, 1 << 30, (1 << 31) - 1):
+    log()
+    assert L.sbh_mlp_loss_grad(D, D, D, D, n, S1, D) == 0, (n, L.sbh_last_error())
+    rows = of(log(False), "launch")
+    first, part = 0, H.stand_in_arg(7)
+    for i, r in enumerate(rows[:-1]):          # (the last one adds the partial gradients)
+        a = [H.stand_in_arg(8 * i + k) for k in range(8)]
+        assert a[4] == n and a[5] == first and a[7] == part + first // 64 * 1616 * 4
+        assert r[2] // 256 == (min(a[6], n - first) + 63) // 64
+        first += a[6]
+        assert first == n or first % 64 == 0
+    assert first == n
+''')
+
+
 def test_brute_force_launches(lib):
     host_calls.run(lib, r'''
 H.stand_in_copy_args(9, 0)
