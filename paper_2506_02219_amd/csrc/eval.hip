@@ -2176,8 +2176,9 @@ constexpr int bh_stack_depth()
     return D == 2 ? (8 - 1) * 20 + 2 : (64 - 1) * 10 + 2;
 }
 
-// One tile of 64 consecutive queries per workgroup, whose opened nodes are
-// shared by W parts: level by level, the blocks to open are listed in LDS,
+// One tile of 64 consecutive queries per workgroup (with PW = 1 TPB tiles, a
+// wavefront each), whose opened nodes are shared by W parts: level by level, the
+// blocks to open are listed in LDS,
 // entry f goes to part f mod W, and each part lists the children it finds near;
 // a part whose share of the next list is full walks the child depth-first
 // instead, on its wavefront's stack (always wavefront-uniform).  The parts' sums
@@ -2198,8 +2199,8 @@ constexpr int bh_stack_depth()
 // 3105 -> 1211 (1306 with four), at beta = 0.5 302 -> 132 (182).
 constexpr int kBhList = 64;   // entries of a wavefront's part of a list
 
-template <int D, int K, bool O64, int W, int PW>
-__global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
+template <int D, int K, bool O64, int W, int PW, int TPB>
+__global__ void __launch_bounds__(64 * PW * TPB) k_bh(TreeView tv, const float* __restrict__ queries, int64_t nq, BhArgs a,
                                                float* __restrict__ out)
 {
 #pragma clang fp contract(off)
@@ -2209,13 +2210,29 @@ __global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __rest
     constexpr int MAXS = bh_stack_depth<D>();
     // an entry is a child block to open: {block id, first point} and, apart, the level of its
     // node (block ids take all 32 bits; levels are below 64)
-    __shared__ int2 stack[PW][MAXS];
-    __shared__ uint8_t stack_lvl[PW][MAXS];
-    __shared__ int2 list[2][W][kBhList];   // the level's blocks and the next level's
+    __shared__ int2 stacks[TPB][PW][MAXS];
+    __shared__ uint8_t stack_lvls[TPB][PW][MAXS];
+    __shared__ int2 lists[TPB][2][W][kBhList];   // the level's blocks and the next level's
     __shared__ int n_list[2][W];
-    __shared__ float part[PW > 1 ? W : 1][64];
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    __shared__ float parts[TPB][PW > 1 ? W : 1][64];
+    static_assert(PW == 1 || TPB == 1, "several tiles a workgroup: a wavefront each");
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wv = PW == 1 ? 0 : w, tw = PW == 1 ? w : 0;
+    int2 (&stack)[PW][MAXS] = stacks[tw];
+    uint8_t (&stack_lvl)[PW][MAXS] = stack_lvls[tw];
+    int2 (&list)[2][W][kBhList] = lists[tw];
+    float (&part)[PW > 1 ? W : 1][64] = parts[tw];
+    const int64_t j = ((int64_t)blockIdx.x * TPB + tw) * 64 + lane;
+    if (PW == 1 && j - lane >= nq) return;
+    auto sync = [] {   // the tile's wavefronts
+        if constexpr (PW > 1) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    };
     const bool valid = j < nq;
     float qx = 0.f, qy = 0.f, qz = 0.f;
     if (valid) {
@@ -2250,7 +2267,7 @@ __global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __rest
         listed[i] = 0;
     }
     if (PW > 1 && threadIdx.x < W) n_list[0][threadIdx.x] = 0;
-    __syncthreads();
+    sync();
     if constexpr (K == SBH_SMOOTHDIST) r0 = part[0][lane];
     // root: accepted when every lane passes the far-field test
     {
@@ -2263,13 +2280,13 @@ __global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __rest
                 for (int i = 0; i < tv.n_points; ++i)
                     accs[0] = term_acc<K>(cld4(tv.pts + i), (K == SBH_WINDING) ? cld4(tv.pdip + i) : zero4, qx, qy, qz, kp,
                                           r0, accs[0]);
-        } else if (threadIdx.x == 0) {
+        } else if (wv == 0 && lane == 0) {
             list[0][0][0] = make_int2(0, 0);   // block 0, first point 0
             if (PW > 1) n_list[0][0] = 1;
         }
         if (PW == 1 && tv.root_internal && __ballot(!(norm2(dx, dy, dz) >= limit2(tv.diam0))) != 0ull) listed[0] = 1;
     }
-    __syncthreads();
+    sync();
     int cur = 0;
     for (int depth = 0;; ++depth) {
         int cum[W + 1];   // the level's entries by wavefront that listed them
@@ -2413,7 +2430,7 @@ __global__ void __launch_bounds__(64 * PW) k_bh(TreeView tv, const float* __rest
             for (int i = 0; i < R; ++i)
                 if (lane == 0) n_list[cur ^ 1][wv + i * PW] = listed[i];
         }
-        __syncthreads();
+        sync();
         cur ^= 1;
     }
     float acc = accs[0];
@@ -2764,32 +2781,43 @@ static hipError_t launch_cut_dk(const TreeView& tv, const float* q, int64_t nq, 
 // wavefront slots empty, which it does up to some 1,024 tiles, and where tiles
 // are so unequal that the last ones set its time: at a large beta.  Where a
 // launch of many tiles opens few nodes in each, wavefronts that wait for one
-// another cost more than they save.  10^6 queries (15,625 tiles) in pixel order,
-// d = 2, us with one / two / four: 2^22 surface samples, winding, beta 0.2
-// 14.8 / 15.2 / 16.9, 0.5 125 / 89 / 86, 1 374 / 262 / 222; 2^16 samples, smooth
-// distance, 0.2 27 / 33 / 53, 0.5 71 / 67 / 89, 1 212 / 173 / 180.  200,000
-// queries on 2^22 samples, smooth distance, 0.2 16 / 16 / 21, 0.5 140 / 82 / 55.
-// d = 4, two parts: 10^6 on 2^16 samples, smooth distance, 0.2 79 / 110, 1 409 /
-// 381; winding, 0.2 20 / 26, 1 265 / 232.
-template <int D>
+// another cost more than they save, most of all on a tree of a few nodes.
+// us with one / two / four wavefronts, d = 2.  10^6 queries (15,625 tiles) in
+// pixel order: 2^22 surface samples, winding, beta 0.2 14.8 / 15.2 / 16.9, 0.5
+// 125 / 89 / 86, 1 374 / 262 / 222; 2^16 samples, smooth distance, 0.2 27 / 33 / 53,
+// 0.5 71 / 67 / 89, 1 212 / 173 / 180.  10^6 in a box, winding: 20 sources, 0.5
+// 12 / 17 / 28, 2 16 / 21 / 34; 100, 0.5 27 / 31 / 41, 2 63 / 63 / 73; 1,000, 0.3 12 /
+// 14 / 21, 2 334 / 305 / 322; 4,000, 0.2 18 / 17 / 21, 2 680 / 620 / 632; 2^16, 0.2
+// 22 / 20 / 23, 1 533 / 433 / 405; 2^18 in any order, 0.1 11 / 13 / 19.  200,000
+// (3,125 tiles) in a box, winding: 100 sources, 1 16 / 13 / 15; 16,000, 0.2 19 / 14 /
+// 11, 1 206 / 115 / 89; smooth distance on 2^22 samples, 0.2 16 / 16 / 21, 0.5 140 /
+// 82 / 55.  d = 4, two parts, 10^6: smooth distance on 2^16 samples, pixel order, 0.2
+// 79 / 110, 1 409 / 381; winding in a box, 100 sources 61 / 85 at 2, 2^16 44 / 49 at
+// 0.2, 99 / 102 at 0.3, 278 / 246 at 0.5; 200,000 on 2^16 samples, 0.1 20 / 18.
+constexpr int64_t kFewPoints = 256;
+template <int D, int K>
 static int bh_waves(int64_t tiles, float beta, int64_t n)
 {
-    const bool many = tiles > 4096;
+    constexpr bool SM = K == SBH_SMOOTHDIST;
+    const bool many = tiles > 4096, few_nodes = n < kFewPoints;
     if (tiles <= 1024) return D == 2 ? 4 : 2;
     if (D == 2) {
-        if (beta < 0.4f) return many ? 1 : 2;
-        const float four = n < (1 << 14) ? 1.5f : n < (1 << 17) ? 1.0f : 0.6f;
-        return many && beta < four ? 2 : 4;
+        if (few_nodes) return many ? 1 : 2;
+        if (!many) return SM && beta < 0.4f ? 2 : 4;
+        if (beta < (n < (1 << 12) ? 0.6f : SM ? 0.4f : 0.15f)) return 1;
+        return n >= (1 << 14) && beta >= (n < (1 << 17) ? 1.0f : 0.6f) ? 4 : 2;
     }
-    return beta < (!many ? 0.15f : n < (1 << 17) ? 0.6f : 0.25f) ? 1 : 2;
+    if (few_nodes) return 1;
+    return beta < (many ? (n < (1 << 17) ? 0.4f : 0.25f) : SM ? 0.15f : 0.0f) ? 1 : 2;
 }
 
-template <int D, int K, int W, int PW>
-static void launch_bh_pw(const TreeView& tv, const float* q, int64_t nq, unsigned tiles, const BhArgs& a, float* out,
+template <int D, int K, int W, int PW, int TPB>
+static void launch_bh_pw(const TreeView& tv, const float* q, int64_t nq, int64_t tiles, const BhArgs& a, float* out,
                          hipStream_t s)
 {
-    if (tv.wide) k_bh<D, K, true, W, PW><<<tiles, 64 * PW, 0, s>>>(tv, q, nq, a, out);
-    else k_bh<D, K, false, W, PW><<<tiles, 64 * PW, 0, s>>>(tv, q, nq, a, out);
+    const unsigned blocks = (unsigned)((tiles + TPB - 1) / TPB);
+    if (tv.wide) k_bh<D, K, true, W, PW, TPB><<<blocks, 64 * PW * TPB, 0, s>>>(tv, q, nq, a, out);
+    else k_bh<D, K, false, W, PW, TPB><<<blocks, 64 * PW * TPB, 0, s>>>(tv, q, nq, a, out);
 }
 
 template <int D, int K>
@@ -2799,12 +2827,18 @@ static hipError_t launch_bh_dk(const TreeView& tv, const float* q, int64_t nq, c
     BhArgs a{e.beta, e.eps * e.eps, e.alpha};
     constexpr int W = D == 2 ? 4 : 2;
     const int64_t tiles = (nq + 63) / 64;
-    int waves = bh_waves<D>(tiles, e.beta, tv.n_points);
+    int waves = bh_waves<D, K>(tiles, e.beta, tv.n_points);
     while (tiles * 64 * waves > UINT32_MAX) waves /= 2;   // (a launch's limit of work-items; the values are the same)
     switch (waves) {
-    case 1: launch_bh_pw<D, K, W, 1>(tv, q, nq, (unsigned)tiles, a, out, s); break;
-    case 2: launch_bh_pw<D, K, W, 2>(tv, q, nq, (unsigned)tiles, a, out, s); break;
-    default: launch_bh_pw<D, K, W, W>(tv, q, nq, (unsigned)tiles, a, out, s); break;
+    case 1:
+        // four tiles a workgroup where a tile is little more than its dispatch: us for 10^6 queries with one / four,
+        // smooth distance at beta 0.1 13.5 / 13.3 on 20 sources, 47.5 / 45.6 on 1,000 with d = 4; winding on 100 at
+        // beta 2 72 / 69; but winding on 2^18 at 0.5 403 / 423
+        if (K == SBH_SMOOTHDIST || tv.n_points < kFewPoints) launch_bh_pw<D, K, W, 1, 4>(tv, q, nq, tiles, a, out, s);
+        else launch_bh_pw<D, K, W, 1, 1>(tv, q, nq, tiles, a, out, s);
+        break;
+    case 2: launch_bh_pw<D, K, W, 2, 1>(tv, q, nq, tiles, a, out, s); break;
+    default: launch_bh_pw<D, K, W, W, 1>(tv, q, nq, tiles, a, out, s); break;
     }
     return hipGetLastError();
 }
