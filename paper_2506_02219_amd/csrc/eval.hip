@@ -318,11 +318,6 @@ __device__ __forceinline__ float unit24(uint32_t x) { return (float)(x >> 8) * 5
 
 // A compressed aggregate's field: the binary16 number in the low 16 bits, as a float.
 __device__ __forceinline__ float h16(uint32_t bits) { return (float)__builtin_bit_cast(_Float16, (uint16_t)bits); }
-typedef uint32_t sbh_u32x4v __attribute__((ext_vector_type(4)));
-// 16 bytes (16-byte aligned): adjacent loads of a block merge into one wide scalar load
-__device__ __forceinline__ sbh_u32x4v gld4u(const uint32_t* p) { return *(const SBH_GLOBAL sbh_u32x4v*)p; }
-
-__device__ __forceinline__ sbh_u32x4v cld4u(const uint32_t* p) { return *(const SBH_CONSTANT sbh_u32x4v*)(uintptr_t)p; }
 
 // SOFT: the potential with eps^2 >= FLT_MIN.
 template <int D, int K, bool TRACE, bool CMP = false, bool SOFT = false>
@@ -488,7 +483,7 @@ __global__ void __launch_bounds__(256) k_sbh_pool(TreeView tv, const float* __re
                 // (a reload is another gather per lane), and a compressed block's codes arrive with
                 // them, so decoding the selected child waits on no further load
                 uint32_t cn[KEEPN ? D3 : 1];
-                sbh_u32x4v cb[CMP ? D3 / 2 : 1];
+                sbh_u32x4 cb[CMP ? D3 / 2 : 1];
                 auto count = [&](int c) -> uint32_t {
                     if constexpr (KEEPN) return cn[c];
                     else return gld(bt + c);
@@ -962,7 +957,7 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
             // as eight bits for the swap
             static_assert(D3 == 512, "eight slots per lane");
             const int ln = threadIdx.x & 63;
-            const sbh_u32x4v c0 = gld4u(bt + 8 * ln), c1 = gld4u(bt + 8 * ln + 4);
+            const sbh_u32x4 c0 = gld4u(bt + 8 * ln), c1 = gld4u(bt + 8 * ln + 4);
             const uint32_t cl[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
             const bool deeper = level < lvl_int;
             uint32_t tot = 0u, nin = 0u;
@@ -1268,7 +1263,7 @@ __device__ __forceinline__ float wave_path_q(const TreeView& tv, float qx, float
             // contribution swap, Eq. (6): the selected child's term opens the sum
             const float tC = term_r2<K>(make_float4(0.f, 0.f, 0.f, mC), zero4, cx, cy, cz, r2C, kp, r0);
             float sumc = tC;
-            sbh_u32x4v cb[D3 / 2];   // the block's codes: slot c in words 2c, 2c + 1
+            sbh_u32x4 cb[D3 / 2];   // the block's codes: slot c in words 2c, 2c + 1
 #pragma unroll
             for (int i = 0; i < D3 / 2; ++i) cb[i] = gld4u(bqw + 4 * i);
             const uint32_t rest = nonempty & ~(1u << csel);

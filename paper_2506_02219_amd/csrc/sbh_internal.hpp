@@ -67,6 +67,9 @@ __device__ __forceinline__ float4 gld4(const float4* p)
     const sbh_f32x4 v = *(const SBH_GLOBAL sbh_f32x4*)p;
     return make_float4(v.x, v.y, v.z, v.w);
 }
+typedef uint32_t sbh_u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes (16-byte aligned): adjacent loads of a block merge into one wide scalar load
+__device__ __forceinline__ sbh_u32x4 gld4u(const uint32_t* p) { return *(const SBH_GLOBAL sbh_u32x4*)p; }
 __device__ __forceinline__ float gld(const float* p) { return *(const SBH_GLOBAL float*)p; }
 __device__ __forceinline__ uint32_t gld(const uint32_t* p) { return *(const SBH_GLOBAL uint32_t*)p; }
 // The same from the constant address space: a tree does not change while a
@@ -321,8 +324,7 @@ __device__ __forceinline__ float smooth_shift(const TreeView& tv, float qx, floa
         float best = INFINITY;
         uint32_t pre = 0u, pre_b = 0u, n_b = 0u;
         int c_b = 0, nint = 0, nint_b = 0;
-        for (int c = 0; c < D3; ++c) {
-            const uint32_t cnt = gld(bt + c);
+        auto child = [&](int c, uint32_t cnt) {
             const int ix = digit_axis(c, 0), iy = digit_axis(c, 1), iz = digit_axis(c, 2);
             const float d2 = dd[0][ix] + dd[1][iy] + dd[2][iz];
             if (cnt != 0u && d2 < best) {
@@ -334,6 +336,19 @@ __device__ __forceinline__ float smooth_shift(const TreeView& tv, float qx, floa
             }
             nint += ((int)cnt > tv.leaf_size && level + 1 < tv.max_level) ? 1 : 0;
             pre += cnt;
+        };
+        if constexpr (D < 8) {   // (up to sixteen counts on their way together: one at a time, their waits are the descent)
+            constexpr int B = D3 < 16 ? D3 : 16;
+#pragma unroll
+            for (int c0 = 0; c0 < D3; c0 += B) {
+                sbh_u32x4 n4[B / 4];
+#pragma unroll
+                for (int i = 0; i < B / 4; ++i) n4[i] = gld4u(bt + c0 + 4 * i);
+#pragma unroll
+                for (int i = 0; i < B; ++i) child(c0 + i, n4[i / 4][i % 4]);
+            }
+        } else {
+            for (int c = 0; c < D3; ++c) child(c, gld(bt + c));
         }
         const int ix = digit_axis(c_b, 0), iy = digit_axis(c_b, 1), iz = digit_axis(c_b, 2);
         cl[0] += (float)ix * hs;
