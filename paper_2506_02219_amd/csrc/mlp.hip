@@ -647,28 +647,28 @@ __device__ __forceinline__ double add_term64(double acc, float4 p, float4 dp, do
 // aggregate term, normalised.  The nodes of a path are nested, so only the
 // children that the path does not enter are summed over their points (every
 // point of the subdomain once); the sum of an entered child is that of its own
-// children.  A large child is shared by the workgroup's wavefronts, a small
-// one (most of them) is one wavefront's, and the partial sums, one per
-// wavefront, are added in wavefront order.  Path p = 8 j + slot is workgroup p,
+// children.  A large child is shared by the workgroup's wavefronts in eight
+// parts, a small one (most of them) is one wavefront's, and the partial sums are
+// added in the parts' order, whoever took them.  Path p = 8 j + slot is workgroup p,
 // which the round-robin dispatch gives to die p mod 8: each die's L2 keeps one
 // subdomain's points for every query (2^20 points: 2 MB of 4).  Float64
 // arithmetic and those reads bound it; a workgroup per row, summing every row
 // anew with a square root, a division and eight range tests a point, left most
 // of the chip to a few rows near the root: 6.5 ms for 512 queries on 2^20
 // points, now 0.5 ms (17 float64 instructions a point, 76% of the issue slots).
-constexpr int kTgWaves = 8;
+constexpr int kTgParts = 8;             // parts of a shared child
 constexpr int kTgMaxRows = 20;          // internal nodes on a path: at most the tree's levels
 constexpr uint32_t kTgShared = 2048;    // points from which a child is shared by the wavefronts
 
-template <int K, bool SOFT>
-__global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, const float* __restrict__ queries,
-                                                               int lmax, const int4* __restrict__ loc, double eps2,
-                                                               double alpha, float* __restrict__ Tg)
+template <int K, bool SOFT, int NW>
+__global__ void __launch_bounds__(64 * NW) k_mlp_targets(TreeView tv, const float* __restrict__ queries, int lmax,
+                                                         const int4* __restrict__ loc, double eps2, double alpha,
+                                                         float* __restrict__ Tg)
 {
 #pragma clang fp contract(off)
     __shared__ int4 node[kTgMaxRows];                        // {children block, first point, points, level}
     __shared__ uint32_t first[kTgMaxRows][9];                // first point of each child, then the end
-    __shared__ double part[kTgMaxRows * 8][kTgWaves];
+    __shared__ double part[kTgMaxRows * 8][kTgParts];
     __shared__ double sums[kTgMaxRows][8], resid[kTgMaxRows][8];
     const int64_t path = blockIdx.x;
     const int64_t row0 = path * lmax, j = path / 8;
@@ -688,7 +688,7 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
         }
         first[threadIdx.x][8] = b;
     }
-    for (int i = threadIdx.x; i < rows * 8 * kTgWaves; i += 64 * kTgWaves) (&part[0][0])[i] = 0.0;
+    for (int i = threadIdx.x; i < rows * 8 * kTgParts; i += 64 * NW) (&part[0][0])[i] = 0.0;
     __syncthreads();
     // the child of row k that row k + 1 subdivides
     auto entered = [&](int k, int c) {
@@ -699,37 +699,39 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
         const int k = s >> 3, c = s & 7;
         const uint32_t b = __builtin_amdgcn_readfirstlane(first[k][c]), e = __builtin_amdgcn_readfirstlane(first[k][c + 1]);
         const bool shared = e - b >= kTgShared;
-        if (b == e || (!shared && s % kTgWaves != wv) || entered(k, c)) continue;
-        const uint32_t step = shared ? 64 * kTgWaves : 64;
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
-        uint32_t u = b + (shared ? 64u * wv : 0u);   // the wavefront's next 64 points
-        float4 p[4], m[4];                           // four loads in flight
-        for (; u + 3 * step + 64 <= e; u += 4 * step) {
+        if (b == e || (!shared && s % NW != wv) || entered(k, c)) continue;
+        const uint32_t step = shared ? 64 * kTgParts : 64;
+        for (int v = shared ? wv : 0; v < (shared ? kTgParts : 1); v += NW) {
+            double a[4] = {0.0, 0.0, 0.0, 0.0};
+            uint32_t u = b + 64u * v;   // the part's next 64 points
+            float4 p[4], m[4];          // four loads in flight
+            for (; u + 3 * step + 64 <= e; u += 4 * step) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    p[t] = (tv.pts + (u + t * step))[lane];
+                    m[t] = K == SBH_WINDING ? (tv.pdip + (u + t * step))[lane] : zero4;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
+            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
+                if (u + t * step + lane >= e) continue;
                 p[t] = (tv.pts + (u + t * step))[lane];
                 m[t] = K == SBH_WINDING ? (tv.pdip + (u + t * step))[lane] : zero4;
             }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
+            for (int t = 0; t < 4; ++t)
+                if (u + t * step + lane < e) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
+            double acc = (a[0] + a[1]) + (a[2] + a[3]);
+            for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+            if (lane == 0) part[s][v] = acc;
         }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (u + t * step + lane >= e) continue;
-            p[t] = (tv.pts + (u + t * step))[lane];
-            m[t] = K == SBH_WINDING ? (tv.pdip + (u + t * step))[lane] : zero4;
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (u + t * step + lane < e) a[t] = add_term64<K, SOFT>(a[t], p[t], m[t], qx, qy, qz, eps2, alpha);
-        double acc = (a[0] + a[1]) + (a[2] + a[3]);
-        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-        if (lane == 0) part[s][wv] = acc;
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < rows * 8; s += 64 * kTgWaves) {
+    for (int s = threadIdx.x; s < rows * 8; s += 64 * NW) {
         double t = part[s][0];
-        for (int v = 1; v < kTgWaves; ++v) t += part[s][v];
+        for (int v = 1; v < kTgParts; ++v) t += part[s][v];
         sums[s >> 3][s & 7] = t;
     }
     __syncthreads();
@@ -742,7 +744,7 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
                     sums[k][c] = t;
                 }
     __syncthreads();
-    for (int s = threadIdx.x; s < rows * 8; s += 64 * kTgWaves) {
+    for (int s = threadIdx.x; s < rows * 8; s += 64 * NW) {
         const int k = s >> 3, c = s & 7;
         double r = 0.0;
         if (first[k][c + 1] != first[k][c]) {
@@ -752,7 +754,7 @@ __global__ void __launch_bounds__(64 * kTgWaves) k_mlp_targets(TreeView tv, cons
         resid[k][c] = r;
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < lmax * 8; s += 64 * kTgWaves) {
+    for (int s = threadIdx.x; s < lmax * 8; s += 64 * NW) {
         const int k = s >> 3, c = s & 7;
         float t = 0.0f;   // rows past the end of the path
         if (k < rows) {
@@ -1361,6 +1363,21 @@ hipError_t launch_mlp_step(float* prm, float* state, const float* X, const float
     return hipGetLastError();
 }
 
+// Wavefronts of a path's workgroup: eight where paths are few and their children large, fewer where a path has
+// little to share and its workgroup's barriers are what it waits for. us with eight / four / two, winding: 16
+// queries on 2^20 sources, all levels 87 / 109 / 175; 512 on 2^20 711 / 692 / 747, on 200,000 239 / 200 / 198, on
+// 20,000 116 / 84 / 70; 2,000 on 300, the first level 108 / 72 / 53 (a workgroup of four per row before: 52); 100 on
+// 20,000 45 / 38 / 41, on 2^20 207 / 206 / 228.
+template <int K, bool SOFT>
+static void launch_mlp_targets(const TreeView& tv, unsigned paths, const float* q, int lmax, const int4* l, double eps2,
+                               double alpha, float* t, hipStream_t s)
+{
+    const bool small = tv.n_points < (1 << 17);
+    if (paths >= 4096 && small) k_mlp_targets<K, SOFT, 2><<<paths, 64 * 2, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+    else if (paths >= 4096 || (paths >= 512 && small)) k_mlp_targets<K, SOFT, 4><<<paths, 64 * 4, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+    else k_mlp_targets<K, SOFT, 8><<<paths, 64 * 8, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+}
+
 hipError_t launch_mlp_pairs(const sbh_tree_impl* t, const float* queries, int64_t nq, int lmax, uint64_t seed,
                             int kernel, float eps, float alpha, float* X, float* Tg, float* Cn, int4* loc,
                             hipStream_t s)
@@ -1378,10 +1395,10 @@ hipError_t launch_mlp_pairs(const sbh_tree_impl* t, const float* queries, int64_
         const float* q = queries + 3 * (p0 / 8);
         const int4* l = loc + p0 * lmax;
         float* t = Tg + 8 * p0 * lmax;
-        if (kernel == SBH_POTENTIAL && eps2 > 0.0) k_mlp_targets<SBH_POTENTIAL, true><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
-        else if (kernel == SBH_POTENTIAL) k_mlp_targets<SBH_POTENTIAL, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
-        else if (kernel == SBH_WINDING) k_mlp_targets<SBH_WINDING, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
-        else k_mlp_targets<SBH_SMOOTHDIST, false><<<paths, 64 * kTgWaves, 0, s>>>(tv, q, lmax, l, eps2, alpha, t);
+        if (kernel == SBH_POTENTIAL && eps2 > 0.0) launch_mlp_targets<SBH_POTENTIAL, true>(tv, paths, q, lmax, l, eps2, alpha, t, s);
+        else if (kernel == SBH_POTENTIAL) launch_mlp_targets<SBH_POTENTIAL, false>(tv, paths, q, lmax, l, eps2, alpha, t, s);
+        else if (kernel == SBH_WINDING) launch_mlp_targets<SBH_WINDING, false>(tv, paths, q, lmax, l, eps2, alpha, t, s);
+        else launch_mlp_targets<SBH_SMOOTHDIST, false>(tv, paths, q, lmax, l, eps2, alpha, t, s);
     }
     return hipGetLastError();
 }

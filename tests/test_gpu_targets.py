@@ -70,3 +70,20 @@ def test_targets_match_the_points(n, side, depth, kernel, eps):
         checked += 1
     assert checked >= 10
     assert (Tg[where[:, 0] < 0] == 0).all()
+
+
+@pytest.mark.parametrize("kernel,eps", [(0, 1e-3), (0, 0.0), (1, 1e-3), (2, 1e-3)])
+@pytest.mark.parametrize("n", [300, 40000, 150000])
+def test_same_targets_for_any_number_of_wavefronts(n, kernel, eps):
+    """Few and many queries take different numbers of wavefronts a path (40,000 points: children that the
+    wavefronts share and others): a row's targets are the same bit for bit."""
+    import paper_2506_02219_amd as P
+    rng = np.random.Generator(np.random.PCG64(n))
+    src = rng.random((n, 3)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(a.astype(np.float32)).cuda()
+    tree = P.sbh_build(dev(src), dev(rng.random(n) + 0.5), dev(rng.standard_normal((n, 3))))
+    q = dev(2 * rng.random((600, 3)) - 0.5)
+    whole = P.sbh_mlp_pairs(tree, q, kernel, seed=3, eps=eps, alpha=5.0)[1]
+    for m in (5, 100):   # rows are keyed by the query's index, so the first ones are the same
+        part = P.sbh_mlp_pairs(tree, q[:m].contiguous(), kernel, seed=3, eps=eps, alpha=5.0)[1]
+        assert torch.equal(whole[:len(part)].view(torch.int32), part.view(torch.int32))

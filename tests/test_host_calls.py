@@ -168,7 +168,7 @@ for d in (2, 4):
 def test_target_launches(lib):
     host_calls.run(lib, r'''
 t = build(5000, normals=True)
-H.stand_in_copy_args(7, 512)
+H.stand_in_copy_args(7, 0)
 for nq, depth in ((5, 3), ((1 << 20) - 1, 1), (1 << 20, 1), (1 << 21, 1), ((1 << 28) - 1, 1), (1 << 20, 20), (3000001, 7)):
     for kernel, eps in ((0, 1e-3), (0, 0.0), (1, 0.0), (2, 0.0)):
         o = P.EvalOpts(); L.sbh_eval_opts_default(C.byref(o)); o.eps = eps
@@ -176,12 +176,12 @@ for nq, depth in ((5, 3), ((1 << 20) - 1, 1), (1 << 20, 1), (1 << 21, 1), ((1 <<
         assert L.sbh_mlp_pairs(t, D, nq, kernel, 0, depth, C.byref(o), S1, D, D, D, D) == 0, (nq, depth, L.sbh_last_error())
         rows = of(log(False), "launch")
         path = 0
-        for i, r in enumerate(rows[1:]):             # (the first one walks the paths)
+        for i, r in list(enumerate(rows))[1:]:       # (the first one walks the paths)
             a = [H.stand_in_arg(7 * i + k) for k in range(7)]
             assert path % 8 == 0
             assert a[1] == D.value + 12 * (path // 8) and a[3] == D.value + 16 * depth * path
             assert a[6] == D.value + 32 * depth * path
-            path += r[2] // 512
+            path += r[2] // H.stand_in_block(i)
         assert path == 8 * nq, (path, nq)
 ''')
 
