@@ -159,6 +159,14 @@ std::unordered_map<void*, Block>& g_live = *new std::unordered_map<void*, Block>
 std::list<Block>& g_idle = *new std::list<Block>;   // oldest first
 size_t g_idle_bytes = 0;
 
+// the work before the block's last free is done (a query of work that is not leaves an error, taken back here)
+bool is_done(const Block& b)
+{
+    const hipError_t e = hipEventQuery(b.freed);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+}
+
 // back to the device in the order of s, after the work that uses the block and without waiting for it
 void release_block(const Block& b, hipStream_t s)
 {
@@ -172,7 +180,7 @@ void release_block(const Block& b, hipStream_t s)
 void limit_idle(size_t most, int device, hipStream_t s)
 {
     for (auto it = g_idle.begin(); g_idle_bytes > most && it != g_idle.end();) {
-        if (it->device != device || (it->stream != s && hipEventQuery(it->freed) != hipSuccess)) {
+        if (it->device != device || (it->stream != s && !is_done(*it))) {
             ++it;
             continue;
         }
@@ -180,7 +188,6 @@ void limit_idle(size_t most, int device, hipStream_t s)
         g_idle_bytes -= it->bytes;
         it = g_idle.erase(it);
     }
-    (void)hipGetLastError();   // an event that has not completed leaves hipErrorNotReady
 }
 
 bool capturing(hipStream_t s)
@@ -202,9 +209,8 @@ hipError_t block_alloc(void** p, size_t bytes, hipStream_t s)
     for (auto it = g_idle.begin(); it != g_idle.end(); ++it) {
         if (it->device != dev || it->bytes < bytes || it->bytes - bytes > it->bytes / 4) continue;
         if (best != g_idle.end() && best->bytes <= it->bytes) continue;
-        if (it->stream == s || hipEventQuery(it->freed) == hipSuccess) best = it;
+        if (it->stream == s || is_done(*it)) best = it;
     }
-    (void)hipGetLastError();   // an event that has not completed leaves hipErrorNotReady
     if (best != g_idle.end() && hipStreamWaitEvent(s, best->freed, 0) == hipSuccess) {
         g_live.emplace(best->p, *best);
         *p = best->p;

@@ -47,6 +47,7 @@ extern "C" {
 // --- for the test
 const char* stand_in_log() { return g_log.c_str(); }
 void stand_in_clear() { g_log.clear(); g_args.clear(); g_blocks.clear(); }
+void stand_in_error(int e) { g_error = e; }   // the runtime's last error
 void stand_in_events_done(int done) { g_done = done; }
 void stand_in_capture(void* stream) { g_capturing = stream; }
 void stand_in_refuse(int allocations) { g_refuse = allocations; }   // the next ones fail
@@ -77,7 +78,11 @@ int hipMallocAsync(void** p, size_t bytes, void* s)
 int hipFreeAsync(void* p, void* s) { note("free", p, 0, s); return 0; }
 int hipEventCreateWithFlags(void** e, unsigned) { *e = (void*)(g_event += 16); return 0; }
 int hipEventRecord(void* e, void* s) { note("record", e, 0, s); return 0; }
-int hipEventQuery(void*) { return g_done ? 0 : kNotReady; }
+int hipEventQuery(void*)
+{
+    if (!g_done) g_error = kNotReady;
+    return g_done ? 0 : kNotReady;
+}
 int hipEventSynchronize(void* e) { note("eventsync", e, 0, nullptr); return 0; }
 int hipEventDestroy(void* e) { note("destroy", e, 0, nullptr); return 0; }
 int hipStreamWaitEvent(void* s, void* e, unsigned) { note("wait", e, 0, s); return 0; }

@@ -151,6 +151,24 @@ assert all(r[3] == S2.value for r in of(rows, "free", "streamsync", "wait")) and
 ''')
 
 
+def test_release_leaves_the_last_error(lib):
+    """An error that the caller has not read yet is still there after a release; a release's own queries
+    leave none."""
+    host_calls.run(lib, r'''
+trees = [build() for _ in range(3)]
+H.stand_in_error(98)
+assert L.sbh_free_async(trees[0], S1) == 0
+assert H.hipGetLastError() == 98
+H.stand_in_events_done(0)
+assert L.sbh_free_async(trees[1], S2) == 0
+assert H.hipGetLastError() == 0
+H.stand_in_events_done(1)
+H.stand_in_error(98)
+assert L.sbh_free(trees[2]) == 0
+assert H.hipGetLastError() == 98
+''')
+
+
 def test_barnes_hut_launches(lib):
     host_calls.run(lib, r'''
 for d in (2, 4):
