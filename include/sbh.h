@@ -345,7 +345,7 @@ sbh_status sbh_mlp_train(float* params, float* adam_state, const float* features
  * callers that cannot allocate: code under HIP graph capture, tight serving
  * or training loops, harnesses that forbid hipMalloc.  Same arguments,
  * kernels and results (bit for bit) as sbh_mlp_train.  The workspace is a
- * static array in device memory of (SBH_NOALLOC_MAX_BATCH_ROWS / 64 + 1)
+ * static array in device memory of SBH_NOALLOC_MAX_BATCH_ROWS / 64
  * * 1616 floats (about 3.2 MiB), one copy per GPU, held until the process
  * ends; its address is looked up on the first call on each device.  The
  * workspace holds no state between calls (every word a call reads it has

@@ -52,10 +52,10 @@ std::mutex g_alloc_mu;
 sbh::Allocator g_alloc{nullptr, nullptr, nullptr};
 
 // The static workspace of sbh_mlp_train_noalloc: the partial gradients of one batch (one row of
-// 1616 floats per 64 rows, and one spare).  Every GPU the library runs on
-// holds its own copy until the process ends.  In host code `scratch` names a host-side stand-in,
-// not device memory: kernels get the per-device address that hipGetSymbolAddress returns.
-constexpr size_t kScratchFloats = (size_t)(SBH_NOALLOC_MAX_BATCH_ROWS / 64 + 1) * 1616;
+// 1616 floats per 64 rows).  Every GPU the library runs on holds its own copy until the process
+// ends.  In host code `scratch` names a host-side stand-in, not device memory: kernels get the
+// per-device address that hipGetSymbolAddress returns.
+constexpr size_t kScratchFloats = (size_t)(SBH_NOALLOC_MAX_BATCH_ROWS / 64) * 1616;
 static __device__ __align__(256) float scratch[kScratchFloats];
 
 constexpr int kMaxDevices = 64;
@@ -134,16 +134,17 @@ struct OnDevice {
 
 // The default allocator: blocks of hipMallocAsync memory, kept when they are freed and handed out again
 // in stream order.  (The pools behind hipMallocAsync unmap what is freed while the device is idle,
-// whatever their release threshold: 2.5 of the 5 ms of a 2^22-point build with its release.)  A freed block carries an
-// event recorded on the stream it was freed on; it is taken again when that event has completed, or by
-// the same stream, which waits for it (so that streams gain no dependency on one another), and for at
+// whatever their release threshold: 2.5 of the 5 ms of a 2^22-point build with its release.)  A freed block
+// carries an event recorded on the stream it was freed on; it is taken again when that event has completed,
+// or by the same stream, which waits for it (so that streams gain no dependency on one another), and for at
 // most a quarter less than its size.  Idle blocks hold at most kIdleBytes: beyond that the oldest go back
-// to the device, in stream order and without waiting for the GPU (a larger block is not kept at all), and
-// all of them go back when sbh_free or sbh_batch_free releases the last block in use, when the allocator is
-// set, or when an allocation fails; where no object is left, the training calls and a failed build keep
-// kKeptBytes at most (a batch of 8,192 rows takes 0.8 MB).  (sbh_free_async of the last tree leaves them: a
-// loop of builds would otherwise pay for their mapping each time.)  One lock guards the lists; nothing but
-// HIP calls is made under it.
+// to the device, in stream order and without waiting for the GPU (a larger block is not kept at all).  All
+// of them go back when sbh_free or sbh_batch_free releases the last block in use, when the allocator is
+// set, and when an allocation fails; where no object is left, the training calls and a failed build keep
+// kKeptBytes at most (a batch of 8,192 rows takes 0.8 MB).  sbh_free_async of the last tree leaves them: a
+// loop of builds would otherwise pay for their mapping each time.  Memory of a stream under capture stays
+// with the graph: it is allocated and freed by nodes of it.  One lock guards the lists; nothing but HIP
+// calls that do not wait is made under it.
 constexpr size_t kIdleBytes = (size_t)2 << 30;
 constexpr size_t kKeptBytes = (size_t)64 << 20;
 struct Block {
