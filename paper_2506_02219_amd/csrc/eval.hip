@@ -832,7 +832,7 @@ __device__ __forceinline__ float wave_path(const TreeView& tv, float qx, float q
     using Off = typename TreeOff<O64>::T;
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     // d = 4: each wavefront's row for the child block of the step; every kernel that walks
-    // paths runs at most four wavefronts per workgroup (256 threads), one row each
+    // them runs at most four wavefronts per workgroup (256 threads), one row each
     // (aggregates, then dipoles: one LDS address serves both)
     __shared__ float4 sblk[D == 4 ? 4 : 1][K == SBH_WINDING ? 2 : 1][64];
     // wavefront-uniform walk state

@@ -86,8 +86,8 @@ __device__ __forceinline__ uint32_t cld(const uint32_t* p) { return *(const SBH_
 __device__ __forceinline__ void gst(float* p, float v) { *(SBH_GLOBAL float*)p = v; }
 
 // Device memory of the library: one allocator pair (sbh_set_allocator), or
-// the default (api.hip).  Objects keep
-// the pair they were allocated with and release through it.
+// the default (api.hip).  Objects keep the pair they were allocated with and
+// release through it.
 struct Allocator {
     sbh_alloc_fn alloc;   // nullptr: the default
     sbh_free_fn free;
